@@ -14,11 +14,17 @@
 //
 // Many queries run in one launch, one workgroup each (the many-small-
 // problems shape of serving): P(q) is sorted into LDS together with the
-// members' current values; a gathered id is looked up there by binary search
-// and, when absent, read as d_s from global memory.  One wave recomputes one
-// member at a time, its rho values in registers (d_s <= 2048) or re-gathered
-// per probe of the h-index search (larger d_s).  Queries whose P(q) does not
-// fit the LDS table run one at a time through the global sweep kernels.
+// members' current values, with a bitmap of hashed ids in front: most
+// gathered ids lie outside P(q), and one LDS word tells so (then the value is
+// d_s from global memory) where the binary search took up to twelve dependent
+// reads.  One wave recomputes one member at a time, its rho values in
+// registers (4, 8, 16 or 32 per lane by d_s) or re-gathered per probe of the
+// h-index search (d_s > 2048).  After the first sweep only members that a
+// fallen neighbour may have pulled below their value run again (a byte each).
+// Queries go out heaviest first (by the query's own d_s) from one counter, so
+// that no workgroup starts a long one when the others are done.  Queries
+// whose P(q) does not fit the LDS table run one at a time through the global
+// sweep kernels.
 #include <limits.h>
 #include <string.h>
 
@@ -39,7 +45,8 @@ namespace {
 using namespace dev;
 
 constexpr int kEgoCap = 4096;      // members of P(q) held in LDS
-constexpr int kEgoThreads = 256;   // 4 waves
+constexpr int kEgoThreads = 512;   // 8 waves
+constexpr int kEgoBits = 15;       // bitmap of hashed members: 2^15 bits
 constexpr int kEgoWaves = kEgoThreads / kWave;
 
 struct EgoArgs {
@@ -54,7 +61,22 @@ struct EgoArgs {
   int32_t *sweeps;         // per query
   uint8_t *big;            // per query: 1 = run it through the fallback
   int32_t *not_converged;  // set when a query stopped at max_iters
+  const int64_t *order;    // queries, heaviest first
+  unsigned long long *head;  // next of them to run
 };
+
+// The tables of one workgroup: P(q) ascending, the members' values, the
+// bitmap, and the members to recompute.
+struct EgoLds {
+  int32_t mem[kEgoCap];
+  int32_t tl[kEgoCap];
+  uint32_t bits[1 << (kEgoBits - 5)];
+  uint8_t dirty[kEgoCap];
+};
+
+__device__ __forceinline__ uint32_t ego_hash(int32_t x) {
+  return ((uint32_t)x * 2654435761u) >> (32 - kEgoBits);
+}
 
 __device__ __forceinline__ int ego_find(const int32_t *mem, int np, int32_t x) {
   int lo = 0, hi = np;
@@ -68,24 +90,46 @@ __device__ __forceinline__ int ego_find(const int32_t *mem, int np, int32_t x) {
   return (lo < np && mem[lo] == x) ? lo : -1;
 }
 
+// Member number of r-clique x, -1 outside P(q).
+__device__ __forceinline__ int ego_member(const EgoLds &L, int np, int32_t x) {
+  const uint32_t h = ego_hash(x);
+  if (!((L.bits[h >> 5] >> (h & 31)) & 1u)) return -1;
+  return ego_find(L.mem, np, x);
+}
+
+__device__ __forceinline__ int32_t ego_load(const int32_t *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 // Current value of r-clique x: its LDS slot when x is in P(q), else d_s.
-__device__ __forceinline__ int32_t ego_val(const int32_t *mem, int32_t *tl,
-                                           int np, const int32_t *ds,
-                                           int32_t x) {
-  const int p = ego_find(mem, np, x);
-  return p >= 0 ? __hip_atomic_load(&tl[p], __ATOMIC_RELAXED,
-                                    __HIP_MEMORY_SCOPE_WORKGROUP)
-                : ds[x];
+__device__ __forceinline__ int32_t ego_val(const EgoLds &L, int np,
+                                           const int32_t *ds, int32_t x) {
+  const int p = ego_member(L, np, x);
+  return p >= 0 ? ego_load(&L.tl[p]) : ds[x];
 }
 
 template <int K>
-__device__ __forceinline__ int32_t ego_rho(const EgoArgs &a, const int32_t *mem,
-                                           int32_t *tl, int np, int64_t j) {
+__device__ __forceinline__ int32_t ego_rho(const EgoArgs &a, const EgoLds &L,
+                                           int np, int64_t j) {
   const int32_t *q = a.inc_ids + (int64_t)K * j;
-  int32_t v = ego_val(mem, tl, np, a.ds, q[0]);
+  int32_t v = ego_val(L, np, a.ds, q[0]);
 #pragma unroll
-  for (int x = 1; x < K; x++) v = min(v, ego_val(mem, tl, np, a.ds, q[x]));
+  for (int x = 1; x < K; x++) v = min(v, ego_val(L, np, a.ds, q[x]));
   return v;
+}
+
+// H of one member with list [b, b + d), d <= 64 M, capped at its value c.
+template <int K, int M>
+__device__ __forceinline__ int32_t ego_h(const EgoArgs &a, const EgoLds &L, int np,
+                                         int64_t b, int64_t d, int32_t c) {
+  int32_t rho[M];
+#pragma unroll
+  for (int m = 0; m < M; m++) {
+    const int64_t j = lane_id() + (int64_t)m * kWave;
+    rho[m] = j < d ? ego_rho<K>(a, L, np, b + j) : -1;
+  }
+  const int cnt = count_ge<kWave, M>(rho, c);
+  return cnt >= c ? c : hindex_search<kWave, M>(rho, c);
 }
 
 __device__ __forceinline__ int wave_sum(int x) {
@@ -114,14 +158,48 @@ __device__ void block_bitonic(int32_t *v, int n) {
   }
 }
 
+// Queries in classes of their d_s (powers of two), largest first: one
+// workgroup counts the classes and deals the queries out.
+__global__ __launch_bounds__(1024) void k_ego_order(EgoArgs a, int64_t *order) {
+  __shared__ unsigned long long at[32];
+  const int t = threadIdx.x;
+  if (t < 32) at[t] = 0;
+  if (t == 0) *a.head = 0;
+  __syncthreads();
+  auto cls = [&](int64_t i) {
+    const int32_t d = a.ds[a.inv[a.queries[i]]];
+    return d < 1 ? 31 : __clz(d);  // 0..30: fewer leading zeros, larger d_s
+  };
+  for (int64_t i = t; i < a.count; i += 1024) atomicAdd(&at[cls(i)], 1ull);
+  __syncthreads();
+  if (t == 0) {
+    unsigned long long run = 0;
+    for (int c = 0; c < 32; c++) {
+      const unsigned long long n = at[c];
+      at[c] = run;
+      run += n;
+    }
+  }
+  __syncthreads();
+  for (int64_t i = t; i < a.count; i += 1024)
+    order[atomicAdd(&at[cls(i)], 1ull)] = i;
+}
+
 template <int K>
 __global__ __launch_bounds__(kEgoThreads) void k_ego(EgoArgs a) {
-  __shared__ int32_t mem[kEgoCap];
-  __shared__ int32_t tl[kEgoCap];
+  __shared__ EgoLds L;
   __shared__ int32_t wsum[kEgoWaves];
   __shared__ int s_np, s_changed;
+  __shared__ unsigned long long s_next;
+  int32_t *mem = L.mem, *tl = L.tl;
   const int t = threadIdx.x, lane = lane_id(), w = t / kWave;
-  for (int64_t qi = blockIdx.x; qi < a.count; qi += gridDim.x) {
+  while (true) {  // until the counter has passed the last query
+    if (t == 0) s_next = atomicAdd(a.head, 1ull);
+    __syncthreads();
+    const int64_t nx = (int64_t)s_next;
+    __syncthreads();
+    if (nx >= a.count) return;  // uniform over the block
+    const int64_t qi = a.order[nx];
     const int32_t R0 = a.inv[a.queries[qi]];
     const int64_t b0 = a.inc_off[R0];
     const int64_t d0 = a.inc_off[R0 + 1] - b0;
@@ -139,6 +217,7 @@ __global__ __launch_bounds__(kEgoThreads) void k_ego(EgoArgs a) {
     for (int i = t; i < n2; i += kEgoThreads)
       mem[i] = i == 0 ? R0 : (i < nraw ? a.inc_ids[(int64_t)K * b0 + i - 1]
                                        : INT_MAX);
+    for (int i = t; i < (1 << (kEgoBits - 5)); i += kEgoThreads) L.bits[i] = 0;
     __syncthreads();
     block_bitonic(mem, n2);
     // drop repeats (none arise from a simple graph, kept for safety): keep
@@ -167,7 +246,13 @@ __global__ __launch_bounds__(kEgoThreads) void k_ego(EgoArgs a) {
     const int np = s_np;
     for (int i = t; i < np; i += kEgoThreads) mem[i] = tl[i];
     __syncthreads();
-    for (int i = t; i < np; i += kEgoThreads) tl[i] = a.ds[mem[i]];
+    for (int i = t; i < np; i += kEgoThreads) {
+      const int32_t x = mem[i];
+      const uint32_t h = ego_hash(x);
+      atomicOr(&L.bits[h >> 5], 1u << (h & 31));
+      tl[i] = a.ds[x];
+      L.dirty[i] = 1;
+    }
     __syncthreads();
 
     int sweeps = 0;
@@ -176,27 +261,35 @@ __global__ __launch_bounds__(kEgoThreads) void k_ego(EgoArgs a) {
       if (t == 0) s_changed = 0;
       __syncthreads();
       for (int i = w; i < np; i += kEgoWaves) {
+        // The mark is cleared before the values are read: a neighbour that
+        // falls after that marks this member again (it stores its value
+        // first, and one CU's LDS serves accesses in order).
+        if (__hip_atomic_load(&L.dirty[i], __ATOMIC_RELAXED,
+                              __HIP_MEMORY_SCOPE_WORKGROUP) == 0)
+          continue;  // uniform over the wave
+        if (lane == 0)
+          __hip_atomic_store(&L.dirty[i], (uint8_t)0, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_WORKGROUP);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
         const int32_t R = mem[i];
         const int64_t b = a.inc_off[R];
         const int64_t d = a.inc_off[R + 1] - b;
-        const int32_t c = __hip_atomic_load(&tl[i], __ATOMIC_RELAXED,
-                                            __HIP_MEMORY_SCOPE_WORKGROUP);
+        const int32_t c = ego_load(&tl[i]);
         int32_t h;
-        if (d <= (int64_t)kWave * 32) {
-          int32_t rho[32];
-#pragma unroll
-          for (int m = 0; m < 32; m++) {
-            const int64_t j = lane + (int64_t)m * kWave;
-            rho[m] = j < d ? ego_rho<K>(a, mem, tl, np, b + j) : -1;
-          }
-          const int cnt = count_ge<kWave, 32>(rho, c);
-          h = cnt >= c ? c : hindex_search<kWave, 32>(rho, c);
+        if (d <= (int64_t)kWave * 4) {
+          h = ego_h<K, 4>(a, L, np, b, d, c);
+        } else if (d <= (int64_t)kWave * 8) {
+          h = ego_h<K, 8>(a, L, np, b, d, c);
+        } else if (d <= (int64_t)kWave * 16) {
+          h = ego_h<K, 16>(a, L, np, b, d, c);
+        } else if (d <= (int64_t)kWave * 32) {
+          h = ego_h<K, 32>(a, L, np, b, d, c);
         } else {
           // long list: count #{rho >= x} by a fresh pass per probe
           auto count = [&](int32_t x) {
             int n = 0;
             for (int64_t j = lane; j < d; j += kWave)
-              n += ego_rho<K>(a, mem, tl, np, b + j) >= x;
+              n += ego_rho<K>(a, L, np, b + j) >= x;
             return wave_sum(n);
           };
           if (count(c) >= c) {
@@ -213,10 +306,21 @@ __global__ __launch_bounds__(kEgoThreads) void k_ego(EgoArgs a) {
             h = l;
           }
         }
-        if (lane == 0 && h != c) {
-          __hip_atomic_store(&tl[i], h, __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_WORKGROUP);
-          s_changed = 1;
+        if (h != c) {  // uniform over the wave
+          if (lane == 0) {
+            __hip_atomic_store(&tl[i], h, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+            s_changed = 1;
+          }
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+          // members above h may have lost this s-clique (one at or below h
+          // has not)
+          for (int64_t j = (int64_t)K * b + lane; j < (int64_t)K * (b + d); j += kWave) {
+            const int p = ego_member(L, np, a.inc_ids[j]);
+            if (p >= 0 && ego_load(&tl[p]) > h)
+              __hip_atomic_store(&L.dirty[p], (uint8_t)1, __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+          }
         }
       }
       __syncthreads();
@@ -289,8 +393,16 @@ nd_status ego_estimate(nd_graph *g, nd_kind kind, const int32_t *queries,
   a.sweeps = dsw.p;
   a.big = big.p;
   a.not_converged = flags.p + 1;
+  DArr<int64_t> order(al, count);
+  DArr<unsigned long long> head(al, 1);
+  a.order = order.p;
+  a.head = head.p;
+  k_ego_order<<<1, 1024, 0, s>>>(a, order.p);
+  ND_LAUNCHED();
+  // as many workgroups as stay resident (4 per CU by LDS); the counter deals
+  // out the rest
   const unsigned grid =
-      (unsigned)std::min<int64_t>(count, (int64_t)g->ctx->num_cu * 8);
+      (unsigned)std::min<int64_t>(count, (int64_t)g->ctx->num_cu * 4);
   switch (ks.k) {
     case 1: k_ego<1><<<grid, kEgoThreads, 0, s>>>(a); break;
     case 2: k_ego<2><<<grid, kEgoThreads, 0, s>>>(a); break;

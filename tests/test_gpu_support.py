@@ -1,0 +1,103 @@
+"""The sweeps' mappings at the edges of their list-length ranges, with and
+without notifications: every SND iterate and the AND result against the CPU
+oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from synth import RawGraph
+
+pytestmark = pytest.mark.gpu
+
+# list lengths around one lane, one wave row, a wave's list, a workgroup
+EDGES = (1, 4, 5, 15, 16, 17, 63, 64, 65, 255, 256, 257, 511, 513, 1023, 1024,
+         1025, 2047, 2048, 2049, 4097, 6500)
+
+
+def _wheels(rims, per=2, seed=3):
+    """Hubs with exactly the given numbers of neighbours: per hub a rim of
+    that size whose vertices form a random graph of mean degree about 10, and
+    `per` hubs share a rim, so that hubs see each other's rims fall."""
+    rng = np.random.default_rng(seed)
+    src, dst, base = [], [], 0
+    for r in rims:
+        hubs = np.arange(base, base + per)
+        rim = np.arange(base + per, base + per + r)
+        for h in hubs:
+            src.append(np.full(r, h))
+            dst.append(rim)
+        m = 5 * r
+        src.append(rng.choice(rim, m))
+        dst.append(rng.choice(rim, m))
+        base += per + r
+    return RawGraph(base, np.concatenate(src).astype(np.int32),
+                    np.concatenate(dst).astype(np.int32), "wheels")
+
+
+def _chain(n, seed):
+    """A long ladder hung on a clique: values fall one step per sweep from the
+    far end on, for many sweeps with few r-cliques each."""
+    i = np.arange(n - 2)
+    src = np.concatenate([i, i, np.repeat(np.arange(n, n + 9), 9)])
+    dst = np.concatenate([i + 1, i + 2, np.tile(np.arange(n, n + 9), 9)])
+    src = np.append(src, [0, 1])
+    dst = np.append(dst, [n, n + 1])
+    perm = np.random.default_rng(seed).permutation(n + 9)
+    return RawGraph(n + 9, perm[src].astype(np.int32), perm[dst].astype(np.int32),
+                    "chain")
+
+
+GRAPHS = {"wheels": lambda: _wheels(EDGES), "wheels1": lambda: _wheels(EDGES, 1, 4),
+          "chain": lambda: _chain(700, 2)}
+KINDS = {"core": (1, 2), "truss": (2, 3)}
+
+
+@pytest.mark.parametrize("kind", list(KINDS))
+@pytest.mark.parametrize("name", list(GRAPHS))
+@pytest.mark.parametrize("switch", ["0", "2", "8"])
+def test_iterates_at_list_edges(monkeypatch, name, kind, switch):
+    import torch
+    import paper_1704_00386_amd as nd
+    monkeypatch.setenv("ND_FRONTIER_SWITCH", switch)
+    raw = GRAPHS[name]()
+    r, s = KINDS[kind]
+    og = oracle.Graph.from_raw(raw)
+    seq = og.snd(r, s)
+    ctx = nd.Context(0)
+    g = nd.Graph.from_edges(ctx, raw.n, torch.from_numpy(raw.src),
+                            torch.from_numpy(raw.dst))
+    for frontier in (False, True):
+        its = []
+        _, res = g.decompose(kind, "snd", use_frontier=frontier, keep_iterates=its)
+        assert res["sweeps"] == len(seq) - 1
+        for t, (changed, tau) in enumerate(its, start=1):
+            assert np.array_equal(tau.cpu().numpy(), seq[t]), (frontier, t)
+            assert changed == int((seq[t] != seq[t - 1]).sum())
+        # chunks of sweeps, as without a callback
+        kappa, res = g.decompose(kind, "snd", use_frontier=frontier)
+        assert np.array_equal(kappa.cpu().numpy(), seq[-1])
+        assert res["sweeps"] == len(seq) - 1
+        kappa, _ = g.decompose(kind, "and", use_frontier=frontier)
+        assert np.array_equal(kappa.cpu().numpy(), seq[-1])
+
+
+def test_noalloc_without_room_for_support_counts():
+    """A decomposition whose flags fit the static workspace while slack words
+    and counters do not runs on flags, with the same result."""
+    import torch
+    import paper_1704_00386_amd as nd
+    n = 30_000_000  # 8-bit values: 4 bytes a vertex with flags, 5 without
+    small = _chain(700, 5)
+    step = n // (small.n + 1)
+    src, dst = small.src.astype(np.int64) * step, small.dst.astype(np.int64) * step
+    ctx = nd.Context(0)
+    g = nd.Graph.from_edges(ctx, n, torch.from_numpy(src.astype(np.int32)),
+                            torch.from_numpy(dst.astype(np.int32)))
+    g.prepare("core")
+    out = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+    _, res = g.decompose("core", "snd", use_frontier=True, out=out, noalloc=True)
+    want = oracle.Graph.from_raw(small).snd(1, 2)
+    assert res["sweeps"] == len(want) - 1 and res["tau_bytes"] == 1
+    got = out.cpu().numpy()
+    assert np.array_equal(got[np.arange(small.n) * step], want[-1])
+    assert int((got != 0).sum()) == int((want[-1] != 0).sum())
