@@ -285,7 +285,9 @@ nd_status nd_decompose(nd_graph *g, nd_kind kind, const nd_opts *opts,
  *     about (2b + 2)|R| bytes for SND with notifications (b = bytes per tau,
  *     nd_result.tau_bytes; b|R| fewer for AND, 2|R| fewer without flags),
  *     plus 4|R| with on_iter and 4|R| for a host kappa; a decomposition
- *     that does not fit fails with ND_ERR_OOM before running anything;
+ *     that does not fit fails with ND_ERR_OOM before running anything (with
+ *     (3b + 2c)|R| bytes of room, c = 1, 2 or 4 bytes per counter, the
+ *     notifications also count what each r-clique lost, and fewer run);
  *   - the call allocates no device or host memory.
  * Every call on a device shares that device's workspace, whose contents
  * persist between calls: calls that overlap in time on one device (other

@@ -26,6 +26,11 @@ CEIL_SRC = "ceiling.hip"
 SOURCES = ["api.hip", "prim.hip", "graph.hip", "cliques.hip", "layout.hip",
            "sweep.hip", "driver.hip", "partial.hip", "levels.hip", "batch.hip", "server.hip"]
 
+# sweep_inst.hip once per k = C(s,r) - 1 and type of tau
+SWEEP_SRC = "sweep_inst.hip"
+SWEEP_OBJS = [(f"sweep_k{k}_{t}", [f"-DND_SWEEP_K={k}", f"-DND_SWEEP_T={t}"])
+              for k in (5, 3, 2, 1) for t in ("int32_t", "uint16_t", "uint8_t")]
+
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 FLAGS = [
@@ -36,9 +41,9 @@ FLAGS = [
 ]
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
-    cmd = [HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+def _compile(src: str, name: str = "", defs=()) -> str:
+    obj = os.path.join(OBJ, (name or os.path.splitext(src)[0]) + ".o")
+    cmd = [HIPCC, *FLAGS, *defs, "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed on {src}:\n{r.stderr}")
@@ -61,9 +66,14 @@ def build(jobs: int | None = None) -> str:
     os.makedirs(OBJ, exist_ok=True)
     jobs = jobs or min(8, os.cpu_count() or 1)
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
-        objs = list(ex.map(_compile, SOURCES + [CEIL_SRC]))
-    _link(objs[:-1], LIB)
-    _link(objs[-1:], CEIL_LIB)
+        # the longest first
+        lib = [ex.submit(_compile, "batch.hip")]
+        lib += [ex.submit(_compile, SWEEP_SRC, n, d) for n, d in SWEEP_OBJS]
+        lib += [ex.submit(_compile, s) for s in SOURCES if s != "batch.hip"]
+        ceil = ex.submit(_compile, CEIL_SRC)
+        objs, ceil_obj = [f.result() for f in lib], ceil.result()
+    _link(objs, LIB)
+    _link([ceil_obj], CEIL_LIB)
     return LIB
 
 

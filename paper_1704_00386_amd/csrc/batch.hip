@@ -225,7 +225,7 @@ template <int K, typename T, bool AND, bool FR>
 __global__ __launch_bounds__(kBlockThreads) void k_batch_hubs(
     const BGraph *__restrict__ gs, const BHub *__restrict__ hubs,
     const BState *__restrict__ st) {
-  __shared__ int32_t hist[kBlockHistBins];
+  __shared__ HubLds L;
   const int64_t e = st->epoch;
   const int nhubs = st->nhubs;
   for (int i = blockIdx.x; i < nhubs; i += gridDim.x) {
@@ -240,11 +240,11 @@ __global__ __launch_bounds__(kBlockThreads) void k_batch_hubs(
     uint8_t *act_next, *sum_next, stamp;
     graph_frontier<FR>(G, local, sst, &act, &act_next, &stamp, &act_sum,
                        &sum_next);
-    bool ev;
-    const bool ch = update_block<K, T, AND, FR>(G.inc_off, G.inc_ids, in, out,
-                                                1, hb.R, hist, act, act_next,
-                                                stamp, &ev, sum_next);
-    stat_add(sst, ch, ev);
+    if (FR && act != nullptr && act[hb.R] != stamp) continue;
+    const bool ch = update_hub<K, T, AND, FR>(G.inc_off, G.inc_ids, in, out, 1,
+                                              hb.R, L, act_next, stamp, sum_next,
+                                              Support());
+    stat_add(sst, ch, threadIdx.x == 0);
   }
 }
 

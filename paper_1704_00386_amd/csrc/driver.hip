@@ -35,6 +35,14 @@ static_assert(kMaxChunk < kStaticRing && kStaticRing <= kHostStatsRing &&
                   kStatsRing <= kHostStatsRing,
               "a chunk and its predecessor must fit every counter ring");
 constexpr int64_t kSumsDiv = 256;  // see sums_after in sweep_loop
+// Sparse sweeps spread their r-cliques over the waves after a sweep that
+// changed fewer than this: a few per wave then, and clusters of them on one
+// wave are what such a sweep waits for (86,000-edge k-truss 746 -> 636 us,
+// late sweeps of the Chung-Lu k-truss 0.15 -> 0.06 ms).  With 1.4 million
+// changed of the (3,4) block model's 4e8, neighbours on one wave share lines:
+// 1.6 ms a sweep side by side, 1.9 spread.
+constexpr unsigned long long kSpreadBelow = 1 << 15;
+constexpr int64_t kWatchGathers = (int64_t)1 << 26;  // see watch in sweep_loop
 constexpr int kGridPerCu = 64;    // sweep workgroups per CU (they stride;
                                   // measured best of 8..64 and uncapped)
 
@@ -106,6 +114,9 @@ struct LoopBufs {
   void *tau[2] = {nullptr, nullptr};  // AND: both the same array
   uint8_t *act[2] = {nullptr, nullptr};      // flags (stamps)
   uint8_t *act_sum[2] = {nullptr, nullptr};  // one stamp per 64 r-cliques
+  // support counting (or NULL); its counters replace the flags: act = lost
+  uint8_t *slack = nullptr;
+  uint8_t *lost[2] = {nullptr, nullptr};
   SweepStats *ring = nullptr;
   int ring_len = 0;
   int32_t *snap = nullptr;   // on_iter: tau_t in r-clique-id order
@@ -136,12 +147,21 @@ bool wants_indicator(const nd_opts &o, bool fixed_set) {
   return !fixed_set && (o.count_active != 0 || o.stop_active_ratio > 0);
 }
 
+// Bytes (log2) of a lost-s-clique counter: at most k d_s are counted for one
+// r-clique in one sweep.
+int lost_shift(const KindState &ks) {
+  const int64_t most = (int64_t)ks.k * ks.max_ds;
+  return most <= 255 ? 0 : most <= 65535 ? 1 : 2;
+}
+
 // Byte sizes of the buffers of a decomposition, each rounded to 256.
 struct LoopLayout {
   int64_t tau, flags, sums, ring, snap, stage;
+  int64_t slack, lost;  // support counting, which needs no flags
   int ntau;  // tau arrays: 2 for SND, 1 for AND (in place)
-  int64_t total() const {
-    return ntau * tau + 2 * flags + 2 * sums + ring + snap + stage;
+  int64_t total(bool support) const {
+    return ntau * tau + (support ? slack + 2 * lost : 2 * flags) + 2 * sums +
+           ring + snap + stage;
   }
 };
 int64_t round256(int64_t b) { return (std::max<int64_t>(b, 1) + 255) / 256 * 256; }
@@ -156,6 +176,13 @@ LoopLayout loop_layout(const KindState &ks, const nd_opts &o, bool flags,
   L.ring = round256((int64_t)sizeof(SweepStats) * ring_len);
   L.snap = o.on_iter ? round256(4 * nr) : 0;
   L.stage = on_device ? 0 : round256(4 * nr);
+  // Support counting skips flagged r-cliques whose value cannot change; with
+  // active counts taken, every flagged one runs (the counts are defined by
+  // what the notifications flag).
+  if (flags && o.use_frontier && !wants_indicator(o, false)) {
+    L.slack = round256(ks.tau_bytes * nr);
+    L.lost = round256(nr << lost_shift(ks));
+  }
   return L;
 }
 
@@ -186,7 +213,10 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
   unsigned long long notify_below = 0, sums_after = 0;
   if (flags) {
     for (int i = 0; i < 2; i++) {
-      fill_u8(b.act[i], 0, nr, s);  // no stamps yet
+      if (b.slack)
+        fill_u8(b.lost[i], 0, nr << lost_shift(ks), s);
+      else
+        fill_u8(b.act[i], 0, nr, s);  // no stamps yet
       fill_u8(b.act_sum[i], 0, ng, s);
     }
     const int div = frontier_switch(and_mode);
@@ -207,7 +237,15 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
   const int grid_per_cu =
       frontier ? grid_per_cu_frontier(ks.bin_lo[kBinZero], ctx->num_cu) : kGridPerCu;
   const bool step_by_step = opts.on_iter != nullptr || opts.stop_active_ratio > 0;
-  int chunk = step_by_step ? 1 : 2;
+  // Whether sweep t's predecessor, as read back, rules out that sweep t
+  // notifies: such a sweep runs as a plain one, on kernels without the
+  // frontier's registers (block model: 22.2 ms against 23.4 a full sweep).
+  // Where sweeps are long (2^26 gathers, about 0.3 ms), they are enqueued one
+  // by one until notifications start, so that all the plain ones are known;
+  // on shorter ones the round trip costs more than it saves.
+  bool plain = flags && !indicator;
+  const bool watch = plain && ks.P * ks.k >= kWatchGathers;
+  int chunk = step_by_step || watch ? 1 : 2;
   int64_t t = 0;  // sweeps enqueued
   int64_t sweeps = 0, updates = 0;
   bool converged = false, stop_ratio = false, stop_cb = false;
@@ -241,7 +279,7 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
       a.prev = t > 0 ? b.ring + ((t - 1) % ring_len) : nullptr;
       a.cap_by_tau = 1;
       a.grid_cap = ctx->num_cu * grid_per_cu;
-      if (flags) {
+      if (flags && !(plain && i == 0)) {
         a.act = b.act[t & 1];
         a.act_next = b.act[(t + 1) & 1];
         a.act_sum = b.act_sum[t & 1];
@@ -251,6 +289,11 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
         a.notify_first = indicator ? 1 : 0;
         a.flags_unused = frontier ? 0 : 1;
         a.sums_after = (frontier && !indicator) ? sums_after : 0;
+        a.spread_below = kSpreadBelow;
+        a.slack = b.slack;
+        a.lost = b.lost[t & 1];
+        a.lost_next = b.lost[(t + 1) & 1];
+        a.lost_shift = lost_shift(ks);
       } else if (fixed_set) {
         a.act = fixed_set;
         a.stamp = 1;
@@ -312,7 +355,15 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
       }
     }
     if (done) break;
-    chunk = std::min(chunk * 2, step_by_step ? 1 : kMaxChunk);
+    if (plain) {
+      const SweepStats &last = hst[(t - 1) % ring_len];
+      plain = !last.notified && last.changed_total() > notify_below;
+    }
+    // once few r-cliques change, notifications keep the summaries themselves
+    if (sums_after != 0 && hst[(t - 1) % ring_len].notified &&
+        hst[(t - 1) % ring_len].changed_total() < sums_after)
+      sums_after = 0;
+    chunk = std::min(chunk * 2, step_by_step || (watch && plain) ? 1 : kMaxChunk);
   }
   ND_HIP(hipEventRecord(ev[1], s));
   r.ms_iterate = elapsed_ms(ev[0], ev[1]);
@@ -372,6 +423,7 @@ nd_status decompose_impl(nd_graph *g, nd_kind kind, const nd_opts *opts_in,
       opts.use_frontier != 0 || wants_indicator(opts, fixed_set != nullptr);
   const LoopLayout L = loop_layout(ks, opts, flags, on_device != 0, kStatsRing);
   DArr<uint8_t> tau0(al, L.tau), tau1, act[2], sums[2], snap, stage;
+  DArr<uint8_t> slack, lost[2];
   DArr<uint8_t> ring(al, L.ring);
   LoopBufs b;
   b.tau[0] = b.tau[1] = tau0.p;
@@ -381,10 +433,24 @@ nd_status decompose_impl(nd_graph *g, nd_kind kind, const nd_opts *opts_in,
   }
   if (flags)
     for (int i = 0; i < 2; i++) {
-      act[i].reset(al, L.flags);
       sums[i].reset(al, L.sums);
-      b.act[i] = act[i].p;
       b.act_sum[i] = sums[i].p;
+    }
+  if (L.slack) {
+    try {
+      slack.reset(al, L.slack);
+      for (int i = 0; i < 2; i++) lost[i].reset(al, L.lost);
+      b.slack = slack.p;
+      for (int i = 0; i < 2; i++) b.act[i] = b.lost[i] = lost[i].p;
+    } catch (const Err &) {  // short of memory: flags alone take less
+      slack.free();
+      for (int i = 0; i < 2; i++) lost[i].free();
+    }
+  }
+  if (flags && !b.slack)
+    for (int i = 0; i < 2; i++) {
+      act[i].reset(al, L.flags);
+      b.act[i] = act[i].p;
     }
   b.ring = (SweepStats *)ring.p;
   b.ring_len = kStatsRing;
@@ -420,10 +486,13 @@ nd_status decompose_noalloc(nd_graph *g, nd_kind kind, const nd_opts *opts_in,
   }
   const bool flags = opts.use_frontier != 0 || wants_indicator(opts, false);
   const LoopLayout L = loop_layout(ks, opts, flags, on_device != 0, kStaticRing);
-  ND_REQUIRE(L.total() <= (int64_t)kNoallocWorkspaceBytes, ND_ERR_OOM,
+  const bool support =
+      L.slack > 0 && L.total(true) <= (int64_t)kNoallocWorkspaceBytes;
+  ND_REQUIRE(support || L.total(false) <= (int64_t)kNoallocWorkspaceBytes,
+             ND_ERR_OOM,
              "the decomposition needs %lld bytes of workspace; the static "
              "workspace holds %lld",
-             (long long)L.total(), (long long)kNoallocWorkspaceBytes);
+             (long long)L.total(false), (long long)kNoallocWorkspaceBytes);
   uint8_t *w = (uint8_t *)noalloc_workspace(g->ctx->device);
   ND_REQUIRE(w != nullptr, ND_ERR_DEVICE,
              "no static workspace on device %d", g->ctx->device);
@@ -435,9 +504,11 @@ nd_status decompose_noalloc(nd_graph *g, nd_kind kind, const nd_opts *opts_in,
   LoopBufs b;
   b.tau[0] = b.tau[1] = take(L.tau);
   if (opts.mode != ND_AND) b.tau[1] = take(L.tau);
+  if (support) b.slack = take(L.slack);
   if (flags)
     for (int i = 0; i < 2; i++) {
-      b.act[i] = take(L.flags);
+      b.act[i] = take(support ? L.lost : L.flags);
+      if (support) b.lost[i] = b.act[i];
       b.act_sum[i] = take(L.sums);
     }
   b.ring = (SweepStats *)take(L.ring);

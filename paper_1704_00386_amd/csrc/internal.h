@@ -133,6 +133,8 @@ namespace nd {
 // and zero-degree r-cliques (never swept) sit at the end.  Bins in internal
 // order, with their d_s ranges:
 enum SweepBin : int {
+  // (the one-graph sweeps give 1025 and up a workgroup, 257..1024 a wave with
+  // its values in LDS; the lanes below are the batches')
   kBinBlock = 0,  // d_s >= 2048:  one workgroup per r-clique, LDS histogram
   kBinWave,       // 1025..2047:   one wave, 32 values per lane in registers
   kBinWave16,     // 513..1024:    one wave, 16 values per lane
@@ -144,9 +146,6 @@ enum SweepBin : int {
   kBinZero,       // 0:            tau stays 0
   kNumBins
 };
-// kBinWave16 .. kBinG1: the bins swept by one launch (k_sweep_small)
-constexpr int kFirstSmall = kBinWave16;
-constexpr int kNumSmall = kBinZero - kFirstSmall;
 
 // Per-kind state of a graph: internal numbering, incidence lists, schedule.
 struct KindState {
@@ -345,6 +344,18 @@ struct SweepArgs {
   // 1: flags are written and counted but never used to skip r-cliques (the
   // active-ratio indicator without the frontier).
   int flags_unused;
+  // A sparse sweep after one that changed fewer r-cliques than this spreads
+  // them over its waves (see sweep_sparse).
+  unsigned long long spread_below;
+  // Support counting with the frontier (see Support in sweep_dev.h), all NULL
+  // when off: slack holds a tau-sized word per r-clique, lost / lost_next
+  // counters of 1 << lost_shift bytes (this sweep's, the next sweep's), which
+  // take the place of the flags (act and act_next then only say that there
+  // are notifications).
+  void *slack;
+  void *lost;
+  void *lost_next;
+  int lost_shift;
   // PartialAND (Section 4.3, end): act marks a fixed set (stamp 1) that is
   // the only thing recomputed, every sweep, and nothing notifies.
   int fixed_set;
