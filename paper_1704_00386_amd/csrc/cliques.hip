@@ -1964,20 +1964,38 @@ __global__ void k_degree(const int64_t *__restrict__ row_off, int32_t n,
   if (u < n) deg[u] = (int32_t)(row_off[u + 1] - row_off[u]);
 }
 
-// The neighbour list of vertex perm[i], re-indexed, at inc_off[i].
-template <int G>
-__global__ __launch_bounds__(256) void k_csr_fill(
-    const int64_t *__restrict__ row_off, const int32_t *__restrict__ col,
-    const int32_t *__restrict__ perm, const int32_t *__restrict__ inv,
-    const int64_t *__restrict__ off, int64_t lo, int64_t hi,
-    int32_t *__restrict__ out) {
-  const int sl = lane_id() % G;
-  const int64_t nsub = (int64_t)gridDim.x * blockDim.x / G;
-  for (int64_t i = lo + ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / G;
-       i < hi; i += nsub) {
-    const int32_t u = perm[i];
-    const int64_t b = row_off[u], d = row_off[u + 1] - b, o = off[i];
-    for (int64_t j = sl; j < d; j += G) out[o + j] = inv[col[b + j]];
+// How far the list of vertex u moves between the CSR and the internal order.
+__global__ void k_core_shift(const int64_t *__restrict__ row_off,
+                             const int32_t *__restrict__ inv,
+                             const int64_t *__restrict__ off, int32_t n,
+                             int64_t *__restrict__ shift) {
+  const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (u < n) shift[u] = off[inv[u]] - row_off[u];
+}
+
+// Every CSR entry, re-indexed, to its place in the internal order, in CSR
+// order whatever the degrees: the ids are read and written in runs, eight
+// entries a thread are in flight, and only the gather of inv is random (it
+// bounds the pass: one 4-byte word per 128-byte line, 8 TB/s of lines; 268
+// million entries in 4.2 ms, 5.0 with a wave or four lanes per list).
+constexpr int kCoreItems = 8;
+
+__global__ __launch_bounds__(256) void k_core_fill(
+    const int32_t *__restrict__ col, const int32_t *__restrict__ rowid,
+    const int32_t *__restrict__ inv, const int64_t *__restrict__ shift,
+    int64_t nnz, int32_t *__restrict__ out) {
+  const int64_t p0 = (int64_t)blockIdx.x * 256 * kCoreItems + threadIdx.x;
+  int32_t c[kCoreItems], r[kCoreItems];
+#pragma unroll
+  for (int k = 0; k < kCoreItems; k++) {
+    const int64_t p = p0 + k * 256;
+    c[k] = p < nnz ? col[p] : -1;
+    r[k] = p < nnz ? rowid[p] : 0;
+  }
+#pragma unroll
+  for (int k = 0; k < kCoreItems; k++) {
+    const int64_t p = p0 + k * 256;
+    if (c[k] >= 0) out[p + shift[r[k]]] = inv[c[k]];
   }
 }
 
@@ -1995,19 +2013,13 @@ void build_incidence_core(nd_graph *g, KindState &ks, hipStream_t s) {
   build_layout(g, ks, deg.p, s);
   deg.free();
   ks.inc_ids.reset(al, ks.P);
-  // high-degree vertices first in the internal order: a wave each; the rest
-  // four lanes each
-  const int64_t split = ks.bin_hi[kBinG64];
-  if (split > 0) {
-    k_csr_fill<64><<<grid_stride(split, 64), 256, 0, s>>>(
-        g->row_off.p, g->col.p, ks.perm.p, ks.inv.p, ks.inc_off.p, 0, split,
-        ks.inc_ids.p);
+  if (g->nnz > 0) {
+    DArr<int64_t> shift(al, n);
+    k_core_shift<<<grid_for(n, 256), 256, 0, s>>>(g->row_off.p, ks.inv.p,
+                                                   ks.inc_off.p, n, shift.p);
     ND_LAUNCHED();
-  }
-  if (n > split) {
-    k_csr_fill<4><<<grid_stride(n - split, 4), 256, 0, s>>>(
-        g->row_off.p, g->col.p, ks.perm.p, ks.inv.p, ks.inc_off.p, split, n,
-        ks.inc_ids.p);
+    k_core_fill<<<grid_for(g->nnz, 256 * kCoreItems), 256, 0, s>>>(
+        g->col.p, g->rowid.p, ks.inv.p, shift.p, g->nnz, ks.inc_ids.p);
     ND_LAUNCHED();
   }
 }

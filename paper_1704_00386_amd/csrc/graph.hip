@@ -38,25 +38,69 @@ __global__ void k_make_keys(const int32_t *__restrict__ src,
   keys[2 * i + 1] = k1;
 }
 
-__global__ void k_unique_flags(const uint64_t *__restrict__ keys, int64_t n,
-                               uint64_t sentinel, int32_t *__restrict__ flag) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  uint64_t k = keys[i];
-  flag[i] = (k != sentinel && (i == 0 || keys[i - 1] != k)) ? 1 : 0;
+// Entries of the graph among the sorted keys: the first of each run of equal
+// keys, sentinels excluded.  A workgroup takes 2048 consecutive keys, eight a
+// thread in rows of 256.  Two passes over the keys (count, then place), with
+// only the workgroups' counts scanned in between, move 24 bytes a key; flags
+// and positions kept per key moved 60.
+constexpr int kUniqueItems = 8;
+constexpr int kUniqueTile = 256 * kUniqueItems;
+
+__device__ __forceinline__ bool is_entry(const uint64_t *__restrict__ keys,
+                                         int64_t i, int64_t n,
+                                         uint64_t sentinel, uint64_t *key) {
+  if (i >= n) return false;
+  *key = keys[i];
+  return *key != sentinel && (i == 0 || keys[i - 1] != *key);
 }
 
-__global__ void k_compact(const uint64_t *__restrict__ keys, int64_t n, int bv,
-                          const int32_t *__restrict__ flag,
-                          const int64_t *__restrict__ pos,
-                          int32_t *__restrict__ col,
-                          int32_t *__restrict__ rowid) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n || !flag[i]) return;
-  uint64_t k = keys[i];
-  int64_t p = pos[i];
-  col[p] = (int32_t)(k & (((uint64_t)1 << bv) - 1));
-  rowid[p] = (int32_t)(k >> bv);
+__global__ __launch_bounds__(256) void k_unique_count(
+    const uint64_t *__restrict__ keys, int64_t n, uint64_t sentinel,
+    int32_t *__restrict__ count) {
+  __shared__ int32_t ws[4];
+  const int64_t base = (int64_t)blockIdx.x * kUniqueTile;
+  int c = 0;  // of the wave
+#pragma unroll
+  for (int r = 0; r < kUniqueItems; r++) {
+    uint64_t k;
+    c += __popcll(ballot(is_entry(keys, base + r * 256 + threadIdx.x, n, sentinel, &k)));
+  }
+  if (lane_id() == 0) ws[threadIdx.x / kWave] = c;
+  __syncthreads();
+  if (threadIdx.x == 0) count[blockIdx.x] = ws[0] + ws[1] + ws[2] + ws[3];
+}
+
+__global__ __launch_bounds__(256) void k_unique_place(
+    const uint64_t *__restrict__ keys, int64_t n, int bv, uint64_t sentinel,
+    const int64_t *__restrict__ off, int32_t *__restrict__ col,
+    int32_t *__restrict__ rowid) {
+  __shared__ int32_t ws[kUniqueItems][4];
+  const int64_t base = (int64_t)blockIdx.x * kUniqueTile;
+  const int w = threadIdx.x / kWave;
+  uint64_t key[kUniqueItems];
+  int at[kUniqueItems];  // rank in the wave's row, -1: no entry
+#pragma unroll
+  for (int r = 0; r < kUniqueItems; r++) {
+    const bool e = is_entry(keys, base + r * 256 + threadIdx.x, n, sentinel, &key[r]);
+    const uint64_t m = ballot(e);
+    at[r] = e ? lanes_below(m) : -1;
+    if (lane_id() == 0) ws[r][w] = __popcll(m);
+  }
+  __syncthreads();
+  int64_t p = off[blockIdx.x];
+#pragma unroll
+  for (int r = 0; r < kUniqueItems; r++) {
+    int64_t q = p;
+#pragma unroll
+    for (int x = 0; x < 4; x++) {
+      q += x < w ? ws[r][x] : 0;
+      p += ws[r][x];
+    }
+    if (at[r] >= 0) {
+      col[q + at[r]] = (int32_t)(key[r] & (((uint64_t)1 << bv) - 1));
+      rowid[q + at[r]] = (int32_t)(key[r] >> bv);
+    }
+  }
 }
 
 // row_off[x] = first entry whose row is >= x, for x in [0, n].
@@ -173,22 +217,22 @@ void build_from_edges(nd_graph *g, int64_t m, const int32_t *src,
   ND_REQUIRE(herr == 0, ND_ERR_INVALID,
              "edge list has an endpoint outside [0, %d)", n);
   uint64_t *sorted = radix_sort_u64(keys.p, tmp.p, nk, 0, total_bits, s, al);
-  DArr<int32_t> flag(al, nk);
-  DArr<int64_t> pos(al, nk + 1);
+  const int64_t ntile = ceil_div(nk, kUniqueTile);
+  DArr<int32_t> count(al, ntile);
+  DArr<int64_t> off(al, ntile + 1);
   if (nk > 0) {
-    k_unique_flags<<<grid_for(nk, 256), 256, 0, s>>>(sorted, nk, sentinel,
-                                                      flag.p);
+    k_unique_count<<<(unsigned)ntile, 256, 0, s>>>(sorted, nk, sentinel, count.p);
     ND_LAUNCHED();
   }
-  exclusive_scan_i32(flag.p, pos.p, nk, s, al);
-  const int64_t nnz = read_i64(pos.p + nk, s);
+  exclusive_scan_i32(count.p, off.p, ntile, s, al);
+  const int64_t nnz = read_i64(off.p + ntile, s);
   g->nnz = nnz;
   g->col.reset(al, nnz);
   g->rowid.reset(al, nnz);
   g->row_off.reset(al, (int64_t)n + 1);
   if (nk > 0) {
-    k_compact<<<grid_for(nk, 256), 256, 0, s>>>(sorted, nk, bv, flag.p, pos.p,
-                                                 g->col.p, g->rowid.p);
+    k_unique_place<<<(unsigned)ntile, 256, 0, s>>>(sorted, nk, bv, sentinel, off.p,
+                                                   g->col.p, g->rowid.p);
     ND_LAUNCHED();
   }
   k_row_off<<<grid_for((int64_t)n + 1, 256), 256, 0, s>>>(g->rowid.p, nnz, n,

@@ -230,25 +230,41 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_hist(
   hist[(int64_t)threadIdx.x * nb + blockIdx.x] = h[threadIdx.x];
 }
 
-// Stable scatter: keys of the tile are ranked in input order (round, wave,
-// lane); equal digits within a wave are matched with 8 ballots.
+// Stable scatter of one tile by one digit.  A wave ranks its own 1024
+// consecutive keys, 64 at a time: equal digits within the 64 are matched with
+// 8 ballots, a per-wave counter in LDS carries each digit's count on (one
+// wave's LDS accesses are served in order, so no barrier is needed).  Then
+// the tile's digit starts are scanned, the keys go to LDS in digit order, and
+// leave it in runs of consecutive addresses: bound by its 16 bytes a key.
+// (Storing each key straight to its place took three barriers per 256 keys
+// and wrote 8-byte pieces: 2.35 ms for 268 million keys, 1.8 TB/s; now 1.21
+// ms, 3.6 TB/s.)
 __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
     const uint64_t *__restrict__ in, uint64_t *__restrict__ out, int64_t n,
     int shift, const int64_t *__restrict__ offs, int64_t nb) {
-  __shared__ int64_t run[256];
+  __shared__ uint64_t keys[kSortTile];
   __shared__ int32_t cnt[kSortWaves][256];
-  const int tid = threadIdx.x;
-  const int wid = tid / kWave;
-  run[tid] = offs[(int64_t)tid * nb + blockIdx.x];
-#pragma unroll
-  for (int w = 0; w < kSortWaves; w++) cnt[w][tid] = 0;
-  __syncthreads();
+  __shared__ int32_t start[256];  // first place of each digit in the tile
+  __shared__ int64_t to[256];     // its global place, less that
+  __shared__ int32_t ws[kSortWaves];
+  const int tid = threadIdx.x, lane = lane_id(), w = tid / kWave;
   const int64_t base = (int64_t)blockIdx.x * kSortTile;
+  const int total = (int)std::min<int64_t>(kSortTile, n - base);
+  const int64_t goff = offs[(int64_t)tid * nb + blockIdx.x];
+#pragma unroll
+  for (int x = 0; x < 256 / kWave; x++) cnt[w][x * kWave + lane] = 0;
+  uint64_t key[kSortItems];
+  int32_t rank[kSortItems];
+  const int wbase = w * kWave * kSortItems;
+#pragma unroll
   for (int it = 0; it < kSortItems; it++) {
-    const int64_t i = base + it * kSortThreads + tid;
-    const bool valid = i < n;
-    const uint64_t key = valid ? in[i] : 0;
-    const int d = (int)((key >> shift) & 255);
+    const int i = wbase + it * kWave + lane;
+    key[it] = i < total ? in[base + i] : 0;
+  }
+#pragma unroll
+  for (int it = 0; it < kSortItems; it++) {
+    const bool valid = wbase + it * kWave + lane < total;
+    const int d = (int)((key[it] >> shift) & 255);
     uint64_t peers = ballot(valid);
 #pragma unroll
     for (int b = 0; b < 8; b++) {
@@ -256,23 +272,49 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
       const uint64_t m = ballot(bit);
       peers &= bit ? m : ~m;
     }
-    const int rank = lanes_below(peers);
-    if (valid && rank == 0) cnt[wid][d] = __popcll(peers);
-    __syncthreads();
-    if (valid) {
-      int64_t pos = run[d] + rank;
-      for (int w = 0; w < wid; w++) pos += cnt[w][d];
-      out[pos] = key;
-    }
-    __syncthreads();
-    int32_t add = 0;
+    const int below = lanes_below(peers);
+    __builtin_amdgcn_wave_barrier();
+    const int before = valid ? cnt[w][d] : 0;
+    __builtin_amdgcn_wave_barrier();
+    if (valid && below == 0) cnt[w][d] = before + __popcll(peers);
+    __builtin_amdgcn_wave_barrier();
+    rank[it] = before + below;
+  }
+  __syncthreads();
+  // digit tid: its count, the waves' starts within it, its start in the tile
+  int32_t run = 0;
 #pragma unroll
-    for (int w = 0; w < kSortWaves; w++) {
-      add += cnt[w][tid];
-      cnt[w][tid] = 0;
+  for (int x = 0; x < kSortWaves; x++) {
+    const int32_t c = cnt[x][tid];
+    cnt[x][tid] = run;
+    run += c;
+  }
+  int32_t inc = run;
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const int32_t y = __shfl_up(inc, off, kWave);
+    if (lane >= off) inc += y;
+  }
+  if (lane == kWave - 1) ws[w] = inc;
+  __syncthreads();
+  int32_t st = inc - run;
+#pragma unroll
+  for (int x = 0; x < kSortWaves; x++) st += x < w ? ws[x] : 0;
+  start[tid] = st;
+  to[tid] = goff - st;
+  __syncthreads();
+#pragma unroll
+  for (int it = 0; it < kSortItems; it++) {
+    if (wbase + it * kWave + lane < total) {
+      const int d = (int)((key[it] >> shift) & 255);
+      keys[start[d] + cnt[w][d] + rank[it]] = key[it];
     }
-    run[tid] += add;
-    __syncthreads();
+  }
+  __syncthreads();
+#pragma unroll 4
+  for (int i = tid; i < total; i += kSortThreads) {
+    const uint64_t k = keys[i];
+    out[to[(k >> shift) & 255] + i] = k;
   }
 }
 
