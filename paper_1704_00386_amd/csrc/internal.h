@@ -218,7 +218,7 @@ void exclusive_scan_i64(const int64_t *in, int64_t *out, int64_t n,
 uint64_t *radix_sort_u64(uint64_t *keys, uint64_t *tmp, int64_t n, int lo_bit,
                          int hi_bit, hipStream_t s, Allocator &al);
 // items[] = 0..n-1 grouped by bin[i] (stable), offsets[b] = first index of
-// bin b (host, nbins+1 entries).  nbins <= 256.
+// bin b (host, nbins+1 entries).  nbins <= 5.
 void partition_by_bin(const uint8_t *bin, int64_t n, int nbins, int32_t *items,
                       int64_t *offsets, hipStream_t s, Allocator &al);
 void fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);

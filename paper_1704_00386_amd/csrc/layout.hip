@@ -16,98 +16,38 @@
 // Results are un-permuted on the way out; nothing observable depends on the
 // internal order (SND iterates are order-independent by definition).
 #include "internal.h"
+#include "partition.h"
 
 namespace nd {
 
 namespace {
 
-int bits_for(int64_t x) {
-  int b = 1;
-  while (b < 62 && ((int64_t)1 << b) <= x) b++;
-  return b;
+// Without branches: the lower bounds of the bins that d reaches.
+__device__ __forceinline__ int bin_of(int32_t d) {
+  static_assert(kBinZero == 8 && kBinG1 == 7 && kBinBlock == 0, "bins in order");
+  return kBinZero - ((d >= 1) + (d >= 5) + (d >= 17) + (d >= 65) + (d >= 257) +
+                     (d >= 513) + (d >= 1025) + (d >= 2048));
 }
 
-__device__ __forceinline__ int bin_of(int64_t d) {
-  return d >= 2048 ? kBinBlock
-       : d >= 1025 ? kBinWave
-       : d >= 513 ? kBinWave16
-       : d >= 257 ? kBinWave8
-       : d >= 65  ? kBinG64
-       : d >= 17  ? kBinG16
-       : d >= 5   ? kBinG4
-       : d >= 1   ? kBinG1
-                  : kBinZero;
-}
-
-// Maximum degree and bin sizes: counts per thread in registers over a
-// grid-stride share, then per block in LDS, then one global atomic per block
-// and bin (atomics from every wave onto the same few words serialise).
-constexpr int kStatsBlocks = 4096;
-
-__global__ __launch_bounds__(256) void k_layout_stats(
-    const int32_t *__restrict__ cnt, int64_t nr, int32_t *__restrict__ maxd,
-    unsigned long long *__restrict__ bins) {
-  __shared__ unsigned int h[kNumBins];
-  __shared__ int32_t hm;
-  if (threadIdx.x < kNumBins) h[threadIdx.x] = 0;
-  if (threadIdx.x == 0) hm = 0;
-  __syncthreads();
-  int32_t m = 0;
-  unsigned int c[kNumBins];
-#pragma unroll
-  for (int b = 0; b < kNumBins; b++) c[b] = 0;
-  const int64_t stride = (int64_t)gridDim.x * 256;
-  for (int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x; i0 < nr;
-       i0 += 4 * stride) {
-    int32_t d[4];
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-      const int64_t i = i0 + j * stride;
-      d[j] = i < nr ? cnt[i] : -1;
-    }
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-      if (d[j] < 0) continue;
-      m = max(m, d[j]);
-      const int bd = bin_of(d[j]);
-#pragma unroll
-      for (int b = 0; b < kNumBins; b++) c[b] += bd == b;
-    }
+// r-cliques grouped by sweep bin in id order (partition.h): an internal id's
+// r-clique, its inverse and its S-degree are written as it is placed.
+struct DegreeIn {
+  const int32_t *cnt;
+  __device__ int load(int64_t i, int32_t *most) const {
+    const int32_t d = cnt[i];
+    *most = max(*most, d);
+    return bin_of(d);
   }
-#pragma unroll
-  for (int b = 0; b < kNumBins; b++) {
-    unsigned int v = c[b];
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    if (lane_id() == 0 && v) atomicAdd(&h[b], v);
+};
+struct LayoutOut {
+  const int32_t *cnt;
+  int32_t *perm, *inv, *ds;
+  __device__ void put(int64_t i, int64_t place) const {
+    perm[place] = (int32_t)i;
+    inv[i] = (int32_t)place;
+    ds[place] = cnt[i];
   }
-  for (int o = kWave / 2; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, kWave));
-  if (lane_id() == 0) atomicMax(&hm, m);
-  __syncthreads();
-  if (threadIdx.x < kNumBins && h[threadIdx.x])
-    atomicAdd(&bins[threadIdx.x], (unsigned long long)h[threadIdx.x]);
-  if (threadIdx.x == kNumBins) atomicMax(maxd, hm);
-}
-
-// Sort key: sweep bin, then ascending id.
-__global__ void k_layout_keys(const int32_t *__restrict__ cnt, int64_t nr,
-                              int rb, uint64_t *__restrict__ keys) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < nr) keys[i] = ((uint64_t)bin_of(cnt[i]) << rb) | (uint64_t)i;
-}
-
-__global__ void k_layout_perm(const uint64_t *__restrict__ keys, int64_t nr,
-                              int rb, const int32_t *__restrict__ cnt,
-                              int32_t *__restrict__ perm,
-                              int32_t *__restrict__ inv,
-                              int32_t *__restrict__ ds) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nr) return;
-  const int32_t R = (int32_t)(keys[i] & (((uint64_t)1 << rb) - 1));
-  perm[i] = R;
-  inv[R] = (int32_t)i;
-  ds[i] = cnt[R];
-}
+};
 
 template <typename T>
 __global__ void k_to_internal(const int32_t *__restrict__ in,
@@ -170,53 +110,33 @@ void build_layout(nd_graph *g, KindState &ks, const int32_t *cnt,
   const int64_t nr = ks.nr;
   ND_REQUIRE(nr < ((int64_t)1 << 31), ND_ERR_INVALID,
              "%lld r-cliques: ids must fit int32", (long long)nr);
-  DArr<int32_t> maxd(al, 1);
-  DArr<unsigned long long> bins(al, kNumBins);
-  fill_i32(maxd.p, 0, 1, s);
-  fill_u64((uint64_t *)bins.p, 0, kNumBins, s);
-  if (nr > 0) {
-    const unsigned grid =
-        (unsigned)std::min<int64_t>(grid_for(nr, 256 * 4), kStatsBlocks);
-    k_layout_stats<<<grid, 256, 0, s>>>(cnt, nr, maxd.p, bins.p);
-    ND_LAUNCHED();
-  }
-  PinnedChunk pc;
-  unsigned long long *hb = pc.as<unsigned long long>();
-  int32_t *hmaxp = reinterpret_cast<int32_t *>(hb + kNumBins);
-  ND_HIP(hipMemcpyAsync(hmaxp, maxd.p, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  ND_HIP(hipMemcpyAsync(hb, bins.p, sizeof(unsigned long long) * kNumBins,
-                        hipMemcpyDeviceToHost, s));
-  ND_HIP(hipStreamSynchronize(s));
-  const int32_t hmax = *hmaxp;
-  ks.max_ds = hmax;
-  ks.tau16 = hmax < 32768;
-  ks.tau_bytes = hmax < 256 ? 1 : ks.tau16 ? 2 : 4;
-  int64_t at = 0;
-  for (int b = 0; b < kNumBins; b++) {
-    ks.bin_lo[b] = at;
-    at += (int64_t)hb[b];
-    ks.bin_hi[b] = at;
-  }
   ks.perm.reset(al, nr);
   ks.inv.reset(al, nr);
   ks.ds.reset(al, nr);
   ks.inc_off.reset(al, nr + 1);
-  if (nr > 0) {
-    const int rb = bits_for(nr - 1);
-    DArr<uint64_t> keys(al, nr), tmp(al, nr);
-    k_layout_keys<<<grid_for(nr, 256), 256, 0, s>>>(cnt, nr, rb, keys.p);
-    ND_LAUNCHED();
-    static_assert(kNumBins <= 16, "bin index must fit 4 key bits");
-    // the keys are in id order already and the sort is stable, so sorting
-    // by the bin bits alone (one pass) orders them by (bin, id)
-    uint64_t *sorted = radix_sort_u64(keys.p, tmp.p, nr, rb, rb + 4, s, al);
-    k_layout_perm<<<grid_for(nr, 256), 256, 0, s>>>(sorted, nr, rb, cnt,
-                                                     ks.perm.p, ks.inv.p,
-                                                     ks.ds.p);
-    ND_LAUNCHED();
-  }
+  DArr<part::Head> head(al, 1);
+  if (nr > 0)
+    part::run<kNumBins>(DegreeIn{cnt}, LayoutOut{cnt, ks.perm.p, ks.inv.p, ks.ds.p},
+                        nr, head.p, s, al);
   exclusive_scan_i32(ks.ds.p, ks.inc_off.p, nr, s, al);
-  ks.P = read_i64(ks.inc_off.p + nr, s);
+  // one wait for the bins, the largest S-degree and the total
+  PinnedChunk pc;
+  part::Head *h = pc.as<part::Head>();
+  int64_t *total = reinterpret_cast<int64_t *>(h + 1);
+  if (nr > 0)
+    ND_HIP(hipMemcpyAsync(h, head.p, sizeof *h, hipMemcpyDeviceToHost, s));
+  ND_HIP(hipMemcpyAsync(total, ks.inc_off.p + nr, sizeof *total,
+                        hipMemcpyDeviceToHost, s));
+  ND_HIP(hipStreamSynchronize(s));
+  const int32_t hmax = nr > 0 ? h->most : 0;
+  ks.max_ds = hmax;
+  ks.tau16 = hmax < 32768;
+  ks.tau_bytes = hmax < 256 ? 1 : ks.tau16 ? 2 : 4;
+  for (int b = 0; b < kNumBins; b++) {
+    ks.bin_lo[b] = nr > 0 ? h->start[b] : 0;
+    ks.bin_hi[b] = nr > 0 ? h->start[b + 1] : 0;
+  }
+  ks.P = *total;
 }
 
 void to_internal(const KindState &ks, const int32_t *in, void *out, int bytes,

@@ -6,6 +6,7 @@
 #include <vector>
 
 #include "internal.h"
+#include "partition.h"
 
 namespace nd {
 
@@ -341,34 +342,15 @@ __global__ void k_fill_u64(uint64_t *p, uint64_t v, int64_t n) {
   if (i < n) p[i] = v;
 }
 
-// Keys bin<<32 | i, and the bin sizes: counted per block in LDS first, so
-// that the global counters see one atomic per (block, bin) rather than one
-// per item (a handful of bins would otherwise serialise every thread).
-__global__ __launch_bounds__(256) void k_bin_keys(
-    const uint8_t *__restrict__ bin, int64_t n, int nbins,
-    uint64_t *__restrict__ keys, unsigned long long *__restrict__ counts) {
-  __shared__ unsigned int h[256];
-  h[threadIdx.x] = 0;
-  __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * 256 * 8;
-  for (int j = 0; j < 8; j++) {
-    const int64_t i = base + j * 256 + threadIdx.x;
-    if (i < n) {
-      const uint8_t b = bin[i];
-      keys[i] = ((uint64_t)b << 32) | (uint64_t)i;
-      atomicAdd(&h[b], 1u);
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x < nbins && h[threadIdx.x])
-    atomicAdd(&counts[threadIdx.x], (unsigned long long)h[threadIdx.x]);
-}
-
-__global__ void k_low32(const uint64_t *__restrict__ keys, int64_t n,
-                        int32_t *__restrict__ items) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) items[i] = (int32_t)(keys[i] & 0xffffffffu);
-}
+// Items grouped by a byte each.
+struct ByteIn {
+  const uint8_t *bin;
+  __device__ int load(int64_t i, int32_t *) const { return bin[i]; }
+};
+struct ItemOut {
+  int32_t *items;
+  __device__ void put(int64_t i, int64_t place) const { items[place] = (int32_t)i; }
+};
 
 }  // namespace
 
@@ -408,21 +390,15 @@ uint64_t *radix_sort_u64(uint64_t *keys, uint64_t *tmp, int64_t n, int lo_bit,
 
 void partition_by_bin(const uint8_t *bin, int64_t n, int nbins, int32_t *items,
                       int64_t *offsets, hipStream_t s, Allocator &al) {
-  ND_REQUIRE(nbins >= 1 && nbins <= 256, ND_ERR_INVALID, "bad bin count");
+  ND_REQUIRE(nbins >= 1 && nbins <= 5, ND_ERR_INVALID, "bad bin count");
   for (int b = 0; b <= nbins; b++) offsets[b] = 0;
   if (n <= 0) return;
-  DArr<uint64_t> keys(al, n), tmp(al, n);
-  DArr<unsigned long long> counts(al, nbins);
-  ND_HIP(hipMemsetAsync(counts.p, 0, sizeof(unsigned long long) * nbins, s));
-  k_bin_keys<<<grid_for(n, 256 * 8), 256, 0, s>>>(bin, n, nbins, keys.p,
-                                                   counts.p);
-  ND_LAUNCHED();
-  uint64_t *sorted = radix_sort_u64(keys.p, tmp.p, n, 32, 40, s, al);
-  k_low32<<<grid_for(n, 256), 256, 0, s>>>(sorted, n, items);
-  ND_LAUNCHED();
+  DArr<part::Head> head(al, 1);
+  part::run<5>(ByteIn{bin}, ItemOut{items}, n, head.p, s, al);
   PinnedChunk pc;
-  const unsigned long long *h = pc.read(counts.p, (size_t)nbins, s);
-  for (int b = 0; b < nbins; b++) offsets[b + 1] = offsets[b] + (int64_t)h[b];
+  const part::Head *h = pc.read(head.p, 1, s);
+  for (int b = 0; b < nbins; b++) offsets[b] = h->start[b];
+  offsets[nbins] = n;
 }
 
 void fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s) {

@@ -40,3 +40,31 @@ def test_csr_at_scan_edges(m):
     woff, wcol = _numpy_csr(n, src, dst)
     assert np.array_equal(off.cpu().numpy(), woff)
     assert np.array_equal(col.cpu().numpy(), wcol)
+
+
+# Items n of the partition by sweep bin (one per vertex): around a wave's row,
+# a wave's share, one workgroup's 16384 and several; degrees over every bin.
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 1023, 1025, 4096, 16383, 16384,
+                               16385, 20480, 40001, 200001])
+def test_layout_at_partition_edges(n):
+    import torch
+    nd = _nd()
+    rng = np.random.default_rng(n)
+    # a few vertices of large degree, many of small, isolated ones at the end
+    w = rng.random(6 * n) ** 6
+    src = (w * n * 0.9).astype(np.int32)
+    dst = rng.integers(0, n, 6 * n).astype(np.int32)
+    ctx = nd.Context(0)
+    g = nd.Graph.from_edges(ctx, n, torch.from_numpy(src), torch.from_numpy(dst))
+    off, col = _numpy_csr(n, src, dst)
+    nr, P, _ = g.sizes("core")
+    assert (nr, P) == (n, len(col))
+    assert np.array_equal(g.sdegree("core").cpu().numpy(), np.diff(off))
+    goff, gids = g.incidence("core")
+    goff, gids = goff.cpu().numpy(), gids.cpu().numpy()[:, 0]
+    assert np.array_equal(goff, off)
+    row = np.repeat(np.arange(n), np.diff(off))
+    order = np.lexsort((gids, row))
+    assert np.array_equal(gids[order], col)
+    _, res = g.decompose("core", max_iters=1, allow_not_converged=True)
+    assert res["max_sdegree"] == int(np.diff(off).max())
