@@ -312,12 +312,11 @@ static void prepare_kind(nd_graph *g, nd_kind kind, hipStream_t s) {
       k_check_incidence<<<grid, 256, 0, s>>>(ks.inc_ids.p, nids, ks.nr, err.p);
       ND_LAUNCHED();
     }
-    const int32_t h = *PinnedChunk().read(err.p, 1, s);
+    ND_HIP(hipEventRecord(e1, s));
+    const int32_t h = *PinnedChunk().read(err.p, 1, s);  // waits for e1 too
     ND_REQUIRE(h == 0, ND_ERR_DEVICE,
                "internal error: incidence list holds an invalid r-clique id");
   }
-  ND_HIP(hipEventRecord(e1, s));
-  ND_HIP(hipEventSynchronize(e1));
   float ms = 0;
   ND_HIP(hipEventElapsedTime(&ms, e0, e1));
   (void)hipEventDestroy(e0);
@@ -408,7 +407,7 @@ nd_status nd_ctx_create(int device, size_t hbm_budget_bytes, nd_ctx **out) {
                               device) == hipSuccess && cu > 0)
       c->num_cu = cu;
     // what a decomposition needs besides its device buffers, made once
-    ND_HIP(hipHostMalloc(&c->host_stats, sizeof(SweepStats) * kHostStatsRing,
+    ND_HIP(hipHostMalloc(&c->host_stats, sizeof(HostStats) * kHostStatsRing,
                          hipHostMallocDefault));
     for (hipEvent_t &e : c->ev) ND_HIP(hipEventCreate(&e));
     noalloc_setup(device);

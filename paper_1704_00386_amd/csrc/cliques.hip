@@ -1438,7 +1438,8 @@ void build_incidence_truss(nd_graph *g, KindState &ks, hipStream_t s) {
     ND_LAUNCHED();
   }
   int64_t bin_off[5];
-  partition_by_bin(bin.p, ne, 4, items.p, bin_off, s, al);
+  DArr<int64_t> head(al, kPartHeadWords);
+  partition_start(bin.p, ne, items.p, head.p, s, al);
   bin.free();
   // Room for every triangle the count pass can find (the shorter out-list
   // bounds each edge's), so that the fill pass reads them back instead of
@@ -1450,7 +1451,10 @@ void build_incidence_truss(nd_graph *g, KindState &ks, hipStream_t s) {
   DArr<int64_t> tri_off(al, ne + 1);
   exclusive_scan_i32(cap.p, tri_off.p, ne, s, al);
   cap.free();
-  const int64_t tri_cap = read_i64(tri_off.p + ne, s);
+  PinnedChunk pc;
+  const int64_t *hhead = ne > 0 ? pc.post(head.p, kPartHeadWords, s) : nullptr;
+  const int64_t tri_cap = *pc.read(tri_off.p + ne, 1, s);
+  partition_offsets(hhead, ne, 4, bin_off);
   DArr<int2> tri_buf;
   const size_t tri_bytes = sizeof(int2) * (size_t)std::max<int64_t>(tri_cap, 1);
   const size_t live = al.live_bytes();

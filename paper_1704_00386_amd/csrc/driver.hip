@@ -31,7 +31,7 @@ namespace {
 constexpr int kStatsRing = 1024;  // device counters kept per decomposition
 constexpr int kStaticRing = 64;   // the same, in the static workspace
 constexpr int kMaxChunk = 16;     // sweeps enqueued per host round trip
-static_assert(kMaxChunk < kStaticRing && kStaticRing <= kHostStatsRing &&
+static_assert(kMaxChunk <= kWave && kMaxChunk < kStaticRing && kStaticRing <= kHostStatsRing &&
                   kStatsRing <= kHostStatsRing,
               "a chunk and its predecessor must fit every counter ring");
 constexpr int64_t kSumsDiv = 256;  // see sums_after in sweep_loop
@@ -100,6 +100,22 @@ __global__ __launch_bounds__(256) void k_count_active(
 #pragma unroll
   for (int off = kWave / 2; off > 0; off >>= 1) c += __shfl_xor(c, off, kWave);
   if (lane_id() == 0 && c) atomicAdd(&st->active, c);
+}
+
+// The host's counters of the chunk's sweeps (hst is pinned host memory, the
+// same ring as the device's): totals only, 32 bytes a sweep.
+__global__ void k_post_stats(const SweepStats *__restrict__ ring,
+                             HostStats *__restrict__ hst, int ring_len,
+                             int64_t first, int count) {
+  const int i = threadIdx.x;
+  if (i >= count) return;
+  const SweepStats &st = ring[(first + i) % ring_len];
+  HostStats h;
+  h.changed = st.changed_total();
+  h.evaluated = st.evaluated_total();
+  h.notified = st.notified;
+  h.active = st.active;
+  hst[(first + i) % ring_len] = h;
 }
 
 float elapsed_ms(hipEvent_t a, hipEvent_t b) {
@@ -232,7 +248,7 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
       sums_after = std::max<unsigned long long>(
           1, (unsigned long long)(ks.bin_lo[kBinZero] / kSumsDiv));
   }
-  SweepStats *hst = (SweepStats *)ctx->host_stats;
+  HostStats *hst = (HostStats *)ctx->host_stats;
   const int ring_len = b.ring_len;
   const int grid_per_cu =
       frontier ? grid_per_cu_frontier(ks.bin_lo[kBinZero], ctx->num_cu) : kGridPerCu;
@@ -312,21 +328,16 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
       }
       if (step_by_step) ND_HIP(hipEventRecord(ev[3], s));
     }
-    // read back this chunk's counters (the ring may wrap once)
-    const int64_t f = t0 % ring_len;
-    const int64_t first_n = std::min<int64_t>(nb, ring_len - f);
-    ND_HIP(hipMemcpyAsync(hst + f, b.ring + f, sizeof(SweepStats) * first_n,
-                          hipMemcpyDeviceToHost, s));
-    if (first_n < nb)
-      ND_HIP(hipMemcpyAsync(hst, b.ring, sizeof(SweepStats) * (nb - first_n),
-                            hipMemcpyDeviceToHost, s));
+    // read back this chunk's counters
+    k_post_stats<<<1, kWave, 0, s>>>(b.ring, hst, ring_len, t0, nb);
+    ND_LAUNCHED();
     ND_HIP(hipStreamSynchronize(s));
     bool done = false;
     for (int64_t j = t0; j < t0 + nb && !done; j++) {
-      const SweepStats &st = hst[j % ring_len];
+      const HostStats &st = hst[j % ring_len];
       sweeps = j + 1;
-      const int64_t changed = (int64_t)st.changed_total();
-      const int64_t evald = (int64_t)st.evaluated_total();
+      const int64_t changed = (int64_t)st.changed;
+      const int64_t evald = (int64_t)st.evaluated;
       updates += evald;
       const bool last = changed == 0 || j + 1 == opts.max_iters;
       if (opts.on_iter &&
@@ -356,12 +367,12 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
     }
     if (done) break;
     if (plain) {
-      const SweepStats &last = hst[(t - 1) % ring_len];
-      plain = !last.notified && last.changed_total() > notify_below;
+      const HostStats &last = hst[(t - 1) % ring_len];
+      plain = !last.notified && last.changed > notify_below;
     }
     // once few r-cliques change, notifications keep the summaries themselves
     if (sums_after != 0 && hst[(t - 1) % ring_len].notified &&
-        hst[(t - 1) % ring_len].changed_total() < sums_after)
+        hst[(t - 1) % ring_len].changed < sums_after)
       sums_after = 0;
     chunk = std::min(chunk * 2, step_by_step || (watch && plain) ? 1 : kMaxChunk);
   }

@@ -218,7 +218,14 @@ void exclusive_scan_i64(const int64_t *in, int64_t *out, int64_t n,
 uint64_t *radix_sort_u64(uint64_t *keys, uint64_t *tmp, int64_t n, int lo_bit,
                          int hi_bit, hipStream_t s, Allocator &al);
 // items[] = 0..n-1 grouped by bin[i] (stable), offsets[b] = first index of
-// bin b (host, nbins+1 entries).  nbins <= 5.
+// bin b (host, nbins+1 entries).  nbins <= 5.  partition_start leaves the
+// offsets in head (device memory, first kPartHeadWords of it int64) for the
+// caller to post, with partition_offsets to read them.
+constexpr int kPartHeadWords = 18;
+void partition_start(const uint8_t *bin, int64_t n, int32_t *items,
+                     int64_t *head, hipStream_t s, Allocator &al);
+void partition_offsets(const int64_t *head, int64_t n, int nbins,
+                       int64_t *offsets);
 void partition_by_bin(const uint8_t *bin, int64_t n, int nbins, int32_t *items,
                       int64_t *offsets, hipStream_t s, Allocator &al);
 void fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);
@@ -228,9 +235,12 @@ void iota_i32(int32_t *p, int64_t n, hipStream_t s);  // p[i] = i
 int64_t read_i64(const int64_t *dev, hipStream_t s);  // synchronous
 
 // A 4 KiB pinned host chunk taken from a pool for the life of the object,
-// for reading a few words back from the device: a copy into pageable memory
-// goes through the runtime's staging path instead of straight to its
-// destination.  Chunks return to the pool, never to the runtime.
+// for reading a few words back from the device.  A one-workgroup kernel stores
+// them into the chunk (which the device sees), so the wait that follows is all
+// that a read-back costs besides: an asynchronous copy of a few bytes goes
+// through the runtime's copy path, which takes longer than the kernel.
+// Several words can be posted before one wait.  Chunks return to the pool,
+// never to the runtime.
 class PinnedChunk {
  public:
   static constexpr size_t kBytes = 4096;
@@ -240,17 +250,32 @@ class PinnedChunk {
   PinnedChunk &operator=(const PinnedChunk &) = delete;
   template <class T>
   T *as() const { return static_cast<T *>(p_); }
-  // Copy n words of T from the device (ordered on s, waits for it).
+  // Post n words of T (a multiple of 4 bytes, 8-byte aligned places); valid
+  // after a wait for s.
+  template <class T>
+  const T *post(const T *dev, size_t n, hipStream_t s) {
+    static_assert(sizeof(T) % 4 == 0, "whole words are posted");
+    const size_t bytes = (n * sizeof(T) + 7) / 8 * 8;
+    ND_REQUIRE(used_ + bytes <= kBytes, ND_ERR_INVALID, "read-back too large");
+    T *to = reinterpret_cast<T *>(static_cast<char *>(p_) + used_);
+    used_ += bytes;
+    post_words(to, dev, n * sizeof(T) / 4, s);
+    return to;
+  }
+  // Post n words of T and wait for s.  The next post after it starts over at
+  // the chunk's beginning.
   template <class T>
   const T *read(const T *dev, size_t n, hipStream_t s) {
-    ND_REQUIRE(n * sizeof(T) <= kBytes, ND_ERR_INVALID, "read-back too large");
-    ND_HIP(hipMemcpyAsync(p_, dev, n * sizeof(T), hipMemcpyDeviceToHost, s));
+    const T *to = post(dev, n, s);
     ND_HIP(hipStreamSynchronize(s));
-    return as<T>();
+    used_ = 0;
+    return to;
   }
 
  private:
+  static void post_words(void *to, const void *dev, size_t words, hipStream_t s);
   void *p_ = nullptr;
+  size_t used_ = 0;
 };
 
 // ------------------------------------------------------------ graph prep
@@ -375,8 +400,11 @@ struct SweepArgs {
 constexpr size_t kNoallocWorkspaceBytes = ND_NOALLOC_WORKSPACE_BYTES;
 void *noalloc_workspace(int device);
 
-// Entries of the pinned host ring that receives the sweep counters.
+// Entries of the pinned host ring that receives the sweep counters' totals.
 constexpr int kHostStatsRing = 1024;
+struct HostStats {
+  unsigned long long changed, evaluated, notified, active;
+};
 
 // Launch one sweep over every bin of ks (internal numbering, tau of
 // ks.tau_bytes per value).  `and_mode` selects in-place reads.

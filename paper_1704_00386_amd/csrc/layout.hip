@@ -121,13 +121,8 @@ void build_layout(nd_graph *g, KindState &ks, const int32_t *cnt,
   exclusive_scan_i32(ks.ds.p, ks.inc_off.p, nr, s, al);
   // one wait for the bins, the largest S-degree and the total
   PinnedChunk pc;
-  part::Head *h = pc.as<part::Head>();
-  int64_t *total = reinterpret_cast<int64_t *>(h + 1);
-  if (nr > 0)
-    ND_HIP(hipMemcpyAsync(h, head.p, sizeof *h, hipMemcpyDeviceToHost, s));
-  ND_HIP(hipMemcpyAsync(total, ks.inc_off.p + nr, sizeof *total,
-                        hipMemcpyDeviceToHost, s));
-  ND_HIP(hipStreamSynchronize(s));
+  const part::Head *h = nr > 0 ? pc.post(head.p, 1, s) : nullptr;
+  const int64_t *total = pc.read(ks.inc_off.p + nr, 1, s);
   const int32_t hmax = nr > 0 ? h->most : 0;
   ks.max_ds = hmax;
   ks.tau16 = hmax < 32768;

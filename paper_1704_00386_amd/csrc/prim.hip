@@ -388,17 +388,30 @@ uint64_t *radix_sort_u64(uint64_t *keys, uint64_t *tmp, int64_t n, int lo_bit,
   return src;
 }
 
+static_assert(sizeof(part::Head) == 8 * kPartHeadWords, "the head's words");
+
+void partition_start(const uint8_t *bin, int64_t n, int32_t *items,
+                     int64_t *head, hipStream_t s, Allocator &al) {
+  if (n > 0)
+    part::run<5>(ByteIn{bin}, ItemOut{items}, n, reinterpret_cast<part::Head *>(head),
+                 s, al);
+}
+
+void partition_offsets(const int64_t *head, int64_t n, int nbins,
+                       int64_t *offsets) {
+  ND_REQUIRE(nbins >= 1 && nbins <= 5, ND_ERR_INVALID, "bad bin count");
+  const part::Head *h = reinterpret_cast<const part::Head *>(head);
+  for (int b = 0; b < nbins; b++) offsets[b] = n > 0 ? h->start[b] : 0;
+  offsets[nbins] = n > 0 ? n : 0;
+}
+
 void partition_by_bin(const uint8_t *bin, int64_t n, int nbins, int32_t *items,
                       int64_t *offsets, hipStream_t s, Allocator &al) {
-  ND_REQUIRE(nbins >= 1 && nbins <= 5, ND_ERR_INVALID, "bad bin count");
-  for (int b = 0; b <= nbins; b++) offsets[b] = 0;
-  if (n <= 0) return;
-  DArr<part::Head> head(al, 1);
-  part::run<5>(ByteIn{bin}, ItemOut{items}, n, head.p, s, al);
+  DArr<int64_t> head(al, kPartHeadWords);
+  partition_start(bin, n, items, head.p, s, al);
   PinnedChunk pc;
-  const part::Head *h = pc.read(head.p, 1, s);
-  for (int b = 0; b < nbins; b++) offsets[b] = h->start[b];
-  offsets[nbins] = n;
+  const int64_t *h = n > 0 ? pc.read(head.p, kPartHeadWords, s) : head.p;
+  partition_offsets(h, n, nbins, offsets);
 }
 
 void fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s) {
@@ -433,6 +446,12 @@ void fill_u64(uint64_t *p, uint64_t v, int64_t n, hipStream_t s) {
 }
 
 namespace {
+
+__global__ void k_post(uint32_t *__restrict__ to, const uint32_t *__restrict__ from,
+                       int words) {
+  for (int i = threadIdx.x; i < words; i += blockDim.x) to[i] = from[i];
+}
+
 std::mutex g_pinned_mu;
 std::vector<void *> g_pinned_free;
 }  // namespace
@@ -452,6 +471,13 @@ PinnedChunk::PinnedChunk() {
 PinnedChunk::~PinnedChunk() {
   std::lock_guard<std::mutex> lk(g_pinned_mu);
   g_pinned_free.push_back(p_);
+}
+
+void PinnedChunk::post_words(void *to, const void *dev, size_t words,
+                             hipStream_t s) {
+  k_post<<<1, kWave, 0, s>>>(static_cast<uint32_t *>(to),
+                             static_cast<const uint32_t *>(dev), (int)words);
+  ND_LAUNCHED();
 }
 
 int64_t read_i64(const int64_t *dev, hipStream_t s) {
