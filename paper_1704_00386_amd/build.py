@@ -28,7 +28,8 @@ SOURCES = ["api.hip", "prim.hip", "graph.hip", "cliques.hip", "layout.hip",
 
 # sweep_inst.hip once per k = C(s,r) - 1 and type of tau
 SWEEP_SRC = "sweep_inst.hip"
-SWEEP_OBJS = [(f"sweep_k{k}_{t}", [f"-DND_SWEEP_K={k}", f"-DND_SWEEP_T={t}"])
+SWEEP_OBJS = [(f"sweep_k{k}_{t}", [f"-DND_SWEEP_K={k}", f"-DND_SWEEP_T={t}",
+                                   f"-DND_SWEEP_BATCH={int(t != 'uint8_t')}"])
               for k in (5, 3, 2, 1) for t in ("int32_t", "uint16_t", "uint8_t")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -67,9 +68,8 @@ def build(jobs: int | None = None) -> str:
     jobs = jobs or min(8, os.cpu_count() or 1)
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
         # the longest first
-        lib = [ex.submit(_compile, "batch.hip")]
-        lib += [ex.submit(_compile, SWEEP_SRC, n, d) for n, d in SWEEP_OBJS]
-        lib += [ex.submit(_compile, s) for s in SOURCES if s != "batch.hip"]
+        lib = [ex.submit(_compile, SWEEP_SRC, n, d) for n, d in SWEEP_OBJS]
+        lib += [ex.submit(_compile, s) for s in SOURCES]
         ceil = ex.submit(_compile, CEIL_SRC)
         objs, ceil_obj = [f.result() for f in lib], ceil.result()
     _link(objs, LIB)

@@ -22,6 +22,8 @@ struct BGraph {
   int64_t max_local;   // sweeps allowed
   uint8_t *act[2];     // frontier stamps: sweep t reads act[t & 1]
   uint8_t *act_sum[2]; // one stamp per 64 r-cliques, set with any of their flags
+  void *slack;         // support counting (NULL: flags); act is then its counters
+  int64_t lost_shift;  // log2 of the bytes per counter
   unsigned long long notify_below;  // start notifying at <= this many changes
 };
 
@@ -32,21 +34,18 @@ struct BTile {
   int64_t lo, hi;
 };
 
-struct BHub {  // one r-clique with d_s >= 2048
-  int32_t g;
-  int32_t pad;
-  int64_t R;
-};
-
 // Device-resident launch state: every kernel of an epoch reads it, so a
 // chunk of epochs built as a HIP graph stays valid when the tables change.
 struct BState {
   int64_t epoch;
   int32_t ntiles;
-  int32_t nhubs;
   int32_t ng;
-  int32_t nwide;  // tiles [0, nwide): 16 or 32 values per lane (k_batch_sweep<WIDE>)
 };
+
+// The tile kernel of k = K and tau of type T (16 or 32 bits), instantiated in
+// sweep_inst.hip.
+template <int K, typename T>
+const void *batch_kernel(bool and_mode, bool fr);
 
 // Tile length: an epoch is cut into about grid * tiles_per_group tiles of
 // about equal work (one workgroup each).
@@ -66,10 +65,17 @@ struct Member {
   bool finished = false;
   int slot = -1;          // index in the device descriptor table
   int64_t ntiles = 0;     // tiles it contributes
-  DArr<uint8_t> tau0, tau1;
-  DArr<uint8_t> act0, act1;  // frontier batches only
-  DArr<uint8_t> sum0, sum1;  // their group summaries (one per 64 r-cliques)
-  DArr<SweepStats> ring;
+  // one allocation: the values, slack words, and from `zero` on what starts
+  // out cleared
+  DArr<uint8_t> mem;
+  uint8_t *tau[2] = {nullptr, nullptr};  // AND: the second is NULL
+  uint8_t *slack = nullptr;              // support counting, or NULL
+  uint8_t *zero = nullptr;
+  int64_t zero_bytes = 0;                // a multiple of 16
+  SweepStats *ring = nullptr;
+  uint8_t *act[2] = {nullptr, nullptr};  // frontier: flags, or counters
+  uint8_t *sum[2] = {nullptr, nullptr};  // one stamp per 64 r-cliques
+  int lost_shift = 0;
 };
 
 class Batch {
@@ -118,6 +124,7 @@ class Batch {
  private:
   void init_member_tau(Member &m);
   void rebuild();
+  void upload_state(int64_t epoch);
   void set_config(const BatchConfig &c);
   void launch_epoch();
   void build_graph();
@@ -132,14 +139,14 @@ class Batch {
   hipStream_t s_ = nullptr;
   BatchConfig cfg_;
   std::vector<std::unique_ptr<Member>> members_;
-  DArr<BGraph> gs_;
-  DArr<BTile> tiles_;
-  DArr<BHub> hubs_;
-  DArr<BState> state_;
-  DArr<unsigned long long> poll_buf_;
-  int64_t gs_cap_ = 0, tiles_cap_ = 0, hubs_cap_ = 0, poll_cap_ = 0;
-  int64_t wide_grid_ = 0, narrow_grid_ = 0;  // grids of the two tile kernels
-  int ntiles_ = 0, nhubs_ = 0, ng_ = 0, nwide_ = 0;
+  // launch state, graph table and tile table, one buffer filled by one copy
+  DArr<uint8_t> tables_;
+  BState *state_ = nullptr;
+  BGraph *gs_ = nullptr;
+  BTile *tiles_ = nullptr;
+  DArr<int64_t> poll_buf_;
+  int64_t gs_cap_ = 0, tiles_cap_ = 0;  // tiles_cap_: also the sweep's grid
+  int ntiles_ = 0, ng_ = 0;
   int64_t work_ = 0;
   int64_t epoch_ = 0;
   int64_t dead_tiles_ = 0;  // tiles of finished members still in the table

@@ -42,246 +42,82 @@ namespace {
 
 using namespace dev;
 
-constexpr int kHubGrid = 256;
-constexpr int kBeginGrid = 64;
-
-// R's one 256-thread block pass covers, per bin type.
+// r-cliques of one pass of a 256-thread workgroup, per bin type.
 __host__ __device__ constexpr int rclq_per_pass(int type) {
-  return type == kBinG1 ? 256 : type == kBinG4 ? 64 : type == kBinG16 ? 16 : 4;
+  return type == kBinG1 ? 256
+         : type == kBinG4 ? 64
+         : type == kBinG16 ? 16
+         : type >= kBinWave16 ? 4
+                              : 1;
 }
 
-// Largest incidence count of one pass, in units of 1024: passes of the
-// G-bins cover at most 1024 incidences (R per pass x largest d_s of the
-// bin); a pass of the wave bins (4 R of d_s < 2048, 1025, 513) up to 8x,
-// 4x and 2x that.
+// Largest incidence count of one pass, in units of 1024 (hubs: a round one).
 constexpr int pass_units(int type) {
-  return type == kBinWave ? 8 : type == kBinWave16 ? 4 : type == kBinWave8 ? 2 : 1;
+  return type == kBinBlock ? 4 : type == kBinWave ? 2 : type == kBinWave16 ? 4
+         : type == kBinWave8 ? 2 : 1;
 }
 
-__device__ __forceinline__ bool graph_live(const BGraph &G, int64_t e,
-                                           int64_t *local) {
-  *local = e - G.t0;
-  if (*local < 0 || *local >= G.max_local) return false;
-  return *local == 0 || changed_sum(&G.ring[(*local - 1) % kBatchRing]) != 0;
-}
+// After an epoch, one workgroup: each graph's changed total (read by its
+// tiles of the next epoch and by the poll), the next sweep's counters
+// cleared, the epoch advanced.  16 lanes a graph, one counter part each.
+constexpr int kStepThreads = 1024;
+static_assert(kStatParts == 16, "one lane per counter part");
 
-// Frontier state of graph G's sweep `local` (the rule of the one-graph
-// sweep, per graph): flags are read only if the previous sweep wrote them,
-// and notifications start once a sweep changed at most G.notify_below.
-template <bool FR>
-__device__ __forceinline__ void graph_frontier(const BGraph &G, int64_t local,
-                                               SweepStats *sst,
-                                               const uint8_t **act,
-                                               uint8_t **act_next,
-                                               uint8_t *stamp,
-                                               const uint8_t **act_sum,
-                                               uint8_t **sum_next) {
-  *act = nullptr;
-  *act_next = nullptr;
-  *act_sum = nullptr;
-  *sum_next = nullptr;
-  *stamp = 0;
-  if (!FR || local == 0) return;
-  const SweepStats *prev = &G.ring[(local - 1) % kBatchRing];
-  const bool valid = prev->notified != 0;
-  const bool notify = valid || changed_sum(prev) <= G.notify_below;
-  *act = valid ? G.act[local & 1] : nullptr;
-  *act_next = notify ? G.act[(local + 1) & 1] : nullptr;
-  *act_sum = valid ? G.act_sum[local & 1] : nullptr;
-  *sum_next = notify ? G.act_sum[(local + 1) & 1] : nullptr;
-  *stamp = sweep_stamp(local);
-  if (notify && threadIdx.x == 0) sst->notified = 1;
-}
-
-// One epoch's tiles, one workgroup per tile (tile i of the kernel's range
-// on workgroup i; the grid is the table's capacity, surplus workgroups
-// exit at once).  Workgroups are short-lived, so the work of other streams
-// (a server's preparations) is dispatched between them rather than waiting
-// for the epoch to end.  Two instances share the work: WIDE takes the tiles
-// of the bins of 16 and 32 values per lane (tiles [0, nwide)), the other
-// one every other bin, so that the registers of the wide lanes do not set
-// the occupancy of the rest.
-template <int K, typename T, bool AND, bool FR, bool WIDE>
-__global__ __launch_bounds__(256) void k_batch_sweep(
-    const BGraph *__restrict__ gs, const BTile *__restrict__ tiles,
-    const BState *__restrict__ st) {
-  const int64_t e = st->epoch;
-  const int t_lo = WIDE ? 0 : st->nwide;
-  const int t_hi = WIDE ? st->nwide : st->ntiles;
-  const int ti = t_lo + (int)blockIdx.x;
-  if (ti >= t_hi) return;
-  {
-    const BTile tile = tiles[ti];
-    const BGraph &G = gs[tile.g];
-    int64_t local;
-    if (!graph_live(G, e, &local)) return;
-    const T *in = (const T *)G.tau[local & 1];
-    T *out = (T *)G.tau[AND ? (local & 1) : ((local + 1) & 1)];
-    SweepStats *sst = &G.ring[local % kBatchRing];
-    const uint8_t *act, *act_sum;
-    uint8_t *act_next, *sum_next, stamp;
-    graph_frontier<FR>(G, local, sst, &act, &act_next, &stamp, &act_sum,
-                       &sum_next);
-    if (FR && act != nullptr) {
-      // sparse sweep of the tile: flags tested a chunk at a time per wave
-      unsigned long long n_ch = 0, n_ev = 0;
-      const int64_t wv = threadIdx.x / kWave, nw = blockDim.x / kWave;
-      if constexpr (WIDE) {
-        if (tile.type == kBinWave)
-          sweep_sparse<K, 64, 32, T, AND>(G.inc_off, G.inc_ids, in, out, 1, tile.lo,
-                                          tile.hi, wv, nw, act, act_next, stamp,
-                                          &n_ch, &n_ev, act_sum, sum_next);
-        else
-          sweep_sparse<K, 64, 16, T, AND>(G.inc_off, G.inc_ids, in, out, 1, tile.lo,
-                                          tile.hi, wv, nw, act, act_next, stamp,
-                                          &n_ch, &n_ev, act_sum, sum_next);
-      } else {
-        switch (tile.type) {
-          case kBinG1:
-            sweep_sparse<K, 1, 4, T, AND>(G.inc_off, G.inc_ids, in, out, 1, tile.lo,
-                                          tile.hi, wv, nw, act, act_next, stamp,
-                                          &n_ch, &n_ev, act_sum, sum_next);
-            break;
-          case kBinG4:
-            sweep_sparse<K, 4, 4, T, AND>(G.inc_off, G.inc_ids, in, out, 1, tile.lo,
-                                          tile.hi, wv, nw, act, act_next, stamp,
-                                          &n_ch, &n_ev, act_sum, sum_next);
-            break;
-          case kBinG16:
-            sweep_sparse<K, 16, 4, T, AND>(G.inc_off, G.inc_ids, in, out, 1, tile.lo,
-                                           tile.hi, wv, nw, act, act_next, stamp,
-                                           &n_ch, &n_ev, act_sum, sum_next);
-            break;
-          case kBinG64:
-            sweep_sparse<K, 64, 4, T, AND>(G.inc_off, G.inc_ids, in, out, 1, tile.lo,
-                                           tile.hi, wv, nw, act, act_next, stamp,
-                                           &n_ch, &n_ev, act_sum, sum_next);
-            break;
-          default:  // kBinWave8
-            sweep_sparse<K, 64, 8, T, AND>(G.inc_off, G.inc_ids, in, out, 1, tile.lo,
-                                           tile.hi, wv, nw, act, act_next, stamp,
-                                           &n_ch, &n_ev, act_sum, sum_next);
-            break;
-        }
-      }
-      stat_add_counts(sst, n_ch, n_ev);
-      return;
-    }
-    const int per = rclq_per_pass(tile.type);
-    unsigned long long n_ch = 0, n_ev = 0;  // this wave's, over the passes
-    for (int64_t base = tile.lo; base < tile.hi; base += per) {
-      bool ch = false, ev = false;
-      if constexpr (WIDE) {
-        const int64_t R = base + threadIdx.x / 64;
-        if (tile.type == kBinWave)
-          ch = update_regs<K, 64, 32, T, AND, FR>(G.inc_off, G.inc_ids, in, out, 1,
-                                              R, R < tile.hi, act, act_next, stamp, &ev, sum_next);
-        else
-          ch = update_regs<K, 64, 16, T, AND, FR>(G.inc_off, G.inc_ids, in, out, 1,
-                                              R, R < tile.hi, act, act_next, stamp, &ev, sum_next);
-      } else {
-        switch (tile.type) {
-          case kBinG1: {
-            const int64_t R = base + threadIdx.x;
-            ch = update_regs<K, 1, 4, T, AND, FR>(G.inc_off, G.inc_ids, in, out, 1, R,
-                                              R < tile.hi, act, act_next, stamp, &ev, sum_next);
-            break;
-          }
-          case kBinG4: {
-            const int64_t R = base + threadIdx.x / 4;
-            ch = update_regs<K, 4, 4, T, AND, FR>(G.inc_off, G.inc_ids, in, out, 1, R,
-                                              R < tile.hi, act, act_next, stamp, &ev, sum_next);
-            break;
-          }
-          case kBinG16: {
-            const int64_t R = base + threadIdx.x / 16;
-            ch = update_regs<K, 16, 4, T, AND, FR>(G.inc_off, G.inc_ids, in, out, 1,
-                                               R, R < tile.hi, act, act_next, stamp, &ev, sum_next);
-            break;
-          }
-          case kBinG64: {
-            const int64_t R = base + threadIdx.x / 64;
-            ch = update_regs<K, 64, 4, T, AND, FR>(G.inc_off, G.inc_ids, in, out, 1,
-                                               R, R < tile.hi, act, act_next, stamp, &ev, sum_next);
-            break;
-          }
-          default: {  // kBinWave8
-            const int64_t R = base + threadIdx.x / 64;
-            ch = update_regs<K, 64, 8, T, AND, FR>(G.inc_off, G.inc_ids, in, out, 1,
-                                               R, R < tile.hi, act, act_next, stamp, &ev, sum_next);
-            break;
-          }
-        }
-      }
-      n_ch += __popcll(ballot(ch));
-      n_ev += __popcll(ballot(ev));
-    }
-    stat_add_counts(sst, n_ch, n_ev);
-  }
-}
-
-// r-cliques with d_s >= 2048: one workgroup each, grid-stride over the list.
-template <int K, typename T, bool AND, bool FR>
-__global__ __launch_bounds__(kBlockThreads) void k_batch_hubs(
-    const BGraph *__restrict__ gs, const BHub *__restrict__ hubs,
-    const BState *__restrict__ st) {
-  __shared__ HubLds L;
-  const int64_t e = st->epoch;
-  const int nhubs = st->nhubs;
-  for (int i = blockIdx.x; i < nhubs; i += gridDim.x) {
-    const BHub hb = hubs[i];
-    const BGraph &G = gs[hb.g];
-    int64_t local;
-    if (!graph_live(G, e, &local)) continue;
-    const T *in = (const T *)G.tau[local & 1];
-    T *out = (T *)G.tau[AND ? (local & 1) : ((local + 1) & 1)];
-    SweepStats *sst = &G.ring[local % kBatchRing];
-    const uint8_t *act, *act_sum;
-    uint8_t *act_next, *sum_next, stamp;
-    graph_frontier<FR>(G, local, sst, &act, &act_next, &stamp, &act_sum,
-                       &sum_next);
-    if (FR && act != nullptr && act[hb.R] != stamp) continue;
-    const bool ch = update_hub<K, T, AND, FR>(G.inc_off, G.inc_ids, in, out, 1,
-                                              hb.R, L, act_next, stamp, sum_next,
-                                              Support());
-    stat_add(sst, ch, threadIdx.x == 0);
-  }
-}
-
-// Before an epoch: clear each live graph's counters.
-__global__ void k_epoch_begin(const BGraph *__restrict__ gs,
-                              const BState *__restrict__ st) {
+__global__ __launch_bounds__(kStepThreads) void k_epoch_step(
+    const BGraph *__restrict__ gs, BState *__restrict__ st) {
   const int64_t e = st->epoch;
   const int ng = st->ng;
-  const int i0 = blockIdx.x * blockDim.x + threadIdx.x;
-  for (int i = i0; i < ng; i += gridDim.x * blockDim.x) {
+  const int part = threadIdx.x % kStatParts;
+  for (int i = threadIdx.x / kStatParts; i < ng; i += kStepThreads / kStatParts) {
     const int64_t local = e - gs[i].t0;
-    if (local >= 0 && local < gs[i].max_local) {
-      SweepStats &z = gs[i].ring[local % kBatchRing];
-      for (int q = 0; q < kStatParts; q++) {
-        z.part[q].changed = 0;
-        z.part[q].evaluated = 0;
-      }
-      z.notified = 0;
+    if (local < 0 || local >= gs[i].max_local) continue;  // uniform over the 16
+    SweepStats &z = gs[i].ring[local % kBatchRing];
+    SweepStats &next = gs[i].ring[(local + 1) % kBatchRing];
+    unsigned long long c = z.part[part].changed;
+#pragma unroll
+    for (int off = kStatParts / 2; off > 0; off >>= 1) c += __shfl_xor(c, off, kStatParts);
+    next.part[part].changed = 0;
+    next.part[part].evaluated = 0;
+    if (part == 0) {
+      z.total = c;
+      next.notified = 0;
+      next.total = 0;
     }
   }
+  __syncthreads();
+  if (threadIdx.x == 0) st->epoch = e + 1;
 }
 
-__global__ void k_epoch_end(BState *__restrict__ st) { st->epoch += 1; }
-
-// Changed-counters of the last `n` epochs (ending before `e_end`), one row
-// of kPollMax per graph; ~0 marks a sweep the graph did not run.
+// How far each graph got in the last `n` epochs (ending before `e_end`): 2 x
+// its sweeps so far, plus 1 when the last of them changed nothing; 0 when it
+// ran none of them.
 __global__ void k_collect(const BGraph *__restrict__ gs, int ng, int64_t e_end,
-                          int n, unsigned long long *__restrict__ out) {
+                          int n, int64_t *__restrict__ out) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= ng) return;
-  for (int q = 0; q < n; q++) {
+  int64_t r = 0;
+  for (int q = 0; q < n && !(r & 1); q++) {
     const int64_t local = e_end - n + q - gs[i].t0;
-    unsigned long long v = ~0ull;
     if (local >= 0 && local < gs[i].max_local)
-      v = gs[i].ring[local % kBatchRing].changed_total();
-    out[(int64_t)i * kPollMax + q] = v;
+      r = 2 * (local + 1) + (gs[i].ring[local % kBatchRing].total == 0);
   }
+  out[i] = r;
+}
+
+// A member's start: tau_0 = d_s in its one or two arrays; no counts, stamps
+// or losses.
+template <typename T>
+__global__ __launch_bounds__(256) void k_member_init(
+    const int32_t *__restrict__ ds, int64_t nr, T *__restrict__ tau0,
+    T *__restrict__ tau1, uint4 *__restrict__ zero, int64_t nzero) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (int64_t i = t0; i < nr; i += stride) {
+    const T v = (T)ds[i];
+    tau0[i] = v;
+    if (tau1 != nullptr) tau1[i] = v;
+  }
+  for (int64_t i = t0; i < nzero; i += stride) zero[i] = make_uint4(0, 0, 0, 0);
 }
 
 struct TuneKey {
@@ -320,10 +156,6 @@ Batch::Batch(nd_ctx *ctx, nd_kind kind, nd_mode mode, bool tau16,
   ND_HIP(hipStreamWaitEvent(s_, ev, 0));
   (void)hipEventDestroy(ev);
   StreamScope scope(s_);
-  state_.reset(ctx->alloc, 1);
-  BState z{};
-  ND_HIP(hipMemcpyAsync(state_.p, &z, sizeof z, hipMemcpyHostToDevice, s_));
-  ND_HIP(hipStreamSynchronize(s_));
 }
 
 Batch::~Batch() {
@@ -332,10 +164,7 @@ Batch::~Batch() {
   {
     StreamScope scope(s_);
     members_.clear();
-    gs_.free();
-    tiles_.free();
-    hubs_.free();
-    state_.free();
+    tables_.free();
     poll_buf_.free();
   }
   ctx_->alloc.forget_stream(s_);
@@ -368,17 +197,44 @@ Member *Batch::add(nd_graph *g, int32_t max_iters, void *user) {
   m->t0 = epoch_;
   const int64_t cap = ks.nr + 1;  // Lemma 2: enough to observe convergence
   m->max_local = (max_iters < 0 || max_iters > cap) ? cap : max_iters;
-  const int64_t tb = (tau16_ ? 2 : 4) * std::max<int64_t>(ks.nr, 1);
-  m->tau0.reset(ctx_->alloc, tb);
-  if (mode_ == ND_SND) m->tau1.reset(ctx_->alloc, tb);
-  m->ring.reset(ctx_->alloc, kBatchRing);
-  if (frontier_) {
-    m->act0.reset(ctx_->alloc, std::max<int64_t>(ks.nr, 1));
-    m->act1.reset(ctx_->alloc, std::max<int64_t>(ks.nr, 1));
-    const int64_t ng = std::max<int64_t>((ks.nr + (1 << kGroupShift) - 1) >> kGroupShift, 1);
-    m->sum0.reset(ctx_->alloc, ng);
-    m->sum1.reset(ctx_->alloc, ng);
+  // The arrays in one block of memory: a batch of many small graphs would
+  // spend milliseconds in allocations and fills of a few bytes.
+  const int64_t nr = std::max<int64_t>(ks.nr, 1);
+  const int64_t ng = (nr + (1 << kGroupShift) - 1) >> kGroupShift;
+  auto place = [&](bool support) {
+    int64_t at = 0;
+    auto take = [&](int64_t bytes) {
+      uint8_t *p = m->mem.p ? m->mem.p + at : nullptr;
+      at += (bytes + 255) / 256 * 256;
+      return p;
+    };
+    const int64_t tb = tau16_ ? 2 : 4;
+    m->lost_shift = support ? lost_shift(ks) : 0;
+    m->tau[0] = take(tb * nr);
+    m->tau[1] = mode_ == ND_SND ? take(tb * nr) : nullptr;
+    m->slack = support ? take(tb * nr) : nullptr;
+    const int64_t z = at;
+    m->ring = (SweepStats *)take((int64_t)sizeof(SweepStats) * kBatchRing);
+    if (frontier_)
+      for (int i = 0; i < 2; i++) {
+        m->act[i] = take(nr << m->lost_shift);
+        m->sum[i] = take(ng);
+      }
+    m->zero = m->mem.p ? m->mem.p + z : nullptr;
+    m->zero_bytes = at - z;
+    return at;
+  };
+  bool support = frontier_;
+  if (support) {
+    try {
+      m->mem.reset(ctx_->alloc, place(true));
+    } catch (const Err &) {  // short of memory: flags alone take less
+      support = false;
+      m->mem.p = nullptr;
+    }
   }
+  if (!support) m->mem.reset(ctx_->alloc, place(false));
+  place(support);
   init_member_tau(*m);
   if (ks.nr == 0 || m->max_local == 0) {
     m->finished = true;
@@ -393,21 +249,17 @@ Member *Batch::add(nd_graph *g, int32_t max_iters, void *user) {
 void Batch::init_member_tau(Member &m) {
   const KindState &ks = m.g->ks[kind_];
   if (ks.nr == 0) return;
-  if (tau16_)
-    init_tau(ks, m.tau0.p, 2, s_);  // ks.tau16 holds (checked in add)
+  const unsigned grid = (unsigned)std::min<int64_t>(
+      grid_for(std::max<int64_t>(ks.nr, m.zero_bytes / 16), 256), 4096);
+  if (tau16_)  // ks.tau16 holds (checked in add)
+    k_member_init<uint16_t><<<grid, 256, 0, s_>>>(
+        ks.ds.p, ks.nr, (uint16_t *)m.tau[0], (uint16_t *)m.tau[1],
+        (uint4 *)m.zero, m.zero_bytes / 16);
   else
-    ND_HIP(hipMemcpyAsync(m.tau0.p, ks.ds.p, sizeof(int32_t) * ks.nr,
-                          hipMemcpyDeviceToDevice, s_));
-  if (mode_ == ND_SND)
-    ND_HIP(hipMemcpyAsync(m.tau1.p, m.tau0.p, (tau16_ ? 2 : 4) * ks.nr,
-                          hipMemcpyDeviceToDevice, s_));
-  if (frontier_) {  // no stamps yet
-    fill_u8(m.act0.p, 0, ks.nr, s_);
-    fill_u8(m.act1.p, 0, ks.nr, s_);
-    const int64_t ng = (ks.nr + (1 << kGroupShift) - 1) >> kGroupShift;
-    fill_u8(m.sum0.p, 0, ng, s_);
-    fill_u8(m.sum1.p, 0, ng, s_);
-  }
+    k_member_init<int32_t><<<grid, 256, 0, s_>>>(
+        ks.ds.p, ks.nr, (int32_t *)m.tau[0], (int32_t *)m.tau[1],
+        (uint4 *)m.zero, m.zero_bytes / 16);
+  ND_LAUNCHED();
 }
 
 std::vector<std::unique_ptr<Member>> Batch::take_finished() {
@@ -424,7 +276,6 @@ void Batch::rebuild() {
   StreamScope scope(s_);
   std::vector<BGraph> hg;
   std::vector<BTile> ht[kBinZero];  // per bin type; heaviest bins first
-  std::vector<BHub> hh;
   int64_t work = 0;
   // Tile length: tiles hold about equal work bounds (pass_units) and an
   // epoch has about grid * tiles_per_group of them -- each a workgroup of
@@ -433,7 +284,7 @@ void Batch::rebuild() {
   for (auto &mp : members_) {
     if (mp->finished) continue;
     const KindState &ks = mp->g->ks[kind_];
-    for (int b = kBinWave; b < kBinZero; b++)
+    for (int b = kBinBlock; b < kBinZero; b++)
       units_total += (ks.bin_hi[b] - ks.bin_lo[b] + rclq_per_pass(b) - 1) /
                      rclq_per_pass(b) * pass_units(b);
   }
@@ -450,27 +301,29 @@ void Batch::rebuild() {
     BGraph G{};
     G.inc_off = ks.inc_off.p;
     G.inc_ids = ks.inc_ids.p;
-    G.tau[0] = m.tau0.p;
-    G.tau[1] = mode_ == ND_SND ? m.tau1.p : m.tau0.p;
-    G.ring = m.ring.p;
+    G.tau[0] = m.tau[0];
+    G.tau[1] = mode_ == ND_SND ? m.tau[1] : m.tau[0];
+    G.ring = m.ring;
     G.t0 = m.t0;
     G.max_local = m.max_local;
     if (frontier_) {
-      G.act[0] = m.act0.p;
-      G.act[1] = m.act1.p;
-      G.act_sum[0] = m.sum0.p;
-      G.act_sum[1] = m.sum1.p;
+      for (int i = 0; i < 2; i++) {
+        G.act[i] = m.act[i];
+        G.act_sum[i] = m.sum[i];
+      }
+      G.slack = m.slack;
+      G.lost_shift = m.lost_shift;
       G.notify_below = notify_div_ <= 0
                            ? ~0ull
                            : (unsigned long long)(ks.bin_lo[kBinZero] / notify_div_);
     }
     hg.push_back(G);
     work += ks.P;
-    for (int64_t R = ks.bin_lo[kBinBlock]; R < ks.bin_hi[kBinBlock]; R++)
-      hh.push_back(BHub{gi, 0, R});
-    for (int b = kBinWave; b < kBinZero; b++) {
+    for (int b = kBinBlock; b < kBinZero; b++) {
       const int64_t lo = ks.bin_lo[b], hi = ks.bin_hi[b];
-      const int64_t passes = std::max<int64_t>(1, units / pass_units(b));
+      int64_t passes = std::max<int64_t>(1, units / pass_units(b));
+      // whole runs of the flat sweep (4 passes) where a tile has several
+      if (b >= kBinG64 && passes > 4) passes = passes / 4 * 4;
       const int64_t step = (int64_t)rclq_per_pass(b) * passes;
       for (int64_t x = lo; x < hi; x += step) {
         ht[b].push_back(BTile{gi, b, x, std::min(hi, x + step)});
@@ -478,89 +331,70 @@ void Batch::rebuild() {
       }
     }
   }
-  std::vector<BTile> all;
-  for (int b = kBinWave; b < kBinZero; b++)
-    all.insert(all.end(), ht[b].begin(), ht[b].end());
-  ntiles_ = (int)all.size();
-  nwide_ = (int)(ht[kBinWave].size() + ht[kBinWave16].size());  // first in `all`
-  nhubs_ = (int)hh.size();
+  int64_t nt = 0;
+  for (int b = kBinBlock; b < kBinZero; b++) nt += (int64_t)ht[b].size();
+  ntiles_ = (int)nt;
   ng_ = (int)hg.size();
   work_ = work;
   dead_tiles_ = 0;
-  // Grow device tables (capacity doubles); a new buffer invalidates the
-  // epoch graph, whose kernel nodes hold the table pointers.
-  auto ensure = [&](auto &arr, int64_t need, int64_t &cap) {
-    need = std::max<int64_t>(need, 1);
-    if (need > cap) {
-      cap = std::max<int64_t>(need, 2 * cap);
-      arr.reset(ctx_->alloc, cap);
-      drop_graph();
-    }
-  };
-  ensure(gs_, (int64_t)hg.size(), gs_cap_);
-  ensure(tiles_, (int64_t)all.size(), tiles_cap_);
-  ensure(hubs_, (int64_t)hh.size(), hubs_cap_);
-  ensure(poll_buf_, (int64_t)hg.size() * kPollMax, poll_cap_);
-  if (!hg.empty())
-    ND_HIP(hipMemcpyAsync(gs_.p, hg.data(), sizeof(BGraph) * hg.size(),
-                          hipMemcpyHostToDevice, s_));
-  if (!all.empty())
-    ND_HIP(hipMemcpyAsync(tiles_.p, all.data(), sizeof(BTile) * all.size(),
-                          hipMemcpyHostToDevice, s_));
-  if (!hh.empty())
-    ND_HIP(hipMemcpyAsync(hubs_.p, hh.data(), sizeof(BHub) * hh.size(),
-                          hipMemcpyHostToDevice, s_));
-  // grids of the two tile kernels: the capacity of their tile ranges
-  auto ensure_grid = [&](int64_t need, int64_t &cap) {
-    need = std::max<int64_t>(need, 1);
-    if (need > cap) {
-      cap = std::max<int64_t>(need, 2 * cap);
-      drop_graph();
-    }
-  };
-  ensure_grid(nwide_, wide_grid_);
-  ensure_grid((int64_t)ntiles_ - nwide_, narrow_grid_);
-  int32_t counts[4] = {ntiles_, nhubs_, ng_, nwide_};
-  ND_HIP(hipMemcpyAsync(&state_.p->ntiles, counts, sizeof counts,
-                        hipMemcpyHostToDevice, s_));
+  // Grow the device tables (capacities double); a new buffer, or a larger
+  // grid, invalidates the epoch graph, whose kernel nodes hold them.
+  if (tables_.p == nullptr || ng_ > gs_cap_ || nt > tiles_cap_) {
+    if (ng_ > gs_cap_ || gs_cap_ == 0) gs_cap_ = std::max<int64_t>(std::max(ng_, 1), 2 * gs_cap_);
+    if (nt > tiles_cap_ || tiles_cap_ == 0)
+      tiles_cap_ = std::max<int64_t>(std::max<int64_t>(nt, 1), 2 * tiles_cap_);
+    const int64_t gs_at = 256;
+    const int64_t tiles_at = (gs_at + (int64_t)sizeof(BGraph) * gs_cap_ + 255) / 256 * 256;
+    tables_.reset(ctx_->alloc, tiles_at + (int64_t)sizeof(BTile) * tiles_cap_);
+    poll_buf_.reset(ctx_->alloc, gs_cap_);
+    state_ = (BState *)tables_.p;
+    gs_ = (BGraph *)(tables_.p + gs_at);
+    tiles_ = (BTile *)(tables_.p + tiles_at);
+    drop_graph();
+  }
+  // one copy: state, graphs, tiles heaviest bins first
+  const size_t tiles_at = (uint8_t *)tiles_ - tables_.p;
+  std::vector<uint8_t> host(tiles_at + sizeof(BTile) * (size_t)nt);
+  const BState z{epoch_, ntiles_, ng_};
+  memcpy(host.data(), &z, sizeof z);
+  memcpy(host.data() + ((uint8_t *)gs_ - tables_.p), hg.data(), sizeof(BGraph) * hg.size());
+  size_t at = tiles_at;
+  for (int b = kBinBlock; b < kBinZero; b++) {
+    if (ht[b].empty()) continue;
+    memcpy(host.data() + at, ht[b].data(), sizeof(BTile) * ht[b].size());
+    at += sizeof(BTile) * ht[b].size();
+  }
+  ND_HIP(hipMemcpyAsync(tables_.p, host.data(), host.size(), hipMemcpyHostToDevice, s_));
   ND_HIP(hipStreamSynchronize(s_));  // the host vectors go out of scope
   dirty_ = false;
 }
 
-// The kernels of one epoch, in launch order, for the batch's instance.
-struct EpochKernels {
-  const void *fn[5];  // begin, wide tiles, other tiles, hubs, end
-};
-
-template <int K, typename T, bool AND, bool FR>
-EpochKernels epoch_kernels_t() {
-  return {{(const void *)k_epoch_begin,
-           (const void *)k_batch_sweep<K, T, AND, FR, true>,
-           (const void *)k_batch_sweep<K, T, AND, FR, false>,
-           (const void *)k_batch_hubs<K, T, AND, FR>, (const void *)k_epoch_end}};
+void Batch::upload_state(int64_t epoch) {
+  const BState z{epoch, ntiles_, ng_};
+  ND_HIP(hipMemcpyAsync(state_, &z, sizeof z, hipMemcpyHostToDevice, s_));
+  ND_HIP(hipStreamSynchronize(s_));
 }
 
+// The kernels of one epoch, in launch order, for the batch's instance.
+struct EpochKernels {
+  const void *fn[2];  // tiles, step
+};
+
 static EpochKernels epoch_kernels(int k, bool tau16, bool and_mode, bool fr) {
-  const int key = (k * 2 + (tau16 ? 1 : 0)) * 4 + (and_mode ? 2 : 0) + (fr ? 1 : 0);
-#define ND_EPOCH_CASES(KK, T, BASE)                                 \
-  case BASE + 0: return epoch_kernels_t<KK, T, false, false>();    \
-  case BASE + 1: return epoch_kernels_t<KK, T, false, true>();     \
-  case BASE + 2: return epoch_kernels_t<KK, T, true, false>();     \
-  case BASE + 3: return epoch_kernels_t<KK, T, true, true>();
-  switch (key) {
-    ND_EPOCH_CASES(1, int32_t, 8)
-    ND_EPOCH_CASES(1, uint16_t, 12)
-    ND_EPOCH_CASES(2, int32_t, 16)
-    ND_EPOCH_CASES(2, uint16_t, 20)
-    ND_EPOCH_CASES(3, int32_t, 24)
-    ND_EPOCH_CASES(3, uint16_t, 28)
-    ND_EPOCH_CASES(5, int32_t, 40)
-    ND_EPOCH_CASES(5, uint16_t, 44)
-    default: break;
+  const void *f = nullptr;
+  switch (k * 2 + (tau16 ? 1 : 0)) {
+    case 2: f = batch_kernel<1, int32_t>(and_mode, fr); break;
+    case 3: f = batch_kernel<1, uint16_t>(and_mode, fr); break;
+    case 4: f = batch_kernel<2, int32_t>(and_mode, fr); break;
+    case 5: f = batch_kernel<2, uint16_t>(and_mode, fr); break;
+    case 6: f = batch_kernel<3, int32_t>(and_mode, fr); break;
+    case 7: f = batch_kernel<3, uint16_t>(and_mode, fr); break;
+    case 10: f = batch_kernel<5, int32_t>(and_mode, fr); break;
+    case 11: f = batch_kernel<5, uint16_t>(and_mode, fr); break;
+    default:
+      ND_REQUIRE(false, ND_ERR_INVALID, "no batch kernel for k=%d", k);
   }
-#undef ND_EPOCH_CASES
-  ND_REQUIRE(false, ND_ERR_INVALID, "bad batch key %d", key);
-  return {};
+  return {{f, (const void *)k_epoch_step}};
 }
 
 // Grid, block and arguments of kernel i of an epoch.  The argument values
@@ -568,31 +402,23 @@ static EpochKernels epoch_kernels(int k, bool tau16, bool and_mode, bool fr) {
 struct EpochLaunch {
   const BGraph *gs;
   const BTile *tiles;
-  const BHub *hubs;
   BState *st;
-  void *a_begin[2], *a_tiles[3], *a_hubs[3], *a_end[1];
-  dim3 grid[5], block[5];
-  void **args[5];
-  EpochLaunch(const BGraph *g, const BTile *t, const BHub *h, BState *s,
-              int64_t wide_grid, int64_t narrow_grid)
-      : gs(g), tiles(t), hubs(h), st(s) {
-    a_begin[0] = &gs;
-    a_begin[1] = &st;
+  void *a_tiles[3], *a_step[2];
+  dim3 grid[2], block[2];
+  void **args[2];
+  EpochLaunch(const BGraph *g, const BTile *t, BState *s, int64_t tile_grid)
+      : gs(g), tiles(t), st(s) {
     a_tiles[0] = &gs;
     a_tiles[1] = &tiles;
     a_tiles[2] = &st;
-    a_hubs[0] = &gs;
-    a_hubs[1] = &hubs;
-    a_hubs[2] = &st;
-    a_end[0] = &st;
-    void **a[5] = {a_begin, a_tiles, a_tiles, a_hubs, a_end};
-    const int64_t gr[5] = {kBeginGrid, wide_grid, narrow_grid, kHubGrid, 1};
-    const int bl[5] = {256, 256, 256, kBlockThreads, 1};
-    for (int i = 0; i < 5; i++) {
-      args[i] = a[i];
-      grid[i] = dim3((unsigned)gr[i]);
-      block[i] = dim3(bl[i]);
-    }
+    a_step[0] = &gs;
+    a_step[1] = &st;
+    args[0] = a_tiles;
+    args[1] = a_step;
+    grid[0] = dim3((unsigned)tile_grid);
+    grid[1] = dim3(1);
+    block[0] = dim3(256);
+    block[1] = dim3(kStepThreads);
   }
   EpochLaunch(const EpochLaunch &) = delete;
 };
@@ -600,8 +426,8 @@ struct EpochLaunch {
 void Batch::launch_epoch() {
   const EpochKernels ek =
       epoch_kernels(kind_rs(kind_).k, tau16_, mode_ == ND_AND, frontier_);
-  EpochLaunch el(gs_.p, tiles_.p, hubs_.p, state_.p, wide_grid_, narrow_grid_);
-  for (int i = 0; i < 5; i++) {
+  EpochLaunch el(gs_, tiles_, state_, tiles_cap_);
+  for (int i = 0; i < 2; i++) {
     ND_HIP(hipLaunchKernel(ek.fn[i], el.grid[i], el.block[i], el.args[i], 0, s_));
   }
 }
@@ -613,12 +439,12 @@ void Batch::launch_epoch() {
 void Batch::build_graph() {
   const EpochKernels ek =
       epoch_kernels(kind_rs(kind_).k, tau16_, mode_ == ND_AND, frontier_);
-  EpochLaunch el(gs_.p, tiles_.p, hubs_.p, state_.p, wide_grid_, narrow_grid_);
+  EpochLaunch el(gs_, tiles_, state_, tiles_cap_);
   hipGraph_t gr = nullptr;
   bool ok = hipGraphCreate(&gr, 0) == hipSuccess;
   hipGraphNode_t prev = nullptr;
   for (int e = 0; ok && e < kGraphEpochs; e++)
-    for (int i = 0; ok && i < 5; i++) {
+    for (int i = 0; ok && i < 2; i++) {
       hipKernelNodeParams np{};
       np.func = const_cast<void *>(ek.fn[i]);
       np.gridDim = el.grid[i];
@@ -658,25 +484,29 @@ void Batch::run_epochs(int count) {
 void Batch::poll(int epochs_run) {
   if (ng_ == 0 || epochs_run <= 0) return;
   ND_REQUIRE(epochs_run <= kPollMax, ND_ERR_INVALID, "poll window too large");
-  k_collect<<<grid_for(ng_, 256), 256, 0, s_>>>(gs_.p, ng_, epoch_, epochs_run,
+  k_collect<<<grid_for(ng_, 256), 256, 0, s_>>>(gs_, ng_, epoch_, epochs_run,
                                                  poll_buf_.p);
   ND_LAUNCHED();
-  std::vector<unsigned long long> h((size_t)ng_ * kPollMax);
-  ND_HIP(hipMemcpyAsync(h.data(), poll_buf_.p, sizeof(unsigned long long) * h.size(),
-                        hipMemcpyDeviceToHost, s_));
-  ND_HIP(hipStreamSynchronize(s_));
+  PinnedChunk pc;
+  std::vector<int64_t> many;
+  const int64_t *h;
+  if (sizeof(int64_t) * ng_ <= PinnedChunk::kBytes) {
+    h = pc.read(poll_buf_.p, (size_t)ng_, s_);
+  } else {
+    many.resize(ng_);
+    ND_HIP(hipMemcpyAsync(many.data(), poll_buf_.p, sizeof(int64_t) * many.size(),
+                          hipMemcpyDeviceToHost, s_));
+    ND_HIP(hipStreamSynchronize(s_));
+    h = many.data();
+  }
   for (auto &mp : members_) {
     Member &m = *mp;
     if (m.finished || m.slot < 0) continue;
-    for (int q = 0; q < epochs_run && !m.finished; q++) {
-      const int64_t local = epoch_ - epochs_run + q - m.t0;
-      const unsigned long long v = h[(size_t)m.slot * kPollMax + q];
-      if (local < 0 || local >= m.max_local || v == ~0ull) continue;
-      m.sweeps = local + 1;
-      if (v == 0) {
-        m.converged = true;
-        m.finished = true;
-      }
+    const int64_t v = h[m.slot];
+    if (v != 0) m.sweeps = v / 2;
+    if (v & 1) {
+      m.converged = true;
+      m.finished = true;
     }
     if (!m.finished && m.sweeps >= m.max_local) m.finished = true;
     if (m.finished) dead_tiles_ += m.ntiles;
@@ -686,8 +516,7 @@ void Batch::poll(int epochs_run) {
 }
 
 const void *Batch::result_tau(const Member &m) const {
-  if (mode_ == ND_AND) return m.tau0.p;
-  return (m.sweeps & 1) ? m.tau1.p : m.tau0.p;
+  return m.tau[mode_ == ND_SND ? m.sweeps & 1 : 0];
 }
 
 void Batch::set_config(const BatchConfig &c) {
@@ -751,13 +580,7 @@ int Batch::autotune() {
         c.tiles_per_group = tpg;
         set_config(c);
         rebuild();
-        BState z{};
-        z.epoch = e0;
-        z.ntiles = ntiles_;
-        z.nhubs = nhubs_;
-        z.ng = ng_;
-        z.nwide = nwide_;
-        ND_HIP(hipMemcpyAsync(state_.p, &z, sizeof z, hipMemcpyHostToDevice, s_));
+        upload_state(e0);
         const float ms = time_epoch();
         if (ms < best) {
           best = ms;
@@ -767,14 +590,7 @@ int Batch::autotune() {
     for (auto &mp : members_) init_member_tau(*mp);
     set_config(best_cfg);
     rebuild();
-    BState z{};
-    z.epoch = e0;
-    z.ntiles = ntiles_;
-    z.nhubs = nhubs_;
-    z.ng = ng_;
-    z.nwide = nwide_;
-    ND_HIP(hipMemcpyAsync(state_.p, &z, sizeof z, hipMemcpyHostToDevice, s_));
-    ND_HIP(hipStreamSynchronize(s_));
+    upload_state(e0);
   }
   (void)hipEventDestroy(a);
   (void)hipEventDestroy(b);

@@ -1,0 +1,107 @@
+// batch_kernels.h -- the batches' tile kernel for one k = C(s,r) - 1 and one
+// type of tau, compiled beside the one-graph sweeps (sweep_inst.hip).
+// Internal header.
+#pragma once
+
+#include "batch.h"
+#include "sweep_kernels.h"
+
+namespace nd {
+
+namespace {
+
+// One epoch's tiles, one workgroup per tile (the grid is the table's
+// capacity, surplus workgroups exit at once).  Workgroups are short-lived, so
+// the work of other streams (a server's preparations) is dispatched between
+// them rather than waiting for the epoch to end.  A tile is swept as the
+// one-graph sweep would sweep it (sweep_kernels.h): flat while nothing is
+// flagged, then by flags or support counts.
+template <int K, typename T, bool AND, bool FR>
+__global__ __launch_bounds__(256, 6) void k_batch_sweep(
+    const BGraph *__restrict__ gs, const BTile *__restrict__ tiles,
+    const BState *__restrict__ st) {
+  __shared__ union {
+    FlatLds<T> flat;
+    HubLds hub;
+  } lds;
+  const int ti = (int)blockIdx.x;
+  if (ti >= st->ntiles) return;
+  const BTile tile = tiles[ti];
+  const BGraph &G = gs[tile.g];
+  const int64_t local = st->epoch - G.t0;
+  if (local < 0 || local >= G.max_local) return;
+  const SweepStats *prev = local > 0 ? &G.ring[(local - 1) % kBatchRing] : nullptr;
+  const unsigned long long pc = prev != nullptr ? prev->total : 1;
+  if (pc == 0) return;  // converged
+  SweepArgs a{};
+  a.inc_off = G.inc_off;
+  a.inc_ids = G.inc_ids;
+  a.tau_in = G.tau[local & 1];
+  a.tau_out = G.tau[AND ? (local & 1) : ((local + 1) & 1)];
+  a.stats = &G.ring[local % kBatchRing];
+  a.cap_by_tau = 1;
+  a.stamp = sweep_stamp(local);
+  // frontier state of this graph's sweep: the rule of the one-graph sweep
+  const uint8_t *act = nullptr, *act_sum = nullptr;
+  uint8_t *act_next = nullptr, *sum_next = nullptr;
+  Support sp;
+  if (FR && prev != nullptr) {
+    const bool valid = prev->notified != 0;
+    if (valid) {
+      act = G.act[local & 1];
+      act_sum = G.act_sum[local & 1];
+    }
+    if (valid || pc <= G.notify_below) {
+      act_next = G.act[(local + 1) & 1];
+      sum_next = G.act_sum[(local + 1) & 1];
+      if (threadIdx.x == 0) a.stats->notified = 1;
+      if (G.slack != nullptr) {
+        sp.slack = G.slack;
+        sp.lost = G.act[local & 1];
+        sp.lost_next = act_next;
+        sp.shift = (int)G.lost_shift;
+      }
+    }
+  }
+  switch (tile.type) {
+    case kBinBlock:
+    case kBinWave:
+      sweep_hubs<K, T, AND, FR>(a, tile.lo, tile.hi, 0, 1, act, act_next, sum_next,
+                                sp, lds.hub);
+      break;
+    case kBinWave16:
+    case kBinWave8:
+      sweep_bin<K, 64, 0, T, AND, FR>(a, tile.lo, tile.hi, 0, 1, act, act_next,
+                                      act_sum, sum_next, sp, &lds.flat, false);
+      break;
+    case kBinG64:
+      sweep_bin<K, 64, 4, T, AND, FR>(a, tile.lo, tile.hi, 0, 1, act, act_next,
+                                      act_sum, sum_next, sp, &lds.flat, false);
+      break;
+    case kBinG16:
+      sweep_bin<K, 16, 4, T, AND, FR>(a, tile.lo, tile.hi, 0, 1, act, act_next,
+                                      act_sum, sum_next, sp, &lds.flat, false);
+      break;
+    case kBinG4:
+      sweep_bin<K, 4, 4, T, AND, FR>(a, tile.lo, tile.hi, 0, 1, act, act_next,
+                                     act_sum, sum_next, sp, &lds.flat, false);
+      break;
+    default:  // kBinG1
+      sweep_bin<K, 1, 4, T, AND, FR>(a, tile.lo, tile.hi, 0, 1, act, act_next,
+                                     act_sum, sum_next, sp, &lds.flat, false);
+      break;
+  }
+}
+
+}  // namespace
+
+template <int K, typename T>
+const void *batch_kernel(bool and_mode, bool fr) {
+  if (and_mode)
+    return fr ? (const void *)k_batch_sweep<K, T, true, true>
+              : (const void *)k_batch_sweep<K, T, true, false>;
+  return fr ? (const void *)k_batch_sweep<K, T, false, true>
+            : (const void *)k_batch_sweep<K, T, false, false>;
+}
+
+}  // namespace nd

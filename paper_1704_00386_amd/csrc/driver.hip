@@ -163,13 +163,6 @@ bool wants_indicator(const nd_opts &o, bool fixed_set) {
   return !fixed_set && (o.count_active != 0 || o.stop_active_ratio > 0);
 }
 
-// Bytes (log2) of a lost-s-clique counter: at most k d_s are counted for one
-// r-clique in one sweep.
-int lost_shift(const KindState &ks) {
-  const int64_t most = (int64_t)ks.k * ks.max_ds;
-  return most <= 255 ? 0 : most <= 65535 ? 1 : 2;
-}
-
 // Byte sizes of the buffers of a decomposition, each rounded to 256.
 struct LoopLayout {
   int64_t tau, flags, sums, ring, snap, stage;

@@ -328,7 +328,8 @@ struct SweepStats {
   unsigned long long notified;  // 1: this sweep set the next sweep's flags
   unsigned long long active;    // r-cliques flagged for the next sweep
                                 // (counted after the sweep when asked for)
-  unsigned long long pad[14];
+  unsigned long long total;     // batches: changed_total(), summed once
+  unsigned long long pad[13];
   __host__ __device__ unsigned long long changed_total() const {
     unsigned long long s = 0;
     for (int i = 0; i < kStatParts; i++) s += part[i].changed;
@@ -417,6 +418,13 @@ void launch_group_sums(const KindState &ks, const SweepArgs &a, hipStream_t s);
 // Host threads (each with a stream) that build or prepare several graphs
 // at once: 2, or ND_PREP_THREADS.
 int prep_threads();
+
+// Bytes (log2) of a lost-s-clique counter: at most k d_s are counted for one
+// r-clique in one sweep.
+inline int lost_shift(const KindState &ks) {
+  const int64_t most = (int64_t)ks.k * ks.max_ds;
+  return most <= 255 ? 0 : most <= 65535 ? 1 : 2;
+}
 
 // Frontier switch: notifications start once a sweep changes at most
 // 1/d of the swept r-cliques; d = 8 for SND and AND (measured on the three

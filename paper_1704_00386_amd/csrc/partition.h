@@ -25,6 +25,9 @@ constexpr int kPartThreads = 256;
 constexpr int kPartTile = kPartThreads * kPartItems;  // 4096
 constexpr int kPartBig = 1024;
 constexpr int64_t kPartOne = (int64_t)kPartBig * kPartItems;  // 16384
+// Up to this many workgroups each adds up the counts before it, one thread a
+// bin; the launch that would scan them takes longer.
+constexpr int64_t kPartSelf = 64;
 
 // Where the partition ends up on the host's side: the first item of every
 // bin, the total, and the largest of the values that `most` gives.
@@ -88,12 +91,14 @@ __global__ __launch_bounds__(kPartThreads) void k_part_count(
   if (t == NB) block_most[blockIdx.x] = max(max(cm[0], cm[1]), max(cm[2], cm[3]));
 }
 
-// Out: put(i, place) of item i.  off: the scanned counts, NULL for the only
-// workgroup, which counts for itself.  Workgroup 0 also writes the head.
+// Out: put(i, place) of item i.  off: the scanned counts, or NULL: the
+// workgroup adds up `count` itself (NULL too for the only workgroup, which
+// counts for itself).  Workgroup 0 also writes the head.
 template <int NB, int NT, typename In, typename Out>
 __global__ __launch_bounds__(NT) void k_part_place(
-    In in, Out out, int64_t n, int64_t nb, const int64_t *__restrict__ off,
-    const int32_t *__restrict__ block_most, Head *__restrict__ head) {
+    In in, Out out, int64_t n, int64_t nb, const int32_t *__restrict__ count,
+    const int64_t *__restrict__ off, const int32_t *__restrict__ block_most,
+    Head *__restrict__ head) {
   constexpr int kWaves = NT / kWave;
   __shared__ int32_t c[kWaves][kMaxBins];
   __shared__ int32_t cm[kWaves];
@@ -115,6 +120,8 @@ __global__ __launch_bounds__(NT) void k_part_place(
   if (lane == 0) cm[w] = most;
   __syncthreads();
   // bin t: its waves' starts within the workgroup, its start
+  __shared__ int64_t first[NB];  // of the whole bins, without `off`
+  int64_t before = 0;            // bin t's items of earlier workgroups
   if (t < NB) {
     int32_t run = 0;
     for (int x = 0; x < kWaves; x++) {
@@ -122,18 +129,33 @@ __global__ __launch_bounds__(NT) void k_part_place(
       c[x][t] = run;
       run += y;
     }
-    at[t] = off != nullptr ? off[t * nb + blockIdx.x] : run;
+    if (off != nullptr) {
+      at[t] = off[t * nb + blockIdx.x];
+    } else {
+      int64_t all = run;
+      if (count != nullptr) {
+        all = 0;
+        for (int b = 0; b < (int)nb; b++) {
+          const int32_t y = count[t * nb + b];
+          before += b < (int)blockIdx.x ? y : 0;
+          all += y;
+        }
+      }
+      first[t] = all;
+    }
   }
   __syncthreads();
   if (off == nullptr) {  // the bins' totals to their starts
     if (t == 0) {
       int64_t run = 0;
       for (int b = 0; b < NB; b++) {
-        const int64_t y = at[b];
-        at[b] = run;
+        const int64_t y = first[b];
+        first[b] = run;
         run += y;
       }
     }
+    __syncthreads();
+    if (t < NB) at[t] = first[t] + before;
     __syncthreads();
   }
 #pragma unroll
@@ -141,9 +163,9 @@ __global__ __launch_bounds__(NT) void k_part_place(
     if (bin[r] >= 0)
       out.put(base + r * kWave, (int32_t)at[bin[r]] + c[w][bin[r]] + rank[r]);
   if (blockIdx.x != 0) return;
-  if (t < NB) head->start[t] = off != nullptr ? off[t * nb] : at[t];
+  if (t < NB) head->start[t] = off != nullptr ? off[t * nb] : first[t];
   int32_t m = 0;
-  if (off != nullptr) {
+  if (block_most != nullptr) {
     for (int64_t x = t; x < nb; x += NT) m = max(m, block_most[x]);
 #pragma unroll
     for (int o = kWave / 2; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, kWave));
@@ -168,18 +190,22 @@ void run(const In &in, const Out &out, int64_t n, Head *head, hipStream_t s,
              "%lld items: places must fit int32", (long long)n);
   if (n <= kPartOne) {
     k_part_place<NB, kPartBig><<<1, kPartBig, 0, s>>>(in, out, n, 1, nullptr,
-                                                      nullptr, head);
+                                                      nullptr, nullptr, head);
     ND_LAUNCHED();
     return;
   }
   const int64_t nb = ceil_div(n, kPartTile);
+  const bool self = nb <= kPartSelf;
   DArr<int32_t> count(al, NB * nb), most(al, nb);
-  DArr<int64_t> off(al, NB * nb + 1);
+  DArr<int64_t> off;
   k_part_count<NB><<<(unsigned)nb, kPartThreads, 0, s>>>(in, n, nb, count.p, most.p);
   ND_LAUNCHED();
-  exclusive_scan_i32(count.p, off.p, NB * nb, s, al);
+  if (!self) {
+    off.reset(al, NB * nb + 1);
+    exclusive_scan_i32(count.p, off.p, NB * nb, s, al);
+  }
   k_part_place<NB, kPartThreads><<<(unsigned)nb, kPartThreads, 0, s>>>(
-      in, out, n, nb, off.p, most.p, head);
+      in, out, n, nb, count.p, off.p, most.p, head);
   ND_LAUNCHED();
 }
 

@@ -239,10 +239,15 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_hist(
 // leave it in runs of consecutive addresses: bound by its 16 bytes a key.
 // (Storing each key straight to its place took three barriers per 256 keys
 // and wrote 8-byte pieces: 2.35 ms for 268 million keys, 1.8 TB/s; now 1.21
-// ms, 3.6 TB/s.)
+// ms, 3.6 TB/s.)  Up to kSortSelf tiles there are no scanned offsets: every
+// workgroup adds up the histogram itself (thread d the row of digit d), which
+// is quicker than the launch that would scan it.
+constexpr int64_t kSortSelf = 64;
+
 __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
     const uint64_t *__restrict__ in, uint64_t *__restrict__ out, int64_t n,
-    int shift, const int64_t *__restrict__ offs, int64_t nb) {
+    int shift, const int32_t *__restrict__ hist,
+    const int64_t *__restrict__ offs, int64_t nb) {
   __shared__ uint64_t keys[kSortTile];
   __shared__ int32_t cnt[kSortWaves][256];
   __shared__ int32_t start[256];  // first place of each digit in the tile
@@ -251,7 +256,31 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
   const int tid = threadIdx.x, lane = lane_id(), w = tid / kWave;
   const int64_t base = (int64_t)blockIdx.x * kSortTile;
   const int total = (int)std::min<int64_t>(kSortTile, n - base);
-  const int64_t goff = offs[(int64_t)tid * nb + blockIdx.x];
+  int64_t goff;
+  if (offs != nullptr) {
+    goff = offs[(int64_t)tid * nb + blockIdx.x];
+  } else {
+    int32_t all = 0, before = 0;  // of digit tid
+    const int32_t *row = hist + (int64_t)tid * nb;
+    for (int b = 0; b < (int)nb; b++) {
+      const int32_t c = row[b];
+      before += b < (int)blockIdx.x ? c : 0;
+      all += c;
+    }
+    int32_t inc = all;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+      const int32_t y = __shfl_up(inc, off, kWave);
+      if (lane >= off) inc += y;
+    }
+    if (lane == kWave - 1) ws[w] = inc;
+    __syncthreads();
+    int32_t lower = inc - all;
+#pragma unroll
+    for (int x = 0; x < kSortWaves; x++) lower += x < w ? ws[x] : 0;
+    goff = lower + before;
+    __syncthreads();  // ws is used again
+  }
 #pragma unroll
   for (int x = 0; x < 256 / kWave; x++) cnt[w][x * kWave + lane] = 0;
   uint64_t key[kSortItems];
@@ -370,16 +399,18 @@ uint64_t *radix_sort_u64(uint64_t *keys, uint64_t *tmp, int64_t n, int lo_bit,
   const int64_t nb = ceil_div(n, kSortTile);
   ND_REQUIRE(nb * 256 < (int64_t)1 << 31, ND_ERR_INVALID,
              "radix sort: %lld keys is too many", (long long)n);
+  const bool self = nb <= kSortSelf;
   DArr<int32_t> hist(al, 256 * nb);
-  DArr<int64_t> offs(al, 256 * nb + 1);
+  DArr<int64_t> offs;
+  if (!self) offs.reset(al, 256 * nb + 1);
   uint64_t *src = keys, *dst = tmp;
   for (int shift = lo_bit; shift < hi_bit; shift += 8) {
     k_radix_hist<<<(unsigned)nb, kSortThreads, 0, s>>>(src, n, shift, hist.p,
                                                         nb);
     ND_LAUNCHED();
-    exclusive_scan_i32(hist.p, offs.p, 256 * nb, s, al);
+    if (!self) exclusive_scan_i32(hist.p, offs.p, 256 * nb, s, al);
     k_radix_scatter<<<(unsigned)nb, kSortThreads, 0, s>>>(src, dst, n, shift,
-                                                           offs.p, nb);
+                                                           hist.p, offs.p, nb);
     ND_LAUNCHED();
     uint64_t *t = src;
     src = dst;
