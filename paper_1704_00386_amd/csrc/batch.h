@@ -51,7 +51,7 @@ const void *batch_kernel(bool and_mode, bool fr);
 // about equal work (one workgroup each).
 struct BatchConfig {
   int grid = 2048;
-  int tiles_per_group = 8;
+  int tiles_per_group = 2;
 };
 
 // One graph taking part in a batch.

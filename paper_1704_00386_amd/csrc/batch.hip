@@ -181,7 +181,7 @@ void Batch::drop_graph() {
 BatchConfig Batch::default_config(nd_ctx *ctx) {
   BatchConfig c;
   c.grid = ctx->num_cu * 8;
-  c.tiles_per_group = 8;
+  c.tiles_per_group = 2;
   return c;
 }
 
@@ -574,7 +574,7 @@ int Batch::autotune() {
   } else {
     const int cus = ctx_->num_cu;
     for (int gm : {4, 8, 16})
-      for (int tpg : {4, 16}) {
+      for (int tpg : {1, 4}) {
         BatchConfig c;
         c.grid = cus * gm;
         c.tiles_per_group = tpg;
