@@ -24,7 +24,8 @@ CEIL_LIB = os.path.join(HERE, "libndceil.so")
 CEIL_SRC = "ceiling.hip"
 
 SOURCES = ["api.hip", "prim.hip", "graph.hip", "cliques.hip", "layout.hip",
-           "sweep.hip", "driver.hip", "partial.hip", "levels.hip", "batch.hip", "server.hip"]
+           "sweep.hip", "tiny.hip", "driver.hip", "partial.hip", "levels.hip", "batch.hip",
+           "server.hip"]
 
 # sweep_inst.hip once per k = C(s,r) - 1 and type of tau
 SWEEP_SRC = "sweep_inst.hip"

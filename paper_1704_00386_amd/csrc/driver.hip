@@ -31,7 +31,8 @@ namespace {
 constexpr int kStatsRing = 1024;  // device counters kept per decomposition
 constexpr int kStaticRing = 64;   // the same, in the static workspace
 constexpr int kMaxChunk = 16;     // sweeps enqueued per host round trip
-static_assert(kMaxChunk <= kWave && kMaxChunk < kStaticRing && kStaticRing <= kHostStatsRing &&
+static_assert(kTinySweeps <= kWave && kTinySweeps < kStaticRing &&
+                  kMaxChunk <= kTinySweeps && kStaticRing <= kHostStatsRing &&
                   kStatsRing <= kHostStatsRing,
               "a chunk and its predecessor must fit every counter ring");
 constexpr int64_t kSumsDiv = 256;  // see sums_after in sweep_loop
@@ -254,7 +255,10 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
   // on shorter ones the round trip costs more than it saves.
   bool plain = flags && !indicator;
   const bool watch = plain && ks.P * ks.k >= kWatchGathers;
-  int chunk = step_by_step || watch ? 1 : 2;
+  // Small graphs: every sweep in one workgroup's LDS (tiny.hip).  SND only:
+  // AND's sweeps pass values on within a sweep and so are fewer.
+  const bool tiny = !and_mode && !flags && !step_by_step && tiny_fits(ks);
+  int chunk = tiny ? kTinySweeps : step_by_step || watch ? 1 : 2;
   int64_t t = 0;  // sweeps enqueued
   int64_t sweeps = 0, updates = 0;
   bool converged = false, stop_ratio = false, stop_cb = false;
@@ -278,7 +282,11 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
     k_zero_stats<<<1, 256, 0, s>>>(b.ring, ring_len, t, nb);
     ND_LAUNCHED();
     const int64_t t0 = t;
-    for (int i = 0; i < nb; i++, t++) {
+    if (tiny) {
+      launch_tiny(ks, b.tau[t & 1], b.tau[0], b.tau[1], b.ring, ring_len, t, nb, s);
+      t += nb;
+    }
+    for (int i = 0; i < nb && !tiny; i++, t++) {
       SweepArgs a{};
       a.inc_off = ks.inc_off.p;
       a.inc_ids = ks.inc_ids.p;
@@ -367,7 +375,8 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
     if (sums_after != 0 && hst[(t - 1) % ring_len].notified &&
         hst[(t - 1) % ring_len].changed < sums_after)
       sums_after = 0;
-    chunk = std::min(chunk * 2, step_by_step || (watch && plain) ? 1 : kMaxChunk);
+    if (!tiny)
+      chunk = std::min(chunk * 2, step_by_step || (watch && plain) ? 1 : kMaxChunk);
   }
   ND_HIP(hipEventRecord(ev[1], s));
   r.ms_iterate = elapsed_ms(ev[0], ev[1]);

@@ -415,6 +415,17 @@ void launch_sweep(const KindState &ks, const SweepArgs &a, bool and_mode,
 // wrote, when a.sums_after made it skip them; nothing otherwise.
 void launch_group_sums(const KindState &ks, const SweepArgs &a, hipStream_t s);
 
+// Plain SND sweeps (no notifications, no callback) of a graph that fits one
+// workgroup's LDS: up to kTinySweeps per launch (tiny.hip).  The values after
+// the last sweep go to tau0 and tau1.
+constexpr int kTinyRcliques = 8192;   // swept ones
+constexpr int kTinyIncidence = 20480;
+constexpr int kTinySweeps = 32;
+bool tiny_fits(const KindState &ks);
+void launch_tiny(const KindState &ks, const void *tau_in, void *tau0, void *tau1,
+                 SweepStats *ring, int ring_len, int64_t first, int count,
+                 hipStream_t s);
+
 // Host threads (each with a stream) that build or prepare several graphs
 // at once: 2, or ND_PREP_THREADS.
 int prep_threads();

@@ -101,3 +101,55 @@ def test_noalloc_without_room_for_support_counts():
     got = out.cpu().numpy()
     assert np.array_equal(got[np.arange(small.n) * step], want[-1])
     assert int((got != 0).sum()) == int((want[-1] != 0).sum())
+
+
+# Around the one-workgroup path's limits: 8192 swept r-cliques, 20480
+# incidences and lists of 1024; list lengths of every bin inside it; more sweeps than one launch
+# runs (the chain), stopped early or not.
+def _ring_graph(n, m, seed):
+    """n vertices, every one on a cycle, and m further random pairs."""
+    rng = np.random.default_rng(seed)
+    i = np.arange(n)
+    src = np.concatenate([i, rng.integers(0, n, m)])
+    dst = np.concatenate([(i + 1) % n, rng.integers(0, n, m)])
+    return RawGraph(n, src.astype(np.int32), dst.astype(np.int32), "ring")
+
+
+TINY = {"ring8191": lambda: _ring_graph(8191, 1900, 1),
+        "ring8192": lambda: _ring_graph(8192, 1900, 2),
+        "ring8193": lambda: _ring_graph(8193, 1900, 3),
+        "entries_below": lambda: _ring_graph(3000, 7200, 4),
+        "entries_above": lambda: _ring_graph(3000, 7300, 5),
+        "wheels_small": lambda: _wheels((4, 5, 16, 17, 64, 65, 255, 256, 257, 600), 1, 6),
+        "hub1024": lambda: _wheels((4, 1024), 1, 8),
+        "hub1025": lambda: _wheels((4, 1025), 1, 9),
+        "chain": lambda: _chain(700, 7)}
+
+
+@pytest.mark.parametrize("kind", list(KINDS))
+@pytest.mark.parametrize("name", list(TINY))
+def test_small_graphs_plain_sweeps(name, kind):
+    import torch
+    import paper_1704_00386_amd as nd
+    raw = TINY[name]()
+    r, s = KINDS[kind]
+    seq = oracle.Graph.from_raw(raw).snd(r, s)
+    ctx = nd.Context(0)
+    g = nd.Graph.from_edges(ctx, raw.n, torch.from_numpy(raw.src),
+                            torch.from_numpy(raw.dst))
+    nsw = int((g.sdegree(kind).cpu().numpy() > 0).sum())
+    kappa, res = g.decompose(kind, "snd")
+    assert np.array_equal(kappa.cpu().numpy(), seq[-1])
+    assert res["sweeps"] == len(seq) - 1
+    assert res["updates"] == nsw * res["sweeps"]
+    kappa, _ = g.decompose(kind, "and")
+    assert np.array_equal(kappa.cpu().numpy(), seq[-1])
+    for t in (1, 2, 31, 32, 33, 64, 65):
+        if t >= len(seq) - 1:
+            break
+        tau, res = g.decompose(kind, "snd", max_iters=t, allow_not_converged=True)
+        assert res["sweeps"] == t and res["converged"] == 0
+        assert np.array_equal(tau.cpu().numpy(), seq[t])
+    out = torch.empty(max(len(seq[-1]), 1), dtype=torch.int32, device="cuda")
+    g.decompose(kind, "snd", out=out, noalloc=True)
+    assert np.array_equal(out.cpu().numpy()[:len(seq[-1])], seq[-1])
