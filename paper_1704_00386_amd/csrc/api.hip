@@ -816,6 +816,7 @@ nd_status nd_update(nd_graph *g, nd_kind kind, const int32_t *tau_in,
     a.inc_ids = ks.inc_ids.p;
     a.tau_in = ta.p;
     a.tau_out = tbuf.p;
+    a.tau_bytes = ks.tau_bytes;
     a.stats = st.p;
     a.prev = nullptr;
     a.cap_by_tau = 0;

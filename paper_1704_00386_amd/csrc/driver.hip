@@ -44,6 +44,8 @@ constexpr int64_t kSumsDiv = 256;  // see sums_after in sweep_loop
 // 1.6 ms a sweep side by side, 1.9 spread.
 constexpr unsigned long long kSpreadBelow = 1 << 15;
 constexpr int64_t kWatchGathers = (int64_t)1 << 26;  // see watch in sweep_loop
+// Sweeps enqueued one by one for narrowing's sake (see sweep_loop).
+constexpr int64_t kNarrowSweeps = 8;
 constexpr int kGridPerCu = 64;    // sweep workgroups per CU (they stride;
                                   // measured best of 8..64 and uncapped)
 
@@ -56,6 +58,27 @@ constexpr int kGridPerCu = 64;    // sweep workgroups per CU (they stride;
 int grid_per_cu_frontier(int64_t swept, int num_cu) {
   const int64_t waves_per_cu = swept / 4096 / std::max(num_cu, 1);
   return (int)std::min<int64_t>(96, std::max<int64_t>(16, waves_per_cu / 4));
+}
+
+// Whether any of tau[0..n) is above `most`, into st->wide.
+template <typename T>
+__global__ __launch_bounds__(256) void k_any_above(const T *__restrict__ tau,
+                                                   int64_t n, int32_t most,
+                                                   SweepStats *__restrict__ st) {
+  bool any = false;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x)
+    any |= (int32_t)tau[i] > most;
+  if (ballot(any) != 0 && lane_id() == 0) st->wide = 1;
+}
+
+// tau, every value of which fits, in a narrower type.
+template <typename T, typename U>
+__global__ __launch_bounds__(256) void k_narrow(const T *__restrict__ in,
+                                                U *__restrict__ out, int64_t n) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x)
+    out[i] = (U)in[i];
 }
 
 // Zero the counters of sweeps first .. first+count-1 (a kernel, not a
@@ -104,7 +127,7 @@ __global__ __launch_bounds__(256) void k_count_active(
 }
 
 // The host's counters of the chunk's sweeps (hst is pinned host memory, the
-// same ring as the device's): totals only, 32 bytes a sweep.
+// same ring as the device's): totals only.
 __global__ void k_post_stats(const SweepStats *__restrict__ ring,
                              HostStats *__restrict__ hst, int ring_len,
                              int64_t first, int count) {
@@ -116,6 +139,7 @@ __global__ void k_post_stats(const SweepStats *__restrict__ ring,
   h.evaluated = st.evaluated_total();
   h.notified = st.notified;
   h.active = st.active;
+  h.wide = st.wide;
   hst[(first + i) % ring_len] = h;
 }
 
@@ -139,6 +163,31 @@ struct LoopBufs {
   int32_t *snap = nullptr;   // on_iter: tau_t in r-clique-id order
   int32_t *stage = nullptr;  // kappa on the device when it goes to the host
 };
+
+// Whether a value of tau does not fit tb / 2 bytes, into st->wide.  Only lists
+// at least that long can hold one: the first bins.
+void any_above(const KindState &ks, const void *tau, int tb, SweepStats *st,
+               hipStream_t s) {
+  const int64_t n = tb == 2 ? ks.bin_hi[kBinG64] : ks.bin_hi[kBinBlock];
+  if (n == 0) return;
+  const unsigned grid = (unsigned)std::min<int64_t>(grid_for(n, 256), 2048);
+  if (tb == 2)
+    k_any_above<<<grid, 256, 0, s>>>((const uint16_t *)tau, n, 255, st);
+  else
+    k_any_above<<<grid, 256, 0, s>>>((const int32_t *)tau, n, 32767, st);
+  ND_LAUNCHED();
+}
+
+// tau in tb / 2 bytes a value, in tau's own memory and in tmp.
+void narrow(void *tau, void *tmp, int64_t nr, int tb, hipStream_t s) {
+  const unsigned grid = (unsigned)std::min<int64_t>(grid_for(nr, 256), 8192);
+  if (tb == 2)
+    k_narrow<<<grid, 256, 0, s>>>((const uint16_t *)tau, (uint8_t *)tmp, nr);
+  else
+    k_narrow<<<grid, 256, 0, s>>>((const int32_t *)tau, (uint16_t *)tmp, nr);
+  ND_LAUNCHED();
+  ND_HIP(hipMemcpyAsync(tau, tmp, nr * (tb / 2), hipMemcpyDeviceToDevice, s));
+}
 
 // Options as the loop runs them.
 nd_opts effective_opts(const nd_opts *opts_in, bool fixed_set) {
@@ -259,6 +308,20 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
   // AND's sweeps pass values on within a sweep and so are fewer.
   const bool tiny = !and_mode && !flags && !step_by_step && tiny_fits(ks);
   int chunk = tiny ? kTinySweeps : step_by_step || watch ? 1 : 2;
+  // tau's width so far, and whether it may shrink: the largest values fall
+  // fast, and a full sweep of a large graph is bound by the cache lines that
+  // its gathers fetch (k-truss of 16.5M edges, lists up to 670, all below 256
+  // after three sweeps: 2.42 ms a full sweep in 16 bits, 2.15 in 8; the whole
+  // decomposition with its build 70.0 -> 67.4 ms).  From 2^26 gathers a sweep
+  // on, where a check (5 us) and two copies do not show; the first sweeps run
+  // one by one for it, no more than kNarrowSweeps of them where values stay
+  // wide.  Only full sweeps that notify nobody are narrowed after: slack words
+  // have tau's type from the first notifying sweep on.  The other array takes
+  // the narrowed values (SND) or the slack words' memory (AND).
+  int tb = ks.tau_bytes;
+  bool narrowing = tb > 1 && !indicator && !fixed_set && ks.P * ks.k >= kWatchGathers &&
+                   (!and_mode || b.slack != nullptr);
+  if (narrowing) chunk = 1;
   int64_t t = 0;  // sweeps enqueued
   int64_t sweeps = 0, updates = 0;
   bool converged = false, stop_ratio = false, stop_cb = false;
@@ -292,6 +355,7 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
       a.inc_ids = ks.inc_ids.p;
       a.tau_in = b.tau[t & 1];
       a.tau_out = b.tau[(t + 1) & 1];
+      a.tau_bytes = tb;
       a.stats = b.ring + (t % ring_len);
       a.prev = t > 0 ? b.ring + ((t - 1) % ring_len) : nullptr;
       a.cap_by_tau = 1;
@@ -329,6 +393,7 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
       }
       if (step_by_step) ND_HIP(hipEventRecord(ev[3], s));
     }
+    if (narrowing) any_above(ks, b.tau[t & 1], tb, &b.ring[(t - 1) % ring_len], s);
     // read back this chunk's counters
     k_post_stats<<<1, kWave, 0, s>>>(b.ring, hst, ring_len, t0, nb);
     ND_LAUNCHED();
@@ -344,7 +409,7 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
       if (opts.on_iter &&
           (opts.snapshot_every <= 1 || (j + 1) % opts.snapshot_every == 0 ||
            last)) {
-        to_original(ks, b.tau[(j + 1) & 1], ks.tau_bytes, b.snap, s);
+        to_original(ks, b.tau[(j + 1) & 1], tb, b.snap, s);
         ND_HIP(hipStreamSynchronize(s));
         nd_iter_info info{};
         info.iter = (int32_t)(j + 1);
@@ -371,12 +436,22 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
       const HostStats &last = hst[(t - 1) % ring_len];
       plain = !last.notified && last.changed > notify_below;
     }
+    if (flags && !plain) narrowing = false;
+    if (narrowing && !hst[(t - 1) % ring_len].wide) {
+      void *tmp = and_mode ? b.slack : b.tau[(t + 1) & 1];
+      narrow(b.tau[t & 1], tmp, nr, tb, s);
+      tb /= 2;
+      narrowing = tb > 1;
+    }
     // once few r-cliques change, notifications keep the summaries themselves
     if (sums_after != 0 && hst[(t - 1) % ring_len].notified &&
         hst[(t - 1) % ring_len].changed < sums_after)
       sums_after = 0;
     if (!tiny)
-      chunk = std::min(chunk * 2, step_by_step || (watch && plain) ? 1 : kMaxChunk);
+      chunk = std::min(chunk * 2, step_by_step || (watch && plain) ||
+                                          (narrowing && t < kNarrowSweeps)
+                                      ? 1
+                                      : kMaxChunk);
   }
   ND_HIP(hipEventRecord(ev[1], s));
   r.ms_iterate = elapsed_ms(ev[0], ev[1]);
@@ -386,9 +461,9 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
   const void *result = b.tau[sweeps & 1];
   Phase out_phase("nd.output");
   if (on_device) {
-    to_original(ks, result, ks.tau_bytes, kappa, s);
+    to_original(ks, result, tb, kappa, s);
   } else {
-    to_original(ks, result, ks.tau_bytes, b.stage, s);
+    to_original(ks, result, tb, b.stage, s);
     ND_HIP(hipMemcpyAsync(kappa, b.stage, sizeof(int32_t) * nr,
                           hipMemcpyDeviceToHost, s));
   }

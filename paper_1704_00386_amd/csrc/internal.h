@@ -329,7 +329,9 @@ struct SweepStats {
   unsigned long long active;    // r-cliques flagged for the next sweep
                                 // (counted after the sweep when asked for)
   unsigned long long total;     // batches: changed_total(), summed once
-  unsigned long long pad[13];
+  unsigned long long wide;      // nonzero: a value does not fit the next
+                                // narrower type (asked for after a sweep)
+  unsigned long long pad[12];
   __host__ __device__ unsigned long long changed_total() const {
     unsigned long long s = 0;
     for (int i = 0; i < kStatParts; i++) s += part[i].changed;
@@ -347,6 +349,7 @@ struct SweepArgs {
   const int32_t *inc_ids;
   const void *tau_in;      // SND: tau_t; AND: the in-place array
   void *tau_out;           // SND: tau_{t+1}; AND: same as tau_in
+  int tau_bytes;           // 1, 2 or 4, of both
   SweepStats *stats;       // this sweep's counters
   const SweepStats *prev;  // previous sweep's counters (skip when converged)
   int cap_by_tau;          // 1: clamp at tau_in(R) (iterates); 0: at d_s
@@ -404,11 +407,11 @@ void *noalloc_workspace(int device);
 // Entries of the pinned host ring that receives the sweep counters' totals.
 constexpr int kHostStatsRing = 1024;
 struct HostStats {
-  unsigned long long changed, evaluated, notified, active;
+  unsigned long long changed, evaluated, notified, active, wide;
 };
 
 // Launch one sweep over every bin of ks (internal numbering, tau of
-// ks.tau_bytes per value).  `and_mode` selects in-place reads.
+// a.tau_bytes per value).  `and_mode` selects in-place reads.
 void launch_sweep(const KindState &ks, const SweepArgs &a, bool and_mode,
                   hipStream_t s);
 // After the sweep of a (same arguments): the group summaries of the flags it

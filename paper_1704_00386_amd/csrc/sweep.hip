@@ -171,9 +171,9 @@ void launch_group_sums(const KindState &ks, const SweepArgs &a, hipStream_t s) {
   const int64_t ng = (swept + (1 << dev::kGroupShift) - 1) >> dev::kGroupShift;
   const unsigned grid =
       (unsigned)std::min<int64_t>(grid_for(ng, 256), kGroupSumsBlocks);
-  if (ks.tau_bytes == 1)
+  if (a.tau_bytes == 1)
     k_group_sums<uint8_t><<<grid, 256, 0, s>>>(a, swept);
-  else if (ks.tau_bytes == 2)
+  else if (a.tau_bytes == 2)
     k_group_sums<uint16_t><<<grid, 256, 0, s>>>(a, swept);
   else
     k_group_sums<int32_t><<<grid, 256, 0, s>>>(a, swept);
@@ -182,9 +182,9 @@ void launch_group_sums(const KindState &ks, const SweepArgs &a, hipStream_t s) {
 
 void launch_sweep(const KindState &ks, const SweepArgs &a, bool and_mode,
                   hipStream_t s) {
-  if (ks.tau_bytes == 1)
+  if (a.tau_bytes == 1)
     launch_typed<uint8_t>(ks, a, and_mode, s);
-  else if (ks.tau_bytes == 2)
+  else if (a.tau_bytes == 2)
     launch_typed<uint16_t>(ks, a, and_mode, s);
   else
     launch_typed<int32_t>(ks, a, and_mode, s);

@@ -366,7 +366,9 @@ struct SmallBins {
   unsigned first[kRanges + 1];
 };
 
-template <int K, typename T, bool AND, bool FR>
+// LONG: with the ranges of lists above 256.  8-bit values have them only where
+// wider ones were narrowed (see k_narrow in driver.hip).
+template <int K, typename T, bool AND, bool FR, bool LONG>
 __global__ __launch_bounds__(256, 6) void k_sweep_small(SweepArgs a, SmallBins sb) {
   __shared__ union {
     FlatLds<T> flat;
@@ -383,7 +385,7 @@ __global__ __launch_bounds__(256, 6) void k_sweep_small(SweepArgs a, SmallBins s
   while (i + 1 < kRanges && blockIdx.x >= sb.first[i + 1]) i++;
   const int64_t block = blockIdx.x - sb.first[i];
   const int64_t nblocks = sb.first[i + 1] - sb.first[i];
-  if constexpr (sizeof(T) > 1) {  // 8-bit tau: every d_s is below 256
+  if constexpr (LONG) {
     if (i == 0) {
       sweep_hubs<K, T, AND, FR>(a, sb.lo[0], sb.hi[0], block, nblocks, act,
                                 act_next, sum_next, sp, lds.hub);
@@ -442,7 +444,10 @@ void launch_bins(const KindState &ks, const SweepArgs &a, hipStream_t s) {
   }
   sb.first[kRanges] = (unsigned)total;
   if (total > 0) {
-    k_sweep_small<K, T, AND, FR><<<(unsigned)total, 256, 0, s>>>(a, sb);
+    if (sizeof(T) > 1 || sb.hi[1] > 0)
+      k_sweep_small<K, T, AND, FR, true><<<(unsigned)total, 256, 0, s>>>(a, sb);
+    else
+      k_sweep_small<K, T, AND, FR, false><<<(unsigned)total, 256, 0, s>>>(a, sb);
     ND_LAUNCHED();
   }
 }

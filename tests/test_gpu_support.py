@@ -153,3 +153,54 @@ def test_small_graphs_plain_sweeps(name, kind):
     out = torch.empty(max(len(seq[-1]), 1), dtype=torch.int32, device="cuda")
     g.decompose(kind, "snd", out=out, noalloc=True)
     assert np.array_equal(out.cpu().numpy()[:len(seq[-1])], seq[-1])
+
+
+# Values narrowed from 32 to 16 to 8 bits between full sweeps: vertices of
+# degree about 257 (2^26 gathers a sweep) and hubs of every long list's range,
+# whose values fall below 256 within a few sweeps.  Against H-indices by sorting.
+def test_values_narrow_between_sweeps():
+    import torch
+    import paper_1704_00386_amd as nd
+    n, m = 1 << 18, (1 << 25) + (1 << 18)
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    src = torch.randint(0, n, (m,), generator=gen, device="cuda", dtype=torch.int32)
+    dst = torch.randint(0, n, (m,), generator=gen, device="cuda", dtype=torch.int32)
+    for h, deg in enumerate((300, 900, 1100, 3000, 40000)):
+        perm = torch.randperm(n - 5, generator=gen, device="cuda")[:deg] + 5
+        src = torch.cat([src, torch.full((deg,), h, device="cuda", dtype=torch.int32)])
+        dst = torch.cat([dst, perm.to(torch.int32)])
+    ctx = nd.Context(0)
+    g = nd.Graph.from_edges(ctx, n, src, dst)
+    key = torch.unique(torch.cat([src.long() * n + dst, dst.long() * n + src]))
+    key = key[key // n != key % n]
+    row, col = key // n, key % n
+    off = torch.searchsorted(row, torch.arange(n + 1, device="cuda"))
+    rank = torch.arange(row.numel(), device="cuda") - off[row]
+    tau = off.diff()
+    assert row.numel() >= 1 << 26 and int(tau.max()) >= 32768
+    want = []
+    for _ in range(6):
+        order = torch.sort(row * (1 << 20) + ((1 << 20) - 1 - tau[col])).values
+        hits = (((1 << 20) - 1 - (order & ((1 << 20) - 1))) > rank).long()
+        total = torch.cat([hits.new_zeros(1), hits.cumsum(0)])
+        tau = total[off[1:]] - total[off[:-1]]
+        want.append(tau.to(torch.int32))
+    assert int(want[0].max()) >= 256 > int(want[-1].max())
+    kappa = {}
+    for mode in ("snd", "and"):
+        for frontier in (False, True):
+            if mode == "snd":
+                its = []
+                g.decompose("core", mode, use_frontier=frontier, max_iters=6,
+                            keep_iterates=its, allow_not_converged=True)
+                assert [torch.equal(t.cuda().to(torch.int32), w)
+                        for (_, t), w in zip(its, want)] == [True] * 6
+                for it in (1, 3, 6):
+                    t, _ = g.decompose("core", mode, use_frontier=frontier,
+                                       max_iters=it, allow_not_converged=True)
+                    assert torch.equal(t, want[it - 1])
+            kappa[mode, frontier], res = g.decompose("core", mode, use_frontier=frontier)
+            assert res["tau_bytes"] == 4
+    first = kappa["snd", False]
+    assert all(torch.equal(first, k) for k in kappa.values())
+    assert torch.equal(g.update("core", first), first)
