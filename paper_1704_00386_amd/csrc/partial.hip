@@ -129,7 +129,7 @@ __device__ __forceinline__ int32_t ego_h(const EgoArgs &a, const EgoLds &L, int 
     rho[m] = j < d ? ego_rho<K>(a, L, np, b + j) : -1;
   }
   const int cnt = count_ge<kWave, M>(rho, c);
-  return cnt >= c ? c : hindex_search<kWave, M>(rho, c);
+  return cnt >= c ? c : hindex_search<kWave, M>(rho, c, cnt);
 }
 
 __device__ __forceinline__ int wave_sum(int x) {
@@ -292,19 +292,8 @@ __global__ __launch_bounds__(kEgoThreads) void k_ego(EgoArgs a) {
               n += ego_rho<K>(a, L, np, b + j) >= x;
             return wave_sum(n);
           };
-          if (count(c) >= c) {
-            h = c;
-          } else {
-            int32_t l = 0, r = c - 1;
-            while (l < r) {
-              const int32_t mid = (l + r + 1) >> 1;
-              if (count(mid) >= mid)
-                l = mid;
-              else
-                r = mid - 1;
-            }
-            h = l;
-          }
+          const int cnt = count(c);
+          h = cnt >= c ? c : hindex_between(count, c, cnt);
         }
         if (h != c) {  // uniform over the wave
           if (lane == 0) {

@@ -122,7 +122,7 @@ __device__ __forceinline__ void sweep_flat(const SweepArgs &a, int64_t lo,
         rho[m] = j < d ? (int32_t)lds->rho[b + j] : -1;
       }
       const int cnt = count_ge<G, M>(rho, c);
-      const int32_t h = cnt >= c ? c : hindex_search<G, M>(rho, c);
+      const int32_t h = cnt >= c ? c : hindex_search<G, M>(rho, c, cnt);
       const bool lead = sl == 0;
       const bool ch = active && h != told;
       if (active && lead) store_tau<T, AND>(tout + r0 + i, h, ch);
@@ -209,7 +209,7 @@ __device__ __forceinline__ void sweep_flat_fr(const SweepArgs &a, int64_t lo,
         }
       }
       const int cnt = count_ge<G, M>(rho, c);
-      const int32_t h = cnt >= c ? c : hindex_search<G, M>(rho, c);
+      const int32_t h = cnt >= c ? c : hindex_search<G, M>(rho, c, cnt);
       const bool lead = sl == 0;
       const bool ch = active && h != told;
       const int64_t R = r0 + i;

@@ -75,7 +75,7 @@ __device__ __forceinline__ int tiny_bin(TinyLds<T> &L, int cur, int lo, int hi) 
       rho[m] = j < d ? (int32_t)L.rho[b + j] : -1;
     }
     const int cnt = count_ge<G, 4>(rho, c);
-    const int32_t h = cnt >= c ? c : hindex_search<G, 4>(rho, c);
+    const int32_t h = cnt >= c ? c : hindex_search<G, 4>(rho, c, cnt);
     const bool lead = i < hi && sl == 0;
     if (lead) L.tau[cur ^ 1][i] = (T)h;
     changed += __popcll(ballot(lead && h != c));
@@ -97,18 +97,8 @@ __device__ __forceinline__ int tiny_long(TinyLds<T> &L, int cur, int hi) {
         n += __popcll(ballot(j0 + lane < d && (int32_t)L.rho[b + j0 + lane] >= x));
       return n;
     };
-    int32_t h = c;
-    if (count(c) < c) {
-      int32_t lo = 0, up = c - 1;
-      while (lo < up) {
-        const int32_t mid = (lo + up + 1) >> 1;
-        if (count(mid) >= mid)
-          lo = mid;
-        else
-          up = mid - 1;
-      }
-      h = lo;
-    }
+    const int cnt = count(c);
+    const int32_t h = cnt >= c ? c : hindex_between(count, c, cnt);
     if (lane == 0) L.tau[cur ^ 1][i] = (T)h;
     changed += h != c;
   }
