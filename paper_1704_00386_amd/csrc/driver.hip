@@ -36,6 +36,7 @@ static_assert(kTinySweeps <= kWave && kTinySweeps < kStaticRing &&
                   kStatsRing <= kHostStatsRing,
               "a chunk and its predecessor must fit every counter ring");
 constexpr int64_t kSumsDiv = 256;  // see sums_after in sweep_loop
+constexpr int64_t kSumsSwept = 1 << 20;
 // Sparse sweeps spread their r-cliques over the waves after a sweep that
 // changed fewer than this: a few per wave then, and clusters of them on one
 // wave are what such a sweep waits for (86,000-edge k-truss 746 -> 636 us,
@@ -287,7 +288,7 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
     // 1/64, 1/256 against in-sweep stores on the block model: SND 506 /
     // 501 / 497 ms against 505, AND 451 / 446 / 441 against 451; Chung-Lu
     // k-truss 0.5 ms faster, k-core unchanged).
-    if (!indicator)
+    if (!indicator && ks.bin_lo[kBinZero] >= kSumsSwept)
       sums_after = std::max<unsigned long long>(
           1, (unsigned long long)(ks.bin_lo[kBinZero] / kSumsDiv));
   }
