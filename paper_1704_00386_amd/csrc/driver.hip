@@ -287,7 +287,10 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
     // r-cliques leave the group summaries to k_group_sums (measured 1/16,
     // 1/64, 1/256 against in-sweep stores on the block model: SND 506 /
     // 501 / 497 ms against 505, AND 451 / 446 / 441 against 451; Chung-Lu
-    // k-truss 0.5 ms faster, k-core unchanged).
+    // k-truss 0.5 ms faster, k-core unchanged).  Below 2^20 swept r-cliques
+    // that kernel's launch and loads cost more than the stores (k-truss of
+    // 86498 edges 596 us with it, 505 without; (2,4) of 548297 edges 32.0 and
+    // 31.8 ms; the block model's 4.1e8 triangles 622 and 645 ms).
     if (!indicator && ks.bin_lo[kBinZero] >= kSumsSwept)
       sums_after = std::max<unsigned long long>(
           1, (unsigned long long)(ks.bin_lo[kBinZero] / kSumsDiv));
