@@ -147,7 +147,8 @@ Batch::Batch(nd_ctx *ctx, nd_kind kind, nd_mode mode, bool tau16,
              bool frontier, hipStream_t caller)
     : ctx_(ctx), kind_(kind), mode_(mode), tau16_(tau16), frontier_(frontier) {
   cfg_ = default_config(ctx);
-  notify_div_ = frontier_switch(mode == ND_AND);
+  // (an epoch sweeps every member: the gathers of many graphs)
+  notify_div_ = frontier_switch(INT64_MAX);
   if (const char *v = getenv("ND_BATCH_NO_GRAPH")) use_graph = v[0] != '1';
   ND_HIP(hipStreamCreateWithFlags(&s_, hipStreamNonBlocking));
   hipEvent_t ev;

@@ -19,12 +19,10 @@
 
 namespace nd {
 
-int frontier_switch(bool and_mode) {
+int frontier_switch(int64_t gathers) {
   if (const char *v = getenv("ND_FRONTIER_SWITCH")) return atoi(v);
-  (void)and_mode;
-  return 8;
+  return gathers <= (int64_t)1 << 22 ? 512 : 8;
 }
-
 
 namespace {
 
@@ -267,7 +265,7 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
   const int64_t ng = (nr + (1 << dev::kGroupShift) - 1) >> dev::kGroupShift;
   // frontier flags (Section 4.3): act[t & 1] selects the r-cliques of sweep
   // t; every r-clique takes part in the first sweep.  Notifications start
-  // once a sweep changes at most 1/frontier_switch() of the swept r-cliques;
+  // once a sweep changes at most 1/frontier_switch(..) of the swept r-cliques;
   // with the indicator they run from the first sweep, so that every sweep's
   // active count is known.
   unsigned long long notify_below = 0, sums_after = 0;
@@ -279,7 +277,7 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
         fill_u8(b.act[i], 0, nr, s);  // no stamps yet
       fill_u8(b.act_sum[i], 0, ng, s);
     }
-    const int div = frontier_switch(and_mode);
+    const int div = frontier_switch(ks.P * ks.k);
     notify_below = (indicator || div <= 0)
                        ? ~0ull
                        : (unsigned long long)(ks.bin_lo[kBinZero] / div);

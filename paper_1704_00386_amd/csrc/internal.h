@@ -440,10 +440,15 @@ inline int lost_shift(const KindState &ks) {
   return most <= 255 ? 0 : most <= 65535 ? 1 : 2;
 }
 
-// Frontier switch: notifications start once a sweep changes at most
-// 1/d of the swept r-cliques; d = 8 for SND and AND (measured on the three
-// benchmark workloads), ND_FRONTIER_SWITCH overrides it (0: from the first
-// sweep on).
-int frontier_switch(bool and_mode);
+// Frontier switch: notifications start once a sweep changes at most 1/d of the
+// swept r-cliques.  d = 8 where a full sweep is bound by its gathers: 16.5M
+// edges 42.6 ms at 8, 41.9 at 12, 44.6 at 40; 4e8 triangles 456 ms at 8, 484 at
+// 24; 18.7M incidences of a k-core the same from 8 to 64, 3.4 against 2.6 ms at
+// 8192.  Up to 2^22 gathers a sweep a full one is a launch and a chain of loads
+// just as a sparse one, and the sparse one's chain is longer: d = 512 (k-truss
+// of 1.2M gathers 0.46 ms at 8, 0.36 at 256 and 0.37 at 1024; (1,3) of 0.7M
+// 1.11 / 0.50 / 0.38; k-core of 1.9M 0.77 / 0.69 / 0.66).  ND_FRONTIER_SWITCH
+// overrides both (0: from the first sweep on).
+int frontier_switch(int64_t gathers);
 
 }  // namespace nd
