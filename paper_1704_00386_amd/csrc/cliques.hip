@@ -1523,7 +1523,7 @@ void build_incidence_truss(nd_graph *g, KindState &ks, hipStream_t s) {
     ND_LAUNCHED();
   }
   ks.nr = ne;
-  build_layout(g, ks, cnt.p, s);
+  build_layout(g, ks, cnt.p, s, out_eid.p);
   cnt.free();
   ks.inc_ids.reset(al, 2 * ks.P);
   DArr<unsigned long long> cursor(al, ne);

@@ -295,9 +295,10 @@ void build_incidence_truss(nd_graph *g, KindState &ks, hipStream_t s);
 void build_incidence_n34(nd_graph *g, KindState &ks, hipStream_t s);
 void build_incidence_n13(nd_graph *g, KindState &ks, hipStream_t s);
 void build_incidence_n24(nd_graph *g, KindState &ks, hipStream_t s);
-// From S-degrees in r-clique-id order: perm, inv, ds, inc_off, bins.
+// From S-degrees in r-clique-id order: perm, inv, ds, inc_off, bins.  `order`:
+// the r-cliques as they follow each other within a bin (NULL: by id).
 void build_layout(nd_graph *g, KindState &ks, const int32_t *cnt,
-                  hipStream_t s);
+                  hipStream_t s, const int32_t *order = nullptr);
 // Re-index between internal and r-clique-id order; the internal side holds
 // `bytes` (1, 2 or 4) per value.
 void to_internal(const KindState &ks, const int32_t *in, void *out, int bytes,
