@@ -932,14 +932,12 @@ void run_n34_tri(TriIsectArgs a, bool fill, const int32_t *items,
 
 constexpr int kN34VMax = 256;  // largest degree of the per-vertex builder
 
-// LDS of one wave of the per-vertex builder.  Each pass holds only its own
-// arrays (the other's shrink to one element): the workgroup is one wave, so
-// LDS per wave sets how many waves a CU keeps in flight, and both passes
-// wait on dependent loads.  Triangle ids fit 32 bits (at most 2^31 - 1
+// LDS of one workgroup of the per-vertex builder.  Each pass holds only its own
+// arrays: LDS sets how many waves a CU keeps in flight, and every pass waits
+// on dependent loads.  Triangle ids fit 32 bits (at most 2^31 - 1
 // r-cliques).
-template <int D, bool FILL>
+template <int D, int NC>  // NC: the fill pass's waves (0: another pass)
 struct N34VLds {
-  static constexpr int kC = FILL ? kWave : 1;  // fill-pass chunk arrays
   int32_t nb[D];
   int32_t len[D];      // |N(nb[i])|
   int64_t ro[D];       // row_off[nb[i]]
@@ -947,16 +945,19 @@ struct N34VLds {
   int32_t st[D];       // where row i's walk of N(nb[i]) starts (row build)
   uint32_t A[D][D / 32];
   int32_t tb[D];       // toff of edge (p, nb[i]), i >= nl
-  // fill pass: one chunk of up to 64 triangles with their lists (base,
-  // internal id, length), and for each the range of triangles of edge
+  // fill pass, per wave: one chunk of up to 64 triangles with their lists
+  // (base, internal id, length), and for each the range of triangles of edge
   // (nb[i], nb[j]) in which its 4-cliques' remote triangles lie (found once
   // per triangle, not once per 4-clique)
-  int16_t ci[kC], cj[kC];
-  int64_t cb[kC];
-  int32_t cv[kC], cl[kC];
-  int32_t coff[FILL ? kWave + 1 : 1];
-  int32_t cs0[kC];
-  int32_t cn[kC];
+  struct Chunk {
+    int16_t ci[kWave], cj[kWave];
+    int64_t cb[kWave];
+    int32_t cv[kWave], cl[kWave];
+    int32_t coff[kWave + 1];
+    int32_t cs0[kWave];
+    int32_t cn[kWave];
+  };
+  Chunk ch[NC];
 };
 
 // Exclusive prefix sums of v[0..n) in place, v[n] = total (one wave).
@@ -1059,16 +1060,34 @@ struct N34VArgs {
 // triangles; the 4-cliques' entries.
 constexpr int kVRows = 0, kVTris = 1, kVCount = 2, kVFill = 3;
 
-// One wave per vertex p of degree <= D, one pass (MODE) over the triangles
+// Waves per vertex of the fill pass.  It is bound by the memory requests of its
+// scattered entries (block model, degrees up to 128: 8.7e8 4-cliques, 4.0e9
+// reads and writes past the L2 in 110 ms).  The lists of p's triangles are
+// written piece by piece while p is worked on, so the fewer vertices are in
+// flight for the same number of waves, the more pieces of a cache line meet in
+// the L2: one wave a vertex 119 ms, four 97.6, eight 98.3 (the whole
+// decomposition 626 and 621).  Small vertices have too few 4-cliques to
+// share (mean degree 32, 6.4M triangles: 2.50 ms with one wave, 2.59 with two).
+template <int D>
+constexpr int kFillWaves = D == 64 ? 1 : 8;
+
+// NW waves per vertex p of degree <= D, one pass (MODE) over the triangles
 // and 4-cliques whose lowest vertex is p: the bit rows (kept in a.rows) and
 // the triangle count of each of p's upper edges; the triangles of those
 // edges; the triangles' S-degrees and local counts; the 4-cliques' entries.
-template <int D, int MODE>
-__global__ __launch_bounds__(kWave) void k_n34_vertex(N34VArgs a) {
+template <int D, int MODE, int NW>
+__global__ __launch_bounds__(NW * kWave) void k_n34_vertex(N34VArgs a) {
   constexpr int W = D / 32;
+  constexpr int NT = NW * kWave;
   constexpr bool FILL = MODE == kVFill;
-  __shared__ N34VLds<D, FILL> L;
-  const int lane = lane_id();
+  __shared__ N34VLds<D, FILL ? NW : 0> L;
+  const int t = threadIdx.x, lane = lane_id();
+  const auto sync = []() {
+    if constexpr (NW == 1)
+      wave_lds_sync();
+    else
+      __syncthreads();
+  };
   const TriIsectArgs &T = a.t;
   for (int64_t it = blockIdx.x; it < a.nitems; it += gridDim.x) {
     const int32_t p = a.items[it];
@@ -1076,22 +1095,22 @@ __global__ __launch_bounds__(kWave) void k_n34_vertex(N34VArgs a) {
     const int d = (int)(a.row_off[p + 1] - base);
     const int nl = a.nlow[p];
     const int64_t e_lo = a.eoff[p];
-    wave_lds_sync();  // the previous vertex's reads are done
+    sync();  // the previous vertex's reads are done
     const bool reuse = MODE == kVTris || (MODE == kVCount && a.rows_ready) ||
                        (FILL && a.rows != nullptr);
     if (reuse) {
-      for (int x = lane; x < d * W; x += kWave)
+      for (int x = t; x < d * W; x += NT)
         L.A[x / W][x % W] = a.rows[base * kN34RowWords + x];
     } else {
-      for (int x = lane; x < d * W; x += kWave) L.A[x / W][x % W] = 0;
+      for (int x = t; x < d * W; x += NT) L.A[x / W][x % W] = 0;
     }
-    for (int i = lane; i < d; i += kWave) {
+    for (int i = t; i < d; i += NT) {
       const int32_t v = a.col[base + i];
       L.nb[i] = v;
       L.ro[i] = a.row_off[v];
       L.len[i] = (int32_t)(a.row_off[v + 1] - L.ro[i]);
     }
-    wave_lds_sync();
+    sync();
     if (!reuse) {
       // bit rows, which are symmetric: each pair i < q is looked at once,
       // from row i, and sets both bits.  A short row walks the part of
@@ -1099,7 +1118,7 @@ __global__ __launch_bounds__(kWave) void k_n34_vertex(N34VArgs a) {
       // entry among nb above i; a long one (a hub's) looks each nb[q], q > i,
       // up in N(nb[i]) instead.
       const int32_t top = L.nb[d - 1];
-      for (int i = lane; i < d; i += kWave) {
+      for (int i = t; i < d; i += NT) {
         int32_t w = d - 1 - i;
         if (L.len[i] <= 4 * d) {
           const int64_t e1 = L.ro[i] + L.len[i];
@@ -1110,12 +1129,13 @@ __global__ __launch_bounds__(kWave) void k_n34_vertex(N34VArgs a) {
         }
         L.pre[i] = w;
       }
-      wave_lds_sync();
-      wave_scan_lds(L.pre, d);
+      sync();
+      if (t < kWave) wave_scan_lds(L.pre, d);
+      sync();
       const int32_t work = L.pre[d];
-      for (int32_t t = lane; t < work; t += kWave) {
-        const int i = row_of(L.pre, d, t);
-        const int r = t - L.pre[i];
+      for (int32_t y = t; y < work; y += NT) {
+        const int i = row_of(L.pre, d, y);
+        const int r = y - L.pre[i];
         int q = d;
         if (L.len[i] <= 4 * d) {
           const int32_t z = T.col[L.ro[i] + L.st[i] + r];
@@ -1132,13 +1152,13 @@ __global__ __launch_bounds__(kWave) void k_n34_vertex(N34VArgs a) {
           atomicOr(&L.A[q][i >> 5], 1u << (i & 31));
         }
       }
-      wave_lds_sync();
+      sync();
       if (!FILL && a.rows != nullptr)  // keep them for the later passes
-        for (int x = lane; x < d * W; x += kWave)
+        for (int x = t; x < d * W; x += NT)
           a.rows[base * kN34RowWords + x] = L.A[x / W][x % W];
     }
     if constexpr (MODE == kVRows) {  // triangles (p, nb[i], w), w > nb[i]
-      for (int i = lane; i < d; i += kWave)
+      for (int i = t; i < d; i += NT)
         if (i >= nl) a.tcnt[e_lo + (i - nl)] = popc_and<W>(L.A[i], L.A[i], i + 1, d);
       continue;
     }
@@ -1146,7 +1166,7 @@ __global__ __launch_bounds__(kWave) void k_n34_vertex(N34VArgs a) {
     // edge (p, nb[i]), numbered from tb[i]; every row must count exactly
     // the edge's triangles, so that every id below lies in the edge's range
     bool bad = false;
-    for (int i = lane; i < d; i += kWave) {
+    for (int i = t; i < d; i += NT) {
       int c = 0;
       if (i >= nl) {
         const int64_t e = e_lo + (i - nl);
@@ -1156,17 +1176,20 @@ __global__ __launch_bounds__(kWave) void k_n34_vertex(N34VArgs a) {
       }
       L.pre[i] = c;
     }
-    if (ballot(bad)) {  // the triangle list disagrees: write nothing
-      if (lane == 0) *T.err = 1;
+    bool stop = ballot(bad) != 0;
+    if constexpr (NW > 1) stop = __syncthreads_or(stop);
+    if (stop) {  // the triangle list disagrees: write nothing
+      if (t == 0) *T.err = 1;
       continue;
     }
-    wave_lds_sync();
-    wave_scan_lds(L.pre, d);
+    sync();
+    if (t < kWave) wave_scan_lds(L.pre, d);
+    sync();
     const int32_t nt = L.pre[d];
     if constexpr (MODE == kVTris) {  // third vertices ascending, per edge
-      for (int32_t t = lane; t < nt; t += kWave) {
-        const int i = row_of(L.pre, d, t);
-        const int r = t - L.pre[i];
+      for (int32_t y = t; y < nt; y += NT) {
+        const int i = row_of(L.pre, d, y);
+        const int r = y - L.pre[i];
         const int j = nth_and<W>(L.A[i], L.A[i], i + 1, r);
         const int64_t pos = (int64_t)L.tb[i] + r;
         a.tw[pos] = L.nb[j];
@@ -1175,9 +1198,9 @@ __global__ __launch_bounds__(kWave) void k_n34_vertex(N34VArgs a) {
       continue;
     }
     if constexpr (MODE == kVCount) {
-      for (int32_t t = lane; t < nt; t += kWave) {
-        const int i = row_of(L.pre, d, t);
-        const int r = t - L.pre[i];
+      for (int32_t y = t; y < nt; y += NT) {
+        const int i = row_of(L.pre, d, y);
+        const int r = y - L.pre[i];
         const int j = nth_and<W>(L.A[i], L.A[i], i + 1, r);
         const int64_t id = L.tb[i] + r;
         T.count[id] = popc_and<W>(L.A[i], L.A[j], 0, d);
@@ -1187,15 +1210,16 @@ __global__ __launch_bounds__(kWave) void k_n34_vertex(N34VArgs a) {
     }
     if constexpr (FILL) {
     // fill: 64 triangles (i, j) at a time, then their 4-cliques (k > j)
-    for (int32_t t0 = 0; t0 < nt; t0 += kWave) {
-      const int32_t t = t0 + lane;
+    auto &C = L.ch[t / kWave];
+    for (int32_t t0 = t - lane; t0 < nt; t0 += NT) {
+      const int32_t y = t0 + lane;
       int i = 0, j = 0, kc = 0;
       int64_t s0 = 0;
       int32_t sn = 0;
       TriRec rt{0, 0, 0};
-      if (t < nt) {
-        i = row_of(L.pre, d, t);
-        const int r = t - L.pre[i];
+      if (y < nt) {
+        i = row_of(L.pre, d, y);
+        const int r = y - L.pre[i];
         j = nth_and<W>(L.A[i], L.A[i], i + 1, r);
         rt = T.rec[L.tb[i] + r];
         kc = popc_and<W>(L.A[i], L.A[j], j + 1, d);
@@ -1215,28 +1239,28 @@ __global__ __launch_bounds__(kWave) void k_n34_vertex(N34VArgs a) {
       int x = kc;
 #pragma unroll
       for (int off = 1; off < kWave; off <<= 1) {
-        const int y = __shfl_up(x, off, kWave);
-        if (lane >= off) x += y;
+        const int z = __shfl_up(x, off, kWave);
+        if (lane >= off) x += z;
       }
       const int nq = __shfl(x, kWave - 1, kWave);
-      L.ci[lane] = (int16_t)i;
-      L.cj[lane] = (int16_t)j;
-      L.cb[lane] = rt.base;
-      L.cv[lane] = rt.inv;
-      L.cl[lane] = rt.len;
-      L.cs0[lane] = (int32_t)s0;
-      L.cn[lane] = sn;
-      L.coff[lane] = x - kc;
-      if (lane == 0) L.coff[kWave] = nq;
+      C.ci[lane] = (int16_t)i;
+      C.cj[lane] = (int16_t)j;
+      C.cb[lane] = rt.base;
+      C.cv[lane] = rt.inv;
+      C.cl[lane] = rt.len;
+      C.cs0[lane] = (int32_t)s0;
+      C.cn[lane] = sn;
+      C.coff[lane] = x - kc;
+      if (lane == 0) C.coff[kWave] = nq;
       wave_lds_sync();
       for (int q = lane; q < nq; q += kWave) {
-        const int c = row_of(L.coff, kWave, q);
-        const int ii = L.ci[c], jj = L.cj[c];
-        const int k = nth_and<W>(L.A[ii], L.A[jj], jj + 1, q - L.coff[c]);
+        const int c = row_of(C.coff, kWave, q);
+        const int ii = C.ci[c], jj = C.cj[c];
+        const int k = nth_and<W>(L.A[ii], L.A[jj], jj + 1, q - C.coff[c]);
         const int32_t tik = (int32_t)(L.tb[ii] + popc_and<W>(L.A[ii], L.A[ii], ii + 1, k));
         const int32_t tjk = (int32_t)(L.tb[jj] + popc_and<W>(L.A[jj], L.A[jj], jj + 1, k));
         // the triangle without p: third vertex nb[k] on edge (nb[ii], nb[jj])
-        const int64_t s0 = L.cs0[c], s1 = s0 + L.cn[c];
+        const int64_t s0 = C.cs0[c], s1 = s0 + C.cn[c];
         const int64_t s = lower_bound<int32_t>(T.tri_w, s0, s1, L.nb[k]);
         int32_t top = -1;
         if (s < s1 && T.tri_w[s] == L.nb[k]) top = (int32_t)s;
@@ -1245,9 +1269,9 @@ __global__ __launch_bounds__(kWave) void k_n34_vertex(N34VArgs a) {
           continue;
         }
         TriRec rij;
-        rij.base = L.cb[c];
-        rij.inv = L.cv[c];
-        rij.len = L.cl[c];
+        rij.base = C.cb[c];
+        rij.inv = C.cv[c];
+        rij.len = C.cl[c];
         const TriRec rik = T.rec[tik], rjk = T.rec[tjk], rtop = T.rec[top];
         n34_put(T, rij, popc_and<W>(L.A[ii], L.A[jj], nl, k), rik.inv, rjk.inv, rtop.inv);
         n34_put(T, rik, popc_and<W>(L.A[ii], L.A[k], nl, jj), rij.inv, rjk.inv, rtop.inv);
@@ -1348,10 +1372,10 @@ __global__ void k_n34_check_full(const int32_t *__restrict__ cur,
 template <int D>
 void launch_n34_vertex(const N34VArgs &a, int mode, unsigned grid, hipStream_t s) {
   switch (mode) {
-    case kVRows: k_n34_vertex<D, kVRows><<<grid, kWave, 0, s>>>(a); break;
-    case kVTris: k_n34_vertex<D, kVTris><<<grid, kWave, 0, s>>>(a); break;
-    case kVCount: k_n34_vertex<D, kVCount><<<grid, kWave, 0, s>>>(a); break;
-    default: k_n34_vertex<D, kVFill><<<grid, kWave, 0, s>>>(a); break;
+    case kVRows: k_n34_vertex<D, kVRows, 1><<<grid, kWave, 0, s>>>(a); break;
+    case kVTris: k_n34_vertex<D, kVTris, 1><<<grid, kWave, 0, s>>>(a); break;
+    case kVCount: k_n34_vertex<D, kVCount, 1><<<grid, kWave, 0, s>>>(a); break;
+    default: k_n34_vertex<D, kVFill, kFillWaves<D>><<<grid, kFillWaves<D> * kWave, 0, s>>>(a); break;
   }
 }
 
