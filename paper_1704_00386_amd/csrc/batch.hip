@@ -225,7 +225,7 @@ Member *Batch::add(nd_graph *g, int32_t max_iters, void *user) {
     m->zero_bytes = at - z;
     return at;
   };
-  bool support = frontier_;
+  bool support = frontier_ && counts_support(ks);
   if (support) {
     try {
       m->mem.reset(ctx_->alloc, place(true));

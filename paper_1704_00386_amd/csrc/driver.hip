@@ -237,7 +237,8 @@ LoopLayout loop_layout(const KindState &ks, const nd_opts &o, bool flags,
   // Support counting skips flagged r-cliques whose value cannot change; with
   // active counts taken, every flagged one runs (the counts are defined by
   // what the notifications flag).
-  if (flags && o.use_frontier && !wants_indicator(o, false)) {
+  if (flags && o.use_frontier && !wants_indicator(o, false) &&
+      counts_support(ks)) {
     L.slack = round256(ks.tau_bytes * nr);
     L.lost = round256(nr << lost_shift(ks));
   }

@@ -434,6 +434,14 @@ void launch_tiny(const KindState &ks, const void *tau_in, void *tau0, void *tau1
 // at once: 2, or ND_PREP_THREADS.
 int prep_threads();
 
+// Whether frontier sweeps count support (Support in sweep_dev.h) rather than
+// flag.  With s = r + 1 two r-cliques share one s-clique at most.  Two vertices
+// share many triangles, two edges many 4-cliques: a hub's fall adds thousands
+// of times to one counter, where flags store the same byte ((1,3), 79561
+// vertices with lists of 33573: 14.6 ms counted, 3.4 flagged; 24665 vertices
+// 9.1 and 1.2; (2,4), 276464 edges 4.5 and 3.8, 60 communities 20.6 and 20.0).
+inline bool counts_support(const KindState &ks) { return ks.s == ks.r + 1; }
+
 // Bytes (log2) of a lost-s-clique counter: at most k d_s are counted for one
 // r-clique in one sweep.
 inline int lost_shift(const KindState &ks) {
