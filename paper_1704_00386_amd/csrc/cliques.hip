@@ -1133,13 +1133,25 @@ __global__ __launch_bounds__(NW * kWave) void k_n34_vertex(N34VArgs a) {
       if (t < kWave) wave_scan_lds(L.pre, d);
       sync();
       const int32_t work = L.pre[d];
+      // Bound by its instructions (17.7 ms on the block model's vertices of
+      // degree up to 128): a thread's rows only go up, so the next is a step
+      // or two away instead of a search, and nb is searched in 32 bits (12.9).
+      int i = 0;
       for (int32_t y = t; y < work; y += NT) {
-        const int i = row_of(L.pre, d, y);
+        while (L.pre[i + 1] <= y) i++;  // pre[d] = work
         const int r = y - L.pre[i];
         int q = d;
         if (L.len[i] <= 4 * d) {
           const int32_t z = T.col[L.ro[i] + L.st[i] + r];
-          q = (int)lower_bound<int32_t>(L.nb, i + 1, d, z);
+          int e = d;
+          q = i + 1;
+          while (q < e) {
+            const int mid = (q + e) >> 1;
+            if (L.nb[mid] < z)
+              q = mid + 1;
+            else
+              e = mid;
+          }
           if (q < d && L.nb[q] != z) q = d;
         } else {
           const int32_t z = L.nb[i + 1 + r];
