@@ -298,11 +298,16 @@ __device__ __forceinline__ T slack_word(bool changed, int64_t cnt, int32_t c) {
 // told >= c' and tau_t(Q) >= c' for the other members.  SND marks R' when
 //   h < tau_t(R') <= told  and  tau_t(Q) >= tau_t(R') for every other Q,
 // which keeps every R' that can change, so the iterates are those of full
-// sweeps.  AND with support counting self-activates too and adds v <= told to
-// its own test: an R' that keeps its value through the sweep is read exactly,
-// and if it counted S (read R or the others before they fell), the member of
-// S with the lowest new value was at least c' when the sweep began and finds
-// the others at or above that value.  Byte stores of the same stamp race
+// sweeps.  AND with support counting self-activates too and uses SND's test, on
+// values that R read before it wrote its own: the minima its update gathered
+// (notify_kept and the like), or a second gather ahead of the write
+// (update_hub).  One rule for every list length: of the members of S that fall
+// in one sweep, the first to write had read all the others before any of them
+// wrote, so all at or above c', and R', which keeps its value, exactly; R'
+// holds the minimum it saw, which lies in (h, told], and S is counted.  (A hub
+// that wrote first and then tested h <= tau(Q) would not do beside that: a Q
+// that had read the hub's new value and fell below it saw its minimum at the
+// hub alone, and the hub then fails on Q.)  Byte stores of the same stamp race
 // harmlessly.
 template <int K, typename T, bool AND>
 __device__ __forceinline__ void notify(const int32_t *__restrict__ ids,
@@ -338,7 +343,7 @@ __device__ __forceinline__ void notify(const int32_t *__restrict__ ids,
         bool others_ok = true;
 #pragma unroll
         for (int y = 0; y < K; y++)
-          if (y != x) others_ok &= AND ? h <= v[u][y] : v[u][x] <= v[u][y];
+          if (y != x) others_ok &= tight ? v[u][x] <= v[u][y] : h <= v[u][y];
         if (h < v[u][x] && (!tight || v[u][x] <= told) && others_ok)
           mark(r[u][x], act_next, stamp_next, sum_next, sp);
       }
@@ -349,11 +354,7 @@ __device__ __forceinline__ void notify(const int32_t *__restrict__ ids,
 // passes it exactly when it holds the minimum rho of S and h < rho <= told,
 // so the members to mark are those of the slots with rho in (h, told] whose
 // bit is set in the argmin mask (bit m*K + x for slot m, member x; K = 1
-// needs no mask).  Only their ids are read again, no tau.  AND with support
-// counting uses it on the values its update read in place: an R' that keeps
-// its value was read exactly, and of two members of S that both fall in one
-// sweep at least one read the other before that one's write (each reads S
-// before it writes), so it sees S still whole and counts it.
+// needs no mask).  Only their ids are read again, no tau.
 template <int K, int G, int M>
 __device__ __forceinline__ void notify_kept(const int32_t *__restrict__ ids,
                                             int64_t b, int64_t d, int sl,
@@ -1106,15 +1107,25 @@ __device__ bool update_hub(const int64_t *__restrict__ inc_off,
     }
   }
   const bool ch = h != told;
-  if (t == 0) store_tau<T, AND>(tau_out + R, h, ch);
-  if (FR && sp.slack && t == 0)
-    ((T *)sp.slack)[R] = slack_word<T>(ch, ge, c);
-  if (FR && ch && act_next) {
+  auto store = [&] {
+    if (t != 0) return;
+    store_tau<T, AND>(tau_out + R, h, ch);
+    if (FR && sp.slack) ((T *)sp.slack)[R] = slack_word<T>(ch, ge, c);
+  };
+  const bool notifies = FR && ch && act_next != nullptr;
+  // AND with support counting notifies before R's value is written (notify)
+  const bool first = AND && sp.slack != nullptr && notifies;
+  if (!first) store();
+  if (notifies) {
     const uint8_t next = stamp == 255 ? 1 : stamp + 1;
     if ((!AND || sp.slack) && t == 0)
       self_activate(R, act_next, next, sum_next, sp);
     notify<K, T, AND>(inc_ids, b, d, t, kBlockThreads, told, h, tau_in,
                       act_next, next, sum_next, sp);
+  }
+  if (first) {
+    __syncthreads();  // every thread has read
+    store();
   }
   __syncthreads();
   return t == 0 && ch;
