@@ -41,13 +41,13 @@ struct TinyLds {
 struct TinyArgs {
   const int64_t *inc_off;
   const int32_t *inc_ids;
-  const void *tau_in;  // tau of the first sweep, nr values
-  void *tau_out[2];    // receive the last sweep's values
+  const void *tau_in;  // tau of the first sweep
+  void *tau_out[2];    // receive the last sweep's values (of the swept
+                       // r-cliques; the others keep their zeros)
   SweepStats *ring;    // cleared
   int ring_len;
   int64_t first;       // number of the first sweep
   int count;           // sweeps, at most
-  int64_t nr;
   int swept, P;
   // bins by list length, longest first: [0, end[0]) lists above 256, then
   // 65..256, 17..64, 5..16, 1..4
@@ -145,8 +145,7 @@ __global__ __launch_bounds__(kTinyThreads) void k_sweep_tiny(TinyArgs a) {
   }
   for (int q = 0; q < 2; q++) {
     T *out = (T *)a.tau_out[q];
-    for (int64_t i = t; i < a.nr; i += kTinyThreads)
-      out[i] = i < a.swept ? L.tau[cur][i] : (T)0;
+    for (int i = t; i < a.swept; i += kTinyThreads) out[i] = L.tau[cur][i];
   }
 }
 
@@ -183,7 +182,6 @@ void launch_tiny(const KindState &ks, const void *tau_in, void *tau0, void *tau1
   a.ring_len = ring_len;
   a.first = first;
   a.count = count;
-  a.nr = ks.nr;
   a.swept = (int)ks.bin_lo[kBinZero];
   a.P = (int)ks.P;
   const int last[5] = {kBinWave8, kBinG64, kBinG16, kBinG4, kBinG1};

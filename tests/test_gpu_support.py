@@ -204,3 +204,24 @@ def test_values_narrow_between_sweeps():
     first = kappa["snd", False]
     assert all(torch.equal(first, k) for k in kappa.values())
     assert torch.equal(g.update("core", first), first)
+
+
+# The one-workgroup path on a graph most of whose r-cliques are never swept: its
+# time follows the swept ones.  A path of 8000 vertices, 4000 sweeps in 125
+# launches, alone and among ten million isolated vertices: storing the latter's
+# values with every launch takes one workgroup at least 0.13 ms (20 MB at 64
+# bytes a clock), 16 ms in all, beside about 20 ms for the sweeps.
+def test_small_graph_among_many_isolated_vertices():
+    import torch
+    import paper_1704_00386_amd as nd
+    i = torch.arange(7999, device="cuda", dtype=torch.int32)
+    ctx = nd.Context(0)
+    ms = {}
+    for n in (8000, 10_000_000):
+        g = nd.Graph.from_edges(ctx, n, i, i + 1)
+        runs = [g.decompose("core", "snd") for _ in range(4)]
+        kappa, res = runs[0]
+        assert res["sweeps"] == 4000 and int(kappa.sum()) == 8000
+        assert int(kappa[8000:].sum()) == 0
+        ms[n] = min(r["ms_iterate"] for _, r in runs)
+    assert ms[10_000_000] < 1.25 * ms[8000] + 2, ms
