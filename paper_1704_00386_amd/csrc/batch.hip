@@ -148,7 +148,7 @@ Batch::Batch(nd_ctx *ctx, nd_kind kind, nd_mode mode, bool tau16,
     : ctx_(ctx), kind_(kind), mode_(mode), tau16_(tau16), frontier_(frontier) {
   cfg_ = default_config(ctx);
   // (an epoch sweeps every member: the gathers of many graphs)
-  notify_div_ = frontier_switch(INT64_MAX);
+  notify_div_ = frontier_switch(false);
   if (const char *v = getenv("ND_BATCH_NO_GRAPH")) use_graph = v[0] != '1';
   ND_HIP(hipStreamCreateWithFlags(&s_, hipStreamNonBlocking));
   hipEvent_t ev;

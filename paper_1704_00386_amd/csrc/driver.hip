@@ -19,9 +19,9 @@
 
 namespace nd {
 
-int frontier_switch(int64_t gathers) {
+int frontier_switch(bool late) {
   if (const char *v = getenv("ND_FRONTIER_SWITCH")) return atoi(v);
-  return gathers <= (int64_t)1 << 22 ? 512 : 8;
+  return late ? 512 : 8;
 }
 
 namespace {
@@ -43,6 +43,7 @@ constexpr int64_t kSumsSwept = 1 << 20;
 // 1.6 ms a sweep side by side, 1.9 spread.
 constexpr unsigned long long kSpreadBelow = 1 << 15;
 constexpr int64_t kWatchGathers = (int64_t)1 << 26;  // see watch in sweep_loop
+constexpr int64_t kWatchApart = (int64_t)1 << 24;
 // Sweeps enqueued one by one for narrowing's sake (see sweep_loop).
 constexpr int64_t kNarrowSweeps = 8;
 constexpr int kGridPerCu = 64;    // sweep workgroups per CU (they stride;
@@ -278,7 +279,7 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
         fill_u8(b.act[i], 0, nr, s);  // no stamps yet
       fill_u8(b.act_sum[i], 0, ng, s);
     }
-    const int div = frontier_switch(ks.P * ks.k);
+    const int div = frontier_switch(notifies_late(ks));
     notify_below = (indicator || div <= 0)
                        ? ~0ull
                        : (unsigned long long)(ks.bin_lo[kBinZero] / div);
@@ -304,9 +305,12 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
   // frontier's registers (block model: 22.2 ms against 23.4 a full sweep).
   // Where sweeps are long (2^26 gathers, about 0.3 ms), they are enqueued one
   // by one until notifications start, so that all the plain ones are known;
-  // on shorter ones the round trip costs more than it saves.
+  // on shorter ones the round trip costs more than it saves.  From 2^24 where
+  // the plain sweeps have launches that the notifying ones have not (k-core,
+  // 3.6e7 gathers in lists of 1200: 3.6 ms unwatched, 2.6 watched).
   bool plain = flags && !indicator;
-  const bool watch = plain && ks.P * ks.k >= kWatchGathers;
+  const bool apart = swept_apart(ks, kBinWave) || swept_apart(ks, kBinWave16);
+  const bool watch = plain && ks.P * ks.k >= (apart ? kWatchApart : kWatchGathers);
   // Small graphs: every sweep in one workgroup's LDS (tiny.hip).  SND only:
   // AND's sweeps pass values on within a sweep and so are fewer.
   const bool tiny = !and_mode && !flags && !step_by_step && tiny_fits(ks);

@@ -442,6 +442,21 @@ int prep_threads();
 // 9.1 and 1.2; (2,4), 276464 edges 4.5 and 3.8, 60 communities 20.6 and 20.0).
 inline bool counts_support(const KindState &ks) { return ks.s == ks.r + 1; }
 
+// Whether full sweeps that notify nobody give a bin a launch of its own, its
+// values in registers: with k <= 2 where the bin holds at least half of the
+// swept r-cliques and so fills the GPU by itself (k-core, 30000 vertices, lists
+// of 700..1000: 1.34 ms a decomposition, 1.64 in the common launch through LDS;
+// of 1100..1300: 1.93 and 3.76, a workgroup and a histogram each; k-truss, 2.8M
+// edges, 1000..1300: four sweeps 100 and 116 ms).  With k = 5 both are alike
+// (3.4 and 3.6 ms), and with k = 2 lists of 513..1024 are quicker in the common
+// launch ((1,3), 8000 vertices 1.03 and 0.91); where the bins are mixed, the
+// hubs' graphs among them, one launch for all wins.
+inline bool swept_apart(const KindState &ks, int bin) {
+  const int64_t n = ks.bin_hi[bin] - ks.bin_lo[bin];
+  const bool gains = bin == kBinWave ? ks.k <= 2 : bin == kBinWave16 && ks.k == 1;
+  return gains && n > 0 && 2 * n >= ks.bin_lo[kBinZero];
+}
+
 // Bytes (log2) of a lost-s-clique counter: at most k d_s are counted for one
 // r-clique in one sweep.
 inline int lost_shift(const KindState &ks) {
@@ -457,7 +472,10 @@ inline int lost_shift(const KindState &ks) {
 // just as a sparse one, and the sparse one's chain is longer: d = 512 (k-truss
 // of 1.2M gathers 0.46 ms at 8, 0.36 at 256 and 0.37 at 1024; (1,3) of 0.7M
 // 1.11 / 0.50 / 0.38; k-core of 1.9M 0.77 / 0.69 / 0.66).  ND_FRONTIER_SWITCH
-// overrides both (0: from the first sweep on).
-int frontier_switch(int64_t gathers);
+// overrides all (0: from the first sweep on).
+inline bool notifies_late(const KindState &ks) {
+  return ks.P * ks.k <= (int64_t)1 << 22;
+}
+int frontier_switch(bool late);
 
 }  // namespace nd

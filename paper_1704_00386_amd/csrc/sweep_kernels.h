@@ -231,7 +231,7 @@ __device__ __forceinline__ void sweep_flat_fr(const SweepArgs &a, int64_t lo,
 
 // One bin [lo, hi) of G lanes per r-clique with M values per lane, swept by
 // the workgroups block .. of nblocks (a launch of its own, or a block range
-// of k_sweep_small).  With `flat` LDS (small bins), a full sweep that
+// of k_sweep_small).  With `flat` LDS (lists up to 256), a full sweep that
 // notifies nobody runs as sweep_flat and a full SND sweep that notifies as
 // sweep_flat_fr.  Sweeps that read flags find their flagged r-cliques per
 // wave (sweep_sparse): run-based variants of those (marking, or compacting
@@ -246,7 +246,7 @@ __device__ __forceinline__ void sweep_bin(const SweepArgs &a, int64_t lo,
                                           FlatLds<T> *flat, bool spread) {
   constexpr int kPerWave = kWave / G;
   // M == 0: the wave's share of the LDS for its list (update_wave)
-  T *buf = flat->rho + threadIdx.x / kWave * kWaveList;
+  T *buf = M == 0 || G <= 4 ? flat->rho + threadIdx.x / kWave * kWaveList : nullptr;
   const int64_t wave = (block * blockDim.x + threadIdx.x) / kWave;
   const int64_t waves = nblocks * (blockDim.x / kWave);
   const int sub = lane_id() / G;
@@ -265,7 +265,7 @@ __device__ __forceinline__ void sweep_bin(const SweepArgs &a, int64_t lo,
     // ids again to notify); with 64 r-cliques per step instead of 16 there are
     // a quarter of the chains.
     constexpr bool kLane = G <= 4 && M == 4;
-    uint8_t *mbuf = flat->mask + threadIdx.x / kWave * kWaveList;
+    uint8_t *mbuf = kLane ? flat->mask + threadIdx.x / kWave * kWaveList : nullptr;
     sweep_sparse<K, kLane ? 1 : G, kLane ? 0 : M, T, AND>(
                                   a.inc_off, a.inc_ids, tin, tout, a.cap_by_tau,
                                   lo, hi, wave, waves, act, act_next, a.stamp,
@@ -417,6 +417,17 @@ __global__ __launch_bounds__(256, 6) void k_sweep_small(SweepArgs a, SmallBins s
   }
 }
 
+// A full sweep that notifies nobody over one bin of the longer lists, M values
+// per lane in registers (see swept_apart).
+template <int K, int M, typename T, bool AND>
+__global__ __launch_bounds__(256) void k_sweep_regs(SweepArgs a, int64_t lo,
+                                                    int64_t hi) {
+  if (prev_changed(a) == 0) return;
+  sweep_bin<K, 64, M, T, AND, false>(a, lo, hi, blockIdx.x, gridDim.x, nullptr,
+                                     nullptr, nullptr, nullptr, Support(), nullptr,
+                                     false);
+}
+
 // Blocks for a bin of n r-cliques at G lanes each, at most a.grid_cap, and
 // never more than grid_stride allows (the kernels stride over the rest).
 inline unsigned regs_grid(const SweepArgs &a, int64_t n, int G) {
@@ -432,9 +443,28 @@ void launch_bins(const KindState &ks, const SweepArgs &a, hipStream_t s) {
   static_assert(kHubMin == kWaveList + 1 && kRanges == 6, "ranges and bins agree");
   SmallBins sb{};
   int64_t total = 0;
+  bool apart16 = false, apart32 = false;
+  if constexpr (!FR && K <= 2) {
+    apart32 = swept_apart(ks, kBinWave);
+    apart16 = swept_apart(ks, kBinWave16);
+    if (apart32) {
+      const int64_t lo = ks.bin_lo[kBinWave], hi = ks.bin_hi[kBinWave];
+      k_sweep_regs<K, 32, T, AND><<<regs_grid(a, hi - lo, 64), 256, 0, s>>>(a, lo, hi);
+      ND_LAUNCHED();
+    }
+    if constexpr (K == 1) {
+      if (apart16) {
+        const int64_t lo = ks.bin_lo[kBinWave16], hi = ks.bin_hi[kBinWave16];
+        k_sweep_regs<K, 16, T, AND><<<regs_grid(a, hi - lo, 64), 256, 0, s>>>(a, lo, hi);
+        ND_LAUNCHED();
+      }
+    }
+  }
   for (int i = 0; i < kRanges; i++) {
-    const int first = i == 0 ? kBinBlock : i == 1 ? kBinWave16 : kBinG64 + i - 2;
-    const int last = i == 0 ? kBinWave : i == 1 ? kBinWave8 : first;
+    const int first = i == 0   ? kBinBlock
+                      : i == 1 ? (apart16 ? kBinWave8 : kBinWave16)
+                               : kBinG64 + i - 2;
+    const int last = i == 0 ? (apart32 ? kBinBlock : kBinWave) : i == 1 ? kBinWave8 : first;
     sb.lo[i] = ks.bin_lo[first];
     sb.hi[i] = ks.bin_hi[last];
     sb.first[i] = (unsigned)total;

@@ -225,3 +225,43 @@ def test_small_graph_among_many_isolated_vertices():
         assert int(kappa[8000:].sum()) == 0
         ms[n] = min(r["ms_iterate"] for _, r in runs)
     assert ms[10_000_000] < 1.25 * ms[8000] + 2, ms
+
+
+# Graphs most of whose lists lie in one range of the longer ones (257..512,
+# 513..1024, 1025..2047, above), whose full sweeps may run in launches of their
+# own; some lists fall outside the range.
+DENSE = {"core_400": ("core", 1300, 0.3, 257, 512), "core_800": ("core", 1300, 0.62, 513, 1024),
+         "core_1200": ("core", 1500, 0.82, 1025, 2047),
+         "core_mixed": ("core", 1300, 0.79, 800, 1300),
+         "core_2200": ("core", 2400, 0.92, 2048, 2400),
+         "nucleus13_1400": ("nucleus13", 60, 0.95, 1025, 2047)}
+
+
+@pytest.mark.parametrize("name", list(DENSE))
+def test_long_lists_in_one_range(name):
+    import torch
+    import paper_1704_00386_amd as nd
+    kind, n, p, lo, hi = DENSE[name]
+    rng = np.random.default_rng(n)
+    i, j = np.triu_indices(n, 1)
+    keep = rng.random(i.size) < p
+    # and a sparse part
+    src = np.concatenate([i[keep], n + np.arange(100)])
+    dst = np.concatenate([j[keep], n + 1 + np.arange(100)])
+    raw = RawGraph(n + 101, src.astype(np.int32), dst.astype(np.int32), "dense")
+    seq = oracle.Graph.from_raw(raw).snd(*nd.RS[kind])
+    swept = seq[0][seq[0] > 0]
+    assert 2 * ((swept >= lo) & (swept <= hi)).sum() >= swept.size
+    ctx = nd.Context(0)
+    g = nd.Graph.from_edges(ctx, raw.n, torch.from_numpy(raw.src),
+                            torch.from_numpy(raw.dst))
+    for frontier in (False, True):
+        its = []
+        g.decompose(kind, "snd", use_frontier=frontier, keep_iterates=its)
+        assert len(its) == len(seq) - 1
+        for t, (_, tau) in enumerate(its, start=1):
+            assert np.array_equal(tau.cpu().numpy(), seq[t]), (frontier, t)
+        for mode in ("snd", "and"):
+            kappa, _ = g.decompose(kind, mode, use_frontier=frontier)
+            assert np.array_equal(kappa.cpu().numpy(), seq[-1]), (mode, frontier)
+    assert np.array_equal(g.update(kind, torch.from_numpy(seq[0])).cpu().numpy(), seq[1])
