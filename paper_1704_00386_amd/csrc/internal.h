@@ -471,10 +471,18 @@ inline int lost_shift(const KindState &ks) {
 // 8192.  Up to 2^22 gathers a sweep a full one is a launch and a chain of loads
 // just as a sparse one, and the sparse one's chain is longer: d = 512 (k-truss
 // of 1.2M gathers 0.46 ms at 8, 0.36 at 256 and 0.37 at 1024; (1,3) of 0.7M
-// 1.11 / 0.50 / 0.38; k-core of 1.9M 0.77 / 0.69 / 0.66).  ND_FRONTIER_SWITCH
+// 1.11 / 0.50 / 0.38; k-core of 1.9M 0.77 / 0.69 / 0.66).  With support counts
+// also up to 2^17 swept r-cliques with 128 gathers and more each: their values
+// fit the caches, so a full sweep's gathers are quick, while the notifications
+// of long lists meet on few counters (k-core, 30000 vertices, lists of 900:
+// 1.95 ms at 8, 1.43 at 512, of 300: 0.82 and 0.65; 100000 vertices, 900: 12.1
+// and 11.0; k-truss, 108000 edges, 216: 3.87 and 3.12; but 100000 vertices, 100:
+// 1.21 and 1.36, 300000 vertices, 100: 2.71 and 3.22).  ND_FRONTIER_SWITCH
 // overrides all (0: from the first sweep on).
 inline bool notifies_late(const KindState &ks) {
-  return ks.P * ks.k <= (int64_t)1 << 22;
+  const int64_t gathers = ks.P * ks.k, swept = ks.bin_lo[kBinZero];
+  return gathers <= (int64_t)1 << 22 ||
+         (counts_support(ks) && swept <= 1 << 17 && gathers / 128 >= swept);
 }
 int frontier_switch(bool late);
 
