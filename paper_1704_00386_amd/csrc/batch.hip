@@ -147,8 +147,6 @@ Batch::Batch(nd_ctx *ctx, nd_kind kind, nd_mode mode, bool tau16,
              bool frontier, hipStream_t caller)
     : ctx_(ctx), kind_(kind), mode_(mode), tau16_(tau16), frontier_(frontier) {
   cfg_ = default_config(ctx);
-  // (an epoch sweeps every member: the gathers of many graphs)
-  notify_div_ = frontier_switch(false);
   if (const char *v = getenv("ND_BATCH_NO_GRAPH")) use_graph = v[0] != '1';
   ND_HIP(hipStreamCreateWithFlags(&s_, hipStreamNonBlocking));
   hipEvent_t ev;
@@ -314,9 +312,10 @@ void Batch::rebuild() {
       }
       G.slack = m.slack;
       G.lost_shift = m.lost_shift;
-      G.notify_below = notify_div_ <= 0
-                           ? ~0ull
-                           : (unsigned long long)(ks.bin_lo[kBinZero] / notify_div_);
+      // (an epoch sweeps every member: the gathers of many graphs)
+      const int div = frontier_switch(notifies_late(ks, INT64_MAX));
+      G.notify_below = div <= 0 ? ~0ull
+                                : (unsigned long long)(ks.bin_lo[kBinZero] / div);
     }
     hg.push_back(G);
     work += ks.P;

@@ -279,7 +279,7 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
         fill_u8(b.act[i], 0, nr, s);  // no stamps yet
       fill_u8(b.act_sum[i], 0, ng, s);
     }
-    const int div = frontier_switch(notifies_late(ks));
+    const int div = frontier_switch(notifies_late(ks, ks.P * ks.k));
     notify_below = (indicator || div <= 0)
                        ? ~0ull
                        : (unsigned long long)(ks.bin_lo[kBinZero] / div);

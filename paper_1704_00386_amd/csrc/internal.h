@@ -479,10 +479,11 @@ inline int lost_shift(const KindState &ks) {
 // and 11.0; k-truss, 108000 edges, 216: 3.87 and 3.12; but 100000 vertices, 100:
 // 1.21 and 1.36, 300000 vertices, 100: 2.71 and 3.22).  ND_FRONTIER_SWITCH
 // overrides all (0: from the first sweep on).
-inline bool notifies_late(const KindState &ks) {
-  const int64_t gathers = ks.P * ks.k, swept = ks.bin_lo[kBinZero];
+// (gathers: of a sweep that may notify, of many graphs in a batch.)
+inline bool notifies_late(const KindState &ks, int64_t gathers) {
+  const int64_t swept = ks.bin_lo[kBinZero];
   return gathers <= (int64_t)1 << 22 ||
-         (counts_support(ks) && swept <= 1 << 17 && gathers / 128 >= swept);
+         (counts_support(ks) && swept <= 1 << 17 && ks.P * ks.k / 128 >= swept);
 }
 int frontier_switch(bool late);
 

@@ -243,10 +243,11 @@ __device__ __forceinline__ void sweep_bin(const SweepArgs &a, int64_t lo,
                                           uint8_t *act_next,
                                           const uint8_t *act_sum,
                                           uint8_t *sum_next, const Support &sp,
-                                          FlatLds<T> *flat, bool spread) {
+                                          FlatLds<T> *flat, bool spread,
+                                          int wave_list = kWaveList) {
   constexpr int kPerWave = kWave / G;
   // M == 0: the wave's share of the LDS for its list (update_wave)
-  T *buf = M == 0 || G <= 4 ? flat->rho + threadIdx.x / kWave * kWaveList : nullptr;
+  T *buf = M == 0 || G <= 4 ? flat->rho + threadIdx.x / kWave * wave_list : nullptr;
   const int64_t wave = (block * blockDim.x + threadIdx.x) / kWave;
   const int64_t waves = nblocks * (blockDim.x / kWave);
   const int sub = lane_id() / G;

@@ -265,3 +265,30 @@ def test_long_lists_in_one_range(name):
             kappa, _ = g.decompose(kind, mode, use_frontier=frontier)
             assert np.array_equal(kappa.cpu().numpy(), seq[-1]), (mode, frontier)
     assert np.array_equal(g.update(kind, torch.from_numpy(seq[0])).cpu().numpy(), seq[1])
+
+
+# A batch with 83200 lists of 1025..2047, so that a tile holds several (a wave
+# each) at most tile lengths, and one with few (a workgroup each): the values
+# of the graphs one by one.
+@pytest.mark.parametrize("count", [2, 64])
+def test_batch_of_long_lists(count):
+    import torch
+    import paper_1704_00386_amd as nd
+    n = 1300
+    ctx = nd.Context(0)
+    i, j = torch.triu_indices(n, n, 1, device="cuda")
+    gs = []
+    for seed in range(count):
+        gen = torch.Generator(device="cuda").manual_seed(seed)
+        keep = torch.rand(i.numel(), generator=gen, device="cuda") < 0.84
+        gs.append(nd.Graph.from_edges(ctx, n, i[keep].int(), j[keep].int()))
+        gs[-1].prepare("core")
+        ds = gs[-1].sdegree("core")
+        assert int((ds > 1024).sum()) == n
+    want = [g.decompose("core", "snd") for g in gs]
+    for mode in ("snd", "and"):
+        for frontier in (False, True):
+            kappas, res = nd.batch_decompose(ctx, gs, "core", mode, use_frontier=frontier)
+            for k, r, (w, wr) in zip(kappas, res, want):
+                assert torch.equal(k, w), (mode, frontier)
+                assert mode == "and" or r["sweeps"] == wr["sweeps"]
