@@ -57,6 +57,13 @@ constexpr int pass_units(int type) {
          : type == kBinWave8 ? 2 : 1;
 }
 
+// A tile's work at most.  With two tiles a resident workgroup a batch of large
+// graphs ends each epoch on a partly filled round of long tiles (four k-trusses
+// of 500,000 edges with lists of 590: 280 ms in tiles of 290 units, 251 of 64,
+// 244 of 16; 16 gained nothing more on two of 10^6 edges with lists of 1200, 373 /
+// 331 / 326 ms, and lost 4% in AND).
+constexpr int64_t kMaxUnits = 64;
+
 // After an epoch, one workgroup: each graph's changed total (read by its
 // tiles of the next epoch and by the poll), the next sweep's counters
 // cleared, the epoch advanced.  16 lanes a graph, one counter part each.
@@ -288,7 +295,8 @@ void Batch::rebuild() {
                      rclq_per_pass(b) * pass_units(b);
   }
   const int64_t target = (int64_t)cfg_.grid * cfg_.tiles_per_group;
-  const int64_t units = std::max<int64_t>(1, units_total / std::max<int64_t>(target, 1));
+  const int64_t units = std::min(
+      kMaxUnits, std::max<int64_t>(1, units_total / std::max<int64_t>(target, 1)));
   for (auto &mp : members_) {
     Member &m = *mp;
     m.slot = -1;
