@@ -22,7 +22,8 @@
 // h-index search (d_s > 2048).  After the first sweep only members that a
 // fallen neighbour may have pulled below their value run again (a byte each).
 // Queries go out heaviest first (by the query's own d_s) from one counter, so
-// that no workgroup starts a long one when the others are done.  Queries
+// that no workgroup starts a long one when the others are done.  Many small
+// ones have workgroups of one wave with tables of 64 members.  Queries
 // whose P(q) does not fit the LDS table run one at a time through the global
 // sweep kernels.
 #include <limits.h>
@@ -46,8 +47,14 @@ using namespace dev;
 
 constexpr int kEgoCap = 4096;      // members of P(q) held in LDS
 constexpr int kEgoThreads = 512;   // 8 waves
-constexpr int kEgoBits = 15;       // bitmap of hashed members: 2^15 bits
-constexpr int kEgoWaves = kEgoThreads / kWave;
+// Small queries, P(q) of at most 64: a workgroup of 8 waves spends its time on
+// barriers and clearing tables, so from 8192 of them on (twice the one-wave
+// workgroups of a GPU) each has a wave: a million k-core queries on a path 24.8
+// -> 3.4 ms, on a random graph of mean degree 8 46 -> 8.9 ms, 200,000 k-truss
+// queries with lists of 10 14.8 -> 3.9 ms.
+constexpr int kEgoSmall = 64;
+constexpr int64_t kEgoManySmall = 8192;
+constexpr int kEgoClasses = 32;
 
 struct EgoArgs {
   const int64_t *inc_off;  // internal numbering
@@ -62,20 +69,36 @@ struct EgoArgs {
   uint8_t *big;            // per query: 1 = run it through the fallback
   int32_t *not_converged;  // set when a query stopped at max_iters
   const int64_t *order;    // queries, heaviest first
-  unsigned long long *head;  // next of them to run
+  int64_t begin, end;      // those of this launch
+  unsigned long long *head;  // how many of them have been taken
+  int take;                  // so many at a time
+};
+
+// Queries dealt out by class (powers of two of d_s, largest first), all zero to
+// start with.
+
+// Queries dealt out by class (powers of two of d_s, largest first).
+struct EgoDeal {
+  unsigned long long total[kEgoClasses];   // queries per class
+  unsigned long long placed[kEgoClasses];
+  unsigned long long head[2];              // see EgoArgs, per launch
 };
 
 // The tables of one workgroup: P(q) ascending, the members' values, the
-// bitmap, and the members to recompute.
+// bitmap (8 bits a member), and the members to recompute.
+template <int CAP>
 struct EgoLds {
-  int32_t mem[kEgoCap];
-  int32_t tl[kEgoCap];
-  uint32_t bits[1 << (kEgoBits - 5)];
-  uint8_t dirty[kEgoCap];
+  static constexpr int kBits = CAP * 8;
+  int32_t mem[CAP];
+  int32_t tl[CAP];
+  uint32_t bits[kBits / 32];
+  uint8_t dirty[CAP];
 };
 
+template <int CAP>
 __device__ __forceinline__ uint32_t ego_hash(int32_t x) {
-  return ((uint32_t)x * 2654435761u) >> (32 - kEgoBits);
+  constexpr int kLog = 31 - __builtin_clz(EgoLds<CAP>::kBits);
+  return ((uint32_t)x * 2654435761u) >> (32 - kLog);
 }
 
 __device__ __forceinline__ int ego_find(const int32_t *mem, int np, int32_t x) {
@@ -91,8 +114,9 @@ __device__ __forceinline__ int ego_find(const int32_t *mem, int np, int32_t x) {
 }
 
 // Member number of r-clique x, -1 outside P(q).
-__device__ __forceinline__ int ego_member(const EgoLds &L, int np, int32_t x) {
-  const uint32_t h = ego_hash(x);
+template <int CAP>
+__device__ __forceinline__ int ego_member(const EgoLds<CAP> &L, int np, int32_t x) {
+  const uint32_t h = ego_hash<CAP>(x);
   if (!((L.bits[h >> 5] >> (h & 31)) & 1u)) return -1;
   return ego_find(L.mem, np, x);
 }
@@ -102,14 +126,15 @@ __device__ __forceinline__ int32_t ego_load(const int32_t *p) {
 }
 
 // Current value of r-clique x: its LDS slot when x is in P(q), else d_s.
-__device__ __forceinline__ int32_t ego_val(const EgoLds &L, int np,
+template <int CAP>
+__device__ __forceinline__ int32_t ego_val(const EgoLds<CAP> &L, int np,
                                            const int32_t *ds, int32_t x) {
   const int p = ego_member(L, np, x);
   return p >= 0 ? ego_load(&L.tl[p]) : ds[x];
 }
 
-template <int K>
-__device__ __forceinline__ int32_t ego_rho(const EgoArgs &a, const EgoLds &L,
+template <int K, int CAP>
+__device__ __forceinline__ int32_t ego_rho(const EgoArgs &a, const EgoLds<CAP> &L,
                                            int np, int64_t j) {
   const int32_t *q = a.inc_ids + (int64_t)K * j;
   int32_t v = ego_val(L, np, a.ds, q[0]);
@@ -119,8 +144,8 @@ __device__ __forceinline__ int32_t ego_rho(const EgoArgs &a, const EgoLds &L,
 }
 
 // H of one member with list [b, b + d), d <= 64 M, capped at its value c.
-template <int K, int M>
-__device__ __forceinline__ int32_t ego_h(const EgoArgs &a, const EgoLds &L, int np,
+template <int K, int M, int CAP>
+__device__ __forceinline__ int32_t ego_h(const EgoArgs &a, const EgoLds<CAP> &L, int np,
                                          int64_t b, int64_t d, int32_t c) {
   int32_t rho[M];
 #pragma unroll
@@ -158,53 +183,103 @@ __device__ void block_bitonic(int32_t *v, int n) {
   }
 }
 
-// Queries in classes of their d_s (powers of two), largest first: one
-// workgroup counts the classes and deals the queries out.
-__global__ __launch_bounds__(1024) void k_ego_order(EgoArgs a, int64_t *order) {
-  __shared__ unsigned long long at[32];
+// Class of query i: 0..30, fewer leading zeros for larger d_s; 31 for d_s = 0
+// and for ids out of range, which k_check_queries reports.
+__device__ __forceinline__ int ego_class(const EgoArgs &a, int64_t nr, int64_t i) {
+  const int32_t q = a.queries[i];
+  const int32_t d = q >= 0 && q < nr ? a.ds[a.inv[q]] : 0;
+  return d < 1 ? kEgoClasses - 1 : __clz(d);
+}
+
+// Few queries: one workgroup counts the classes and deals the queries out.
+__global__ __launch_bounds__(1024) void k_ego_order(EgoArgs a, int64_t nr,
+                                                    EgoDeal *__restrict__ deal,
+                                                    int64_t *__restrict__ order) {
+  __shared__ int32_t at[kEgoClasses];
   const int t = threadIdx.x;
-  if (t < 32) at[t] = 0;
-  if (t == 0) *a.head = 0;
+  if (t < kEgoClasses) at[t] = 0;
+  if (t < 2) deal->head[t] = 0;
   __syncthreads();
-  auto cls = [&](int64_t i) {
-    const int32_t d = a.ds[a.inv[a.queries[i]]];
-    return d < 1 ? 31 : __clz(d);  // 0..30: fewer leading zeros, larger d_s
-  };
-  for (int64_t i = t; i < a.count; i += 1024) atomicAdd(&at[cls(i)], 1ull);
+  for (int64_t i = t; i < a.count; i += 1024) atomicAdd(&at[ego_class(a, nr, i)], 1);
   __syncthreads();
   if (t == 0) {
-    unsigned long long run = 0;
-    for (int c = 0; c < 32; c++) {
-      const unsigned long long n = at[c];
+    int32_t run = 0;
+    for (int c = 0; c < kEgoClasses; c++) {
+      const int32_t n = at[c];
       at[c] = run;
       run += n;
     }
   }
   __syncthreads();
   for (int64_t i = t; i < a.count; i += 1024)
-    order[atomicAdd(&at[cls(i)], 1ull)] = i;
+    order[atomicAdd(&at[ego_class(a, nr, i)], 1)] = i;
 }
 
-template <int K>
-__global__ __launch_bounds__(kEgoThreads) void k_ego(EgoArgs a) {
-  __shared__ EgoLds L;
-  __shared__ int32_t wsum[kEgoWaves];
+// Many: the classes counted, then the queries dealt out.
+__global__ __launch_bounds__(1024) void k_ego_count(EgoArgs a, int64_t nr,
+                                                    EgoDeal *__restrict__ deal) {
+  __shared__ int32_t n[kEgoClasses];
+  const int t = threadIdx.x;
+  if (t < kEgoClasses) n[t] = 0;
+  __syncthreads();
+  for (int64_t i = (int64_t)blockIdx.x * 1024 + t; i < a.count; i += (int64_t)gridDim.x * 1024)
+    atomicAdd(&n[ego_class(a, nr, i)], 1);
+  __syncthreads();
+  if (t < kEgoClasses && n[t]) atomicAdd(&deal->total[t], (unsigned long long)n[t]);
+}
+
+__global__ __launch_bounds__(1024) void k_ego_deal(EgoArgs a, int64_t nr,
+                                                   EgoDeal *__restrict__ deal,
+                                                   int64_t *__restrict__ order) {
+  __shared__ int32_t n[kEgoClasses];
+  __shared__ unsigned long long at[kEgoClasses];
+  const int t = threadIdx.x;
+  unsigned long long start = 0;  // of class t
+  for (int c = 0; c < t && t < kEgoClasses; c++) start += deal->total[c];
+  for (int64_t b = (int64_t)blockIdx.x * 1024; b < a.count; b += (int64_t)gridDim.x * 1024) {
+    if (t < kEgoClasses) n[t] = 0;
+    __syncthreads();
+    const int64_t i = b + t;
+    const int c = i < a.count ? ego_class(a, nr, i) : -1;
+    const int r = c >= 0 ? atomicAdd(&n[c], 1) : 0;
+    __syncthreads();
+    if (t < kEgoClasses && n[t])
+      at[t] = start + atomicAdd(&deal->placed[t], (unsigned long long)n[t]);
+    __syncthreads();
+    if (c >= 0) order[at[c] + r] = i;
+  }
+}
+
+// One workgroup of NT threads per query at a time, P(q) of at most CAP.
+template <int K, int NT, int CAP>
+__global__ __launch_bounds__(NT, NT == kWave ? 4 : 1) void k_ego(EgoArgs a) {
+  constexpr int kWaves = NT / kWave;
+  __shared__ EgoLds<CAP> L;
+  __shared__ int32_t wsum[kWaves];
   __shared__ int s_np, s_changed;
   __shared__ unsigned long long s_next;
   int32_t *mem = L.mem, *tl = L.tl;
   const int t = threadIdx.x, lane = lane_id(), w = t / kWave;
+  int64_t nx = 0;
+  int left = 0;  // queries still held
   while (true) {  // until the counter has passed the last query
-    if (t == 0) s_next = atomicAdd(a.head, 1ull);
-    __syncthreads();
-    const int64_t nx = (int64_t)s_next;
-    __syncthreads();
-    if (nx >= a.count) return;  // uniform over the block
+    if (left == 0) {
+      if (t == 0) s_next = atomicAdd(a.head, (unsigned long long)a.take);
+      __syncthreads();
+      nx = a.begin + (int64_t)s_next;
+      left = a.take;
+      __syncthreads();
+    } else {
+      nx++;
+    }
+    left--;
+    if (nx >= a.end) return;  // uniform over the block
     const int64_t qi = a.order[nx];
     const int32_t R0 = a.inv[a.queries[qi]];
     const int64_t b0 = a.inc_off[R0];
     const int64_t d0 = a.inc_off[R0 + 1] - b0;
     const int64_t nraw = 1 + (int64_t)K * d0;
-    if (nraw > kEgoCap) {  // uniform over the block
+    if (nraw > CAP) {  // uniform over the block
       if (t == 0) {
         a.big[qi] = 1;
         a.est[qi] = -1;
@@ -214,16 +289,16 @@ __global__ __launch_bounds__(kEgoThreads) void k_ego(EgoArgs a) {
     }
     int n2 = 1;
     while (n2 < nraw) n2 <<= 1;
-    for (int i = t; i < n2; i += kEgoThreads)
+    for (int i = t; i < n2; i += NT)
       mem[i] = i == 0 ? R0 : (i < nraw ? a.inc_ids[(int64_t)K * b0 + i - 1]
                                        : INT_MAX);
-    for (int i = t; i < (1 << (kEgoBits - 5)); i += kEgoThreads) L.bits[i] = 0;
+    for (int i = t; i < EgoLds<CAP>::kBits / 32; i += NT) L.bits[i] = 0;
     __syncthreads();
     block_bitonic(mem, n2);
     // drop repeats (none arise from a simple graph, kept for safety): keep
     // the first of each run, compacted through tl
     int keep_cnt = 0;
-    const int per = (n2 + kEgoThreads - 1) / kEgoThreads;
+    const int per = (n2 + NT - 1) / NT;
     const int lo = min(n2, t * per), hi = min(n2, lo + per);
     for (int i = lo; i < hi; i++)
       keep_cnt += mem[i] != INT_MAX && (i == 0 || mem[i] != mem[i - 1]);
@@ -241,14 +316,14 @@ __global__ __launch_bounds__(kEgoThreads) void k_ego(EgoArgs a) {
     int pos = base + incl - keep_cnt;
     for (int i = lo; i < hi; i++)
       if (mem[i] != INT_MAX && (i == 0 || mem[i] != mem[i - 1])) tl[pos++] = mem[i];
-    if (t == kEgoThreads - 1) s_np = base + incl;
+    if (t == NT - 1) s_np = base + incl;
     __syncthreads();
     const int np = s_np;
-    for (int i = t; i < np; i += kEgoThreads) mem[i] = tl[i];
+    for (int i = t; i < np; i += NT) mem[i] = tl[i];
     __syncthreads();
-    for (int i = t; i < np; i += kEgoThreads) {
+    for (int i = t; i < np; i += NT) {
       const int32_t x = mem[i];
-      const uint32_t h = ego_hash(x);
+      const uint32_t h = ego_hash<CAP>(x);
       atomicOr(&L.bits[h >> 5], 1u << (h & 31));
       tl[i] = a.ds[x];
       L.dirty[i] = 1;
@@ -260,7 +335,7 @@ __global__ __launch_bounds__(kEgoThreads) void k_ego(EgoArgs a) {
     while (sweeps < a.max_iters) {
       if (t == 0) s_changed = 0;
       __syncthreads();
-      for (int i = w; i < np; i += kEgoWaves) {
+      for (int i = w; i < np; i += kWaves) {
         // The mark is cleared before the values are read: a neighbour that
         // falls after that marks this member again (it stores its value
         // first, and one CU's LDS serves accesses in order).
@@ -365,11 +440,6 @@ nd_status ego_estimate(nd_graph *g, nd_kind kind, const int32_t *queries,
   k_check_queries<<<grid_for(count, 256), 256, 0, s>>>(dq.p, count, ks.nr,
                                                         flags.p);
   ND_LAUNCHED();
-  int32_t herr[2] = {0, 0};
-  ND_HIP(hipMemcpyAsync(herr, flags.p, sizeof herr, hipMemcpyDeviceToHost, s));
-  ND_HIP(hipStreamSynchronize(s));
-  ND_REQUIRE(herr[0] == 0, ND_ERR_INVALID,
-             "a query id is outside [0, %lld)", (long long)ks.nr);
   EgoArgs a{};
   a.inc_off = ks.inc_off.p;
   a.inc_ids = ks.inc_ids.p;
@@ -383,23 +453,65 @@ nd_status ego_estimate(nd_graph *g, nd_kind kind, const int32_t *queries,
   a.big = big.p;
   a.not_converged = flags.p + 1;
   DArr<int64_t> order(al, count);
-  DArr<unsigned long long> head(al, 1);
+  DArr<EgoDeal> deal(al, 1);
   a.order = order.p;
-  a.head = head.p;
-  k_ego_order<<<1, 1024, 0, s>>>(a, order.p);
-  ND_LAUNCHED();
-  // as many workgroups as stay resident (4 per CU by LDS); the counter deals
-  // out the rest
-  const unsigned grid =
-      (unsigned)std::min<int64_t>(count, (int64_t)g->ctx->num_cu * 4);
+  const bool many = count >= kEgoManySmall;
+  if (many) {
+    fill_u64((uint64_t *)deal.p, 0, sizeof(EgoDeal) / 8, s);
+    const unsigned grid = (unsigned)std::min<int64_t>(grid_for(count, 1024), g->ctx->num_cu);
+    k_ego_count<<<grid, 1024, 0, s>>>(a, ks.nr, deal.p);
+    ND_LAUNCHED();
+    k_ego_deal<<<grid, 1024, 0, s>>>(a, ks.nr, deal.p, order.p);
+    ND_LAUNCHED();
+  } else {
+    k_ego_order<<<1, 1024, 0, s>>>(a, ks.nr, deal.p, order.p);
+    ND_LAUNCHED();
+  }
+  int32_t herr[2] = {0, 0};
+  int64_t big_end = count;  // queries in the classes that may exceed kEgoSmall
+  {
+    PinnedChunk pc;
+    const unsigned long long *total =
+        many ? pc.post(deal.p->total, kEgoClasses, s) : nullptr;
+    const int32_t *hf = pc.read(flags.p, 1, s);
+    ND_REQUIRE(*hf == 0, ND_ERR_INVALID, "a query id is outside [0, %lld)",
+               (long long)ks.nr);
+    int64_t n = 0;
+    for (int c = 0; many && c < kEgoClasses - 1; c++)  // d_s up to 2^(32 - c) - 1
+      if ((((int64_t)1 << (32 - c)) - 1) * ks.k + 1 > kEgoSmall) n += (int64_t)total[c];
+    if (count - n >= kEgoManySmall) big_end = n;
+  }
+  // As many workgroups as stay resident: one of eight waves per CU, 16 of one wave
+  // (136 and 128 registers); the counters deal out the rest.
+  auto launch = [&](auto big_kernel, auto small_kernel) {
+    if (big_end > 0) {
+      a.begin = 0;
+      a.end = big_end;
+      a.head = &deal.p->head[0];
+      a.take = 1;
+      const int64_t grid = std::min<int64_t>(big_end, (int64_t)g->ctx->num_cu);
+      big_kernel<<<(unsigned)grid, kEgoThreads, 0, s>>>(a);
+      ND_LAUNCHED();
+    }
+    if (big_end < count) {
+      a.begin = big_end;
+      a.end = count;
+      a.head = &deal.p->head[1];
+      const int64_t n = count - big_end;
+      const int64_t grid = std::min<int64_t>(n, (int64_t)g->ctx->num_cu * 16);
+      // the counter gives out a query every few nanoseconds
+      a.take = (int)std::min<int64_t>(16, std::max<int64_t>(1, n / (4 * grid)));
+      small_kernel<<<(unsigned)grid, kWave, 0, s>>>(a);
+      ND_LAUNCHED();
+    }
+  };
   switch (ks.k) {
-    case 1: k_ego<1><<<grid, kEgoThreads, 0, s>>>(a); break;
-    case 2: k_ego<2><<<grid, kEgoThreads, 0, s>>>(a); break;
-    case 3: k_ego<3><<<grid, kEgoThreads, 0, s>>>(a); break;
-    case 5: k_ego<5><<<grid, kEgoThreads, 0, s>>>(a); break;
+    case 1: launch(k_ego<1, kEgoThreads, kEgoCap>, k_ego<1, kWave, kEgoSmall>); break;
+    case 2: launch(k_ego<2, kEgoThreads, kEgoCap>, k_ego<2, kWave, kEgoSmall>); break;
+    case 3: launch(k_ego<3, kEgoThreads, kEgoCap>, k_ego<3, kWave, kEgoSmall>); break;
+    case 5: launch(k_ego<5, kEgoThreads, kEgoCap>, k_ego<5, kWave, kEgoSmall>); break;
     default: ND_REQUIRE(false, ND_ERR_UNSUPPORTED, "no ego kernel for k=%d", ks.k);
   }
-  ND_LAUNCHED();
   std::vector<int32_t> hq(count), he(count), hs(count);
   std::vector<uint8_t> hb(count);
   ND_HIP(hipMemcpyAsync(hq.data(), dq.p, sizeof(int32_t) * count,

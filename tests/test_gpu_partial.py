@@ -3,6 +3,8 @@ on the GPU against the oracle's PartialAND: equal values on every listed
 r-clique, for every kind, on random sets, ego networks, hub queries whose
 ego network exceeds one workgroup's table, and the edge cases."""
 
+from math import comb
+
 import numpy as np
 import pytest
 import torch
@@ -136,3 +138,38 @@ def test_partial_and_edge_cases(nd, ctx):
     gp = make(nd, ctx, path)
     est, sw = gp.ego_estimate("truss", np.arange(49))
     assert (est.cpu().numpy() == 0).all()
+
+
+# Many small queries at once (P(q) of at most 64, 8192 of them and more) run on
+# tables of their own: the same estimates as in calls with few queries, and the
+# oracle's for some.  Lists of lengths around the limit in every kind.
+@pytest.mark.parametrize("kind,n,p", [("core", 1400, 0.045), ("truss", 300, 0.32),
+                                      ("nucleus34", 110, 0.58), ("nucleus13", 1000, 0.04),
+                                      ("nucleus24", 300, 0.197)])
+def test_many_small_queries(nd, ctx, kind, n, p):
+    rng = np.random.default_rng(31)
+    i, j = np.triu_indices(n, 1)
+    keep = rng.random(i.size) < p
+    raw = RawGraph(n, i[keep].astype(np.int32), j[keep].astype(np.int32), "er")
+    g = nd.Graph.from_edges(ctx, n, torch.from_numpy(raw.src), torch.from_numpy(raw.dst))
+    nr = g.sizes(kind)[0]
+    r, s = nd.RS[kind]
+    members = 1 + (comb(s, r) - 1) * g.sdegree(kind).cpu().numpy().astype(np.int64)
+    assert (members <= 64).any() and (members > 64).any()
+    few, few_sw = g.ego_estimate(kind, np.arange(min(nr, 3000)))
+    reps = 20000 // min(nr, 3000) + 8
+    qs = np.tile(np.arange(min(nr, 3000)), reps)
+    qs = qs[rng.permutation(qs.size)]
+    assert (members[qs] <= 64).sum() >= 8192
+    for qq in (qs, qs[members[qs] <= 64]):
+        est, _ = g.ego_estimate(kind, qq)
+        assert np.array_equal(est.cpu().numpy(), few.cpu().numpy()[qq])
+    og = oracle.Graph.from_raw(raw)
+    some = rng.choice(min(nr, 3000), 40, replace=False)
+    want, _ = og.ego_estimate(r, s, some)
+    assert np.array_equal(few.cpu().numpy()[some], want)
+    bad = qs.copy()
+    bad[-1] = nr
+    with pytest.raises(nd.NdError) as e:
+        g.ego_estimate(kind, bad)
+    assert e.value.name == "invalid"
