@@ -45,6 +45,9 @@ struct Err {
     }                                                                       \
   } while (0)
 
+// An error that was dealt with leaves no message behind.
+inline void clear_error() { set_error("%s", ""); }
+
 #define ND_REQUIRE(cond, code, ...) \
   do {                              \
     if (!(cond)) {                  \

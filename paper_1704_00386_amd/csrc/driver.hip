@@ -526,27 +526,6 @@ nd_status decompose_impl(nd_graph *g, nd_kind kind, const nd_opts *opts_in,
     tau1.reset(al, L.tau);
     b.tau[1] = tau1.p;
   }
-  if (flags)
-    for (int i = 0; i < 2; i++) {
-      sums[i].reset(al, L.sums);
-      b.act_sum[i] = sums[i].p;
-    }
-  if (L.slack) {
-    try {
-      slack.reset(al, L.slack);
-      for (int i = 0; i < 2; i++) lost[i].reset(al, L.lost);
-      b.slack = slack.p;
-      for (int i = 0; i < 2; i++) b.act[i] = b.lost[i] = lost[i].p;
-    } catch (const Err &) {  // short of memory: flags alone take less
-      slack.free();
-      for (int i = 0; i < 2; i++) lost[i].free();
-    }
-  }
-  if (flags && !b.slack)
-    for (int i = 0; i < 2; i++) {
-      act[i].reset(al, L.flags);
-      b.act[i] = act[i].p;
-    }
   b.ring = (SweepStats *)ring.p;
   b.ring_len = kStatsRing;
   if (L.snap) {
@@ -557,6 +536,30 @@ nd_status decompose_impl(nd_graph *g, nd_kind kind, const nd_opts *opts_in,
     stage.reset(al, L.stage);
     b.stage = (int32_t *)stage.p;
   }
+  if (flags)
+    for (int i = 0; i < 2; i++) {
+      sums[i].reset(al, L.sums);
+      b.act_sum[i] = sums[i].p;
+    }
+  // last what may give way to the flags, which take less memory
+  if (L.slack) {
+    try {
+      slack.reset(al, L.slack);
+      for (int i = 0; i < 2; i++) lost[i].reset(al, L.lost);
+      b.slack = slack.p;
+      for (int i = 0; i < 2; i++) b.act[i] = b.lost[i] = lost[i].p;
+    } catch (const Err &e) {
+      if (e.code != ND_ERR_OOM) throw;
+      clear_error();
+      slack.free();
+      for (int i = 0; i < 2; i++) lost[i].free();
+    }
+  }
+  if (flags && !b.slack)
+    for (int i = 0; i < 2; i++) {
+      act[i].reset(al, L.flags);
+      b.act[i] = act[i].p;
+    }
   return sweep_loop(g, ks, opts, kappa, on_device, s, res, r, fixed_set, b);
 }
 
