@@ -82,9 +82,10 @@ class Batch {
  public:
   static constexpr int kGraphEpochs = 8;  // epochs per HIP graph
 
-  // Work is issued on a private stream ordered after `caller`.
+  // Work is issued on a private stream ordered after `caller`.  `support`:
+  // members may count support, where that has room (see add).
   Batch(nd_ctx *ctx, nd_kind kind, nd_mode mode, bool tau16, bool frontier,
-        hipStream_t caller);
+        bool support, hipStream_t caller);
   ~Batch();
   Batch(const Batch &) = delete;
   Batch &operator=(const Batch &) = delete;
@@ -135,6 +136,7 @@ class Batch {
   nd_mode mode_;
   bool tau16_;
   bool frontier_;
+  bool support_;
   hipStream_t s_ = nullptr;
   BatchConfig cfg_;
   std::vector<std::unique_ptr<Member>> members_;

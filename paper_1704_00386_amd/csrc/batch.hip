@@ -151,8 +151,9 @@ int work_bucket(int64_t P) {
 // ------------------------------------------------------------ Batch
 
 Batch::Batch(nd_ctx *ctx, nd_kind kind, nd_mode mode, bool tau16,
-             bool frontier, hipStream_t caller)
-    : ctx_(ctx), kind_(kind), mode_(mode), tau16_(tau16), frontier_(frontier) {
+             bool frontier, bool support, hipStream_t caller)
+    : ctx_(ctx), kind_(kind), mode_(mode), tau16_(tau16), frontier_(frontier),
+      support_(support) {
   cfg_ = default_config(ctx);
   if (const char *v = getenv("ND_BATCH_NO_GRAPH")) use_graph = v[0] != '1';
   ND_HIP(hipStreamCreateWithFlags(&s_, hipStreamNonBlocking));
@@ -230,13 +231,21 @@ Member *Batch::add(nd_graph *g, int32_t max_iters, void *user) {
     m->zero_bytes = at - z;
     return at;
   };
-  bool support = frontier_ && counts_support(ks);
+  // Counting support takes more memory than flags do: under a budget at most a
+  // quarter of what is left, so that outputs and other work on the context keep
+  // room.
+  const Allocator &al = ctx_->alloc;
+  const size_t live = al.live_bytes();
+  bool support = support_ && frontier_ && counts_support(ks) &&
+                 (al.budget() == 0 ||
+                  (live < al.budget() && (size_t)place(true) <= (al.budget() - live) / 4));
   if (support) {
     try {
       m->mem.reset(ctx_->alloc, place(true));
-    } catch (const Err &) {  // short of memory: flags alone take less
+    } catch (const Err &e) {
+      if (e.code != ND_ERR_OOM) throw;
+      clear_error();
       support = false;
-      m->mem.p = nullptr;
     }
   }
   if (!support) m->mem.reset(ctx_->alloc, place(false));
@@ -806,27 +815,13 @@ constexpr int64_t kOverlapWork = (int64_t)1 << 24;
 // sweeps are long enough, kOverlapWork): each joins the batch of its tau
 // width (16 or 32 bits; two batches, on streams of their own, when the
 // graphs need both) as soon as it is ready.
-nd_status batch_decompose(nd_ctx *ctx, int32_t count, nd_graph *const *graphs,
-                          nd_kind kind, const nd_opts *opts_in,
-                          int32_t *const *kappas, int on_device, hipStream_t s,
-                          nd_result *res) {
-  nd_opts opts;
-  nd_opts_init(&opts);
-  if (opts_in) opts = *opts_in;
-  ND_REQUIRE(opts.mode == ND_SND || opts.mode == ND_AND, ND_ERR_INVALID,
-             "unknown mode");
-  ND_REQUIRE(opts.on_iter == nullptr && opts.stop_active_ratio == 0,
-             ND_ERR_UNSUPPORTED,
-             "batched decomposition supports mode, max_iters and use_frontier");
-  std::vector<bool> was(count);
-  for (int i = 0; i < count; i++) {
-    ND_REQUIRE(graphs[i] && graphs[i]->ctx == ctx, ND_ERR_INVALID,
-               "graph %d is NULL or from another context", i);
-    was[i] = graphs[i]->ks[kind].ready;
-  }
-  for (int i = 0; i < count; i++)  // outputs of graphs already prepared
-    ND_REQUIRE(!was[i] || graphs[i]->ks[kind].nr == 0 || (kappas && kappas[i]),
-               ND_ERR_INVALID, "kappas[%d] is NULL", i);
+static nd_status batch_attempt(nd_ctx *ctx, int32_t count, nd_graph *const *graphs,
+                               nd_kind kind, const nd_opts &opts,
+                               int32_t *const *kappas, int on_device, hipStream_t s,
+                               nd_result *res, const std::vector<bool> &ready0,
+                               bool support) {
+  std::vector<bool> was(count);  // prepared by now
+  for (int i = 0; i < count; i++) was[i] = graphs[i]->ks[kind].ready;
   std::unique_ptr<Batch> batches[2];  // 16-bit, 32-bit tau
   bool tuned[2] = {false, false};
   std::map<nd_graph *, Member *> member;
@@ -845,7 +840,7 @@ nd_status batch_decompose(nd_ctx *ctx, int32_t count, nd_graph *const *graphs,
     const int w = g->ks[kind].tau16 ? 0 : 1;
     if (!batches[w])
       batches[w] = std::make_unique<Batch>(ctx, kind, opts.mode, w == 0,
-                                           opts.use_frontier != 0, s);
+                                           opts.use_frontier != 0, support, s);
     if (ready) ND_HIP(hipStreamWaitEvent(batches[w]->stream(), ready, 0));
     member[g] = batches[w]->add(g, opts.max_iters, nullptr);
   };
@@ -938,7 +933,7 @@ nd_status batch_decompose(nd_ctx *ctx, int32_t count, nd_graph *const *graphs,
       r.n_rcliques = ks.nr;
       r.n_incidence = ks.P;
       r.updates = ks.bin_lo[kBinZero] * m.sweeps;
-      r.ms_prep = was[i] ? 0.0 : ks.ms_prep;
+      r.ms_prep = ready0[i] ? 0.0 : ks.ms_prep;
       r.ms_iterate = ms_total;  // shared by the whole batch
       r.max_sdegree = ks.max_ds;
       r.tau_bytes = bt.tau16() ? 2 : 4;
@@ -956,6 +951,46 @@ nd_status batch_decompose(nd_ctx *ctx, int32_t count, nd_graph *const *graphs,
     }
   if (out != ND_OK) set_error("a graph of the batch stopped without converging");
   return out;
+}
+
+nd_status batch_decompose(nd_ctx *ctx, int32_t count, nd_graph *const *graphs,
+                          nd_kind kind, const nd_opts *opts_in,
+                          int32_t *const *kappas, int on_device, hipStream_t s,
+                          nd_result *res) {
+  nd_opts opts;
+  nd_opts_init(&opts);
+  if (opts_in) opts = *opts_in;
+  ND_REQUIRE(opts.mode == ND_SND || opts.mode == ND_AND, ND_ERR_INVALID,
+             "unknown mode");
+  ND_REQUIRE(opts.on_iter == nullptr && opts.stop_active_ratio == 0,
+             ND_ERR_UNSUPPORTED,
+             "batched decomposition supports mode, max_iters and use_frontier");
+  std::vector<bool> ready0(count);
+  for (int i = 0; i < count; i++) {
+    ND_REQUIRE(graphs[i] && graphs[i]->ctx == ctx, ND_ERR_INVALID,
+               "graph %d is NULL or from another context", i);
+    ready0[i] = graphs[i]->ks[kind].ready;
+  }
+  for (int i = 0; i < count; i++)  // outputs of graphs already prepared
+    ND_REQUIRE(!ready0[i] || graphs[i]->ks[kind].nr == 0 || (kappas && kappas[i]),
+               ND_ERR_INVALID, "kappas[%d] is NULL", i);
+  const KindRS rs = kind_rs(kind);
+  const bool support = opts.use_frontier != 0 && rs.s == rs.r + 1;
+  try {
+    return batch_attempt(ctx, count, graphs, kind, opts, kappas, on_device, s, res,
+                         ready0, support);
+  } catch (const Err &e) {
+    if (e.code != ND_ERR_OOM || !support) throw;
+  }
+  // Whatever fits with flags alone runs: once more without support counting, the
+  // memory of the first attempt given back.
+  clear_error();
+  ND_HIP(hipStreamSynchronize(s));
+  for (int i = 0; i < count; i++)
+    if (!graphs[i]->ks[kind].ready) graphs[i]->ks[kind] = KindState{};
+  ctx->alloc.trim();
+  return batch_attempt(ctx, count, graphs, kind, opts, kappas, on_device, s, res,
+                       ready0, false);
 }
 
 }  // namespace nd

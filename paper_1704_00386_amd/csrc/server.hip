@@ -341,7 +341,7 @@ bool add_ready(nd_server *srv, Request *r) {
     auto &slot = srv->batches[r->cls][r->kind][mi][wi][fi];
     if (!slot)
       slot = std::make_unique<Batch>(srv->ctx, r->kind, r->opts.mode, ks.tau16,
-                                     fi != 0, ws);
+                                     fi != 0, /*support=*/true, ws);
     int running_before = 0;
     for (Member *m : slot->live()) running_before += m->sweeps > 0 ? 1 : 0;
     r->info.epoch_joined = slot->epoch();

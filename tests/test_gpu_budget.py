@@ -81,3 +81,31 @@ def test_whatever_holds_flags_runs(nd, host, callback):
     assert kappa is not None, least
     assert np.array_equal(kappa, case.want)
     assert nd._lib.nd_last_error() == b""
+
+
+# A batch of eight such graphs in memory for their flags: early members may
+# count support, later ones must find room all the same.
+@pytest.mark.parametrize("mode", ["snd", "and"])
+def test_batch_whatever_holds_flags_runs(nd, mode):
+    n, count = 1 << 18, 8
+    case = _Case(nd, n)
+
+    def run(budget, frontier):
+        try:
+            ctx = nd.Context(0, hbm_budget_bytes=budget)
+            gs = [case.graph(ctx) for _ in range(count)]
+        except nd.NdError as e:
+            assert e.name == "oom"
+            return None
+        try:
+            return nd.batch_decompose(ctx, gs, "core", mode, use_frontier=frontier)[0]
+        except nd.NdError as e:
+            assert e.name == "oom"
+            return None
+
+    least = _smallest(lambda b: run(b, False) is not None, 0, 200 << 20)
+    # flags: a byte per vertex twice, a stamp per 64 of them, in whole 256 bytes
+    flags = count * 2 * (n + n // 64 + 512)
+    kappas = run(least + flags, True)
+    assert kappas is not None, least
+    assert all(np.array_equal(k.cpu().numpy(), case.want) for k in kappas)
