@@ -2018,11 +2018,13 @@ __global__ void k_core_shift(const int64_t *__restrict__ row_off,
 // entries a thread are in flight, and only the gather of inv is random (it
 // bounds the pass: one 4-byte word per 128-byte line, 8 TB/s of lines; 268
 // million entries in 4.2 ms, 5.0 with a wave or four lanes per list).
+// Where memory is too short for the shifts (NULL), each entry finds its own.
 constexpr int kCoreItems = 8;
 
 __global__ __launch_bounds__(256) void k_core_fill(
     const int32_t *__restrict__ col, const int32_t *__restrict__ rowid,
     const int32_t *__restrict__ inv, const int64_t *__restrict__ shift,
+    const int64_t *__restrict__ row_off, const int64_t *__restrict__ off,
     int64_t nnz, int32_t *__restrict__ out) {
   const int64_t p0 = (int64_t)blockIdx.x * 256 * kCoreItems + threadIdx.x;
   int32_t c[kCoreItems], r[kCoreItems];
@@ -2035,7 +2037,10 @@ __global__ __launch_bounds__(256) void k_core_fill(
 #pragma unroll
   for (int k = 0; k < kCoreItems; k++) {
     const int64_t p = p0 + k * 256;
-    if (c[k] >= 0) out[p + shift[r[k]]] = inv[c[k]];
+    if (c[k] >= 0) {
+      const int64_t by = shift ? shift[r[k]] : off[inv[r[k]]] - row_off[r[k]];
+      out[p + by] = inv[c[k]];
+    }
   }
 }
 
@@ -2054,12 +2059,19 @@ void build_incidence_core(nd_graph *g, KindState &ks, hipStream_t s) {
   deg.free();
   ks.inc_ids.reset(al, ks.P);
   if (g->nnz > 0) {
-    DArr<int64_t> shift(al, n);
-    k_core_shift<<<grid_for(n, 256), 256, 0, s>>>(g->row_off.p, ks.inv.p,
-                                                   ks.inc_off.p, n, shift.p);
-    ND_LAUNCHED();
+    DArr<int64_t> shift;
+    try {
+      shift.reset(al, n);
+      k_core_shift<<<grid_for(n, 256), 256, 0, s>>>(g->row_off.p, ks.inv.p,
+                                                     ks.inc_off.p, n, shift.p);
+      ND_LAUNCHED();
+    } catch (const Err &e) {
+      if (e.code != ND_ERR_OOM) throw;
+      clear_error();
+    }
     k_core_fill<<<grid_for(g->nnz, 256 * kCoreItems), 256, 0, s>>>(
-        g->col.p, g->rowid.p, ks.inv.p, shift.p, g->nnz, ks.inc_ids.p);
+        g->col.p, g->rowid.p, ks.inv.p, shift.p, g->row_off.p, ks.inc_off.p, g->nnz,
+        ks.inc_ids.p);
     ND_LAUNCHED();
   }
 }

@@ -68,7 +68,7 @@ struct EgoArgs {
   int32_t *sweeps;         // per query
   uint8_t *big;            // per query: 1 = run it through the fallback
   int32_t *not_converged;  // set when a query stopped at max_iters
-  const int64_t *order;    // queries, heaviest first
+  const int64_t *order;    // queries, heaviest first (NULL: as given)
   int64_t begin, end;      // those of this launch
   unsigned long long *head;  // how many of them have been taken
   int take;                  // so many at a time
@@ -274,7 +274,7 @@ __global__ __launch_bounds__(NT, NT == kWave ? 4 : 1) void k_ego(EgoArgs a) {
     }
     left--;
     if (nx >= a.end) return;  // uniform over the block
-    const int64_t qi = a.order[nx];
+    const int64_t qi = a.order ? a.order[nx] : nx;
     const int32_t R0 = a.inv[a.queries[qi]];
     const int64_t b0 = a.inc_off[R0];
     const int64_t d0 = a.inc_off[R0 + 1] - b0;
@@ -452,11 +452,19 @@ nd_status ego_estimate(nd_graph *g, nd_kind kind, const int32_t *queries,
   a.sweeps = dsw.p;
   a.big = big.p;
   a.not_converged = flags.p + 1;
-  DArr<int64_t> order(al, count);
   DArr<EgoDeal> deal(al, 1);
+  DArr<int64_t> order;
+  try {
+    order.reset(al, count);
+  } catch (const Err &e) {  // short of memory: in the order given
+    if (e.code != ND_ERR_OOM) throw;
+    clear_error();
+  }
   a.order = order.p;
-  const bool many = count >= kEgoManySmall;
-  if (many) {
+  const bool many = count >= kEgoManySmall && order.p != nullptr;
+  if (order.p == nullptr) {
+    fill_u64((uint64_t *)deal.p, 0, sizeof(EgoDeal) / 8, s);
+  } else if (many) {
     fill_u64((uint64_t *)deal.p, 0, sizeof(EgoDeal) / 8, s);
     const unsigned grid = (unsigned)std::min<int64_t>(grid_for(count, 1024), g->ctx->num_cu);
     k_ego_count<<<grid, 1024, 0, s>>>(a, ks.nr, deal.p);

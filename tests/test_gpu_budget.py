@@ -8,7 +8,7 @@ import pytest
 import torch
 
 import oracle
-from synth import chung_lu
+from synth import RawGraph, chung_lu
 
 pytestmark = pytest.mark.gpu
 
@@ -109,3 +109,34 @@ def test_batch_whatever_holds_flags_runs(nd, mode):
     kappas = run(least + flags, True)
     assert kappas is not None, least
     assert all(np.array_equal(k.cpu().numpy(), case.want) for k in kappas)
+
+
+# Preparing a k-core takes its arrays and nothing besides that grows with the
+# graph (here with room for the 4 bytes a vertex that nd_incidence takes); ego
+# estimates 13 bytes a query (id, estimate, sweeps, a mark).
+@pytest.mark.parametrize("queries", [0, 400000])
+def test_core_in_its_own_arrays(nd, queries):
+    n, m = 1 << 17, 1 << 20
+    rng = np.random.default_rng(3)
+    raw = RawGraph(n, rng.integers(0, n, m).astype(np.int32),
+                   rng.integers(0, n, m).astype(np.int32), "random")
+    off, col = nd.Graph.from_edges(nd.Context(0), n, torch.from_numpy(raw.src),
+                                   torch.from_numpy(raw.dst)).csr()
+    nnz = col.numel()
+    arrays = 8 * (n + 1) + 8 * nnz + 12 * n + 8 * (n + 1) + 4 * nnz
+    ctx = nd.Context(0, hbm_budget_bytes=arrays + (13 * queries or 4 * n) + (192 << 10))
+    g = nd.Graph.from_csr(ctx, n, off, col)
+    g.prepare("core")
+    goff, gids = nd.Graph.incidence(g, "core") if not queries else (None, None)
+    if queries:
+        qs = rng.integers(0, n, queries)
+        est, _ = g.ego_estimate("core", qs)
+        some = rng.choice(queries, 200, replace=False)
+        want, _ = oracle.Graph.from_raw(raw).ego_estimate(1, 2, qs[some])
+        assert np.array_equal(est.cpu().numpy()[some], want)
+    else:
+        row = np.repeat(np.arange(n), np.diff(goff.cpu().numpy()))
+        order = np.lexsort((gids.cpu().numpy()[:, 0], row))
+        assert np.array_equal(goff.cpu().numpy(), off.cpu().numpy())
+        assert np.array_equal(gids.cpu().numpy()[order, 0], col.cpu().numpy())
+    assert nd._lib.nd_last_error() == b""
