@@ -92,3 +92,35 @@ def test_n34_without_kept_rows(nd, ctx, name, make, monkeypatch):
             assert np.array_equal(kappa.cpu().numpy(), want), (env, mode)
         g.close()
     assert torch.equal(canon[0], canon[1])
+
+
+# k-truss of 2^20 edges and more: numbered by the oriented lists where a quarter
+# of the edges or more lie in triangles, by id otherwise.
+@pytest.mark.parametrize("cliques,tail", [(0, 1_100_000), (5000, 1_000_000),
+                                          (6000, 800_000), (24000, 0)])
+def test_truss_numbering_of_many_edges(cliques, tail):
+    import torch
+    import paper_1704_00386_amd as nd
+    # cliques of 10 (45 edges each), then a path of `tail` edges
+    i, j = np.triu_indices(10, 1)
+    base = 10 * np.arange(cliques)[:, None]
+    src = np.concatenate([(base + i).ravel(), 10 * cliques + np.arange(tail)])
+    dst = np.concatenate([(base + j).ravel(), 10 * cliques + np.arange(tail) + 1])
+    # edges between cliques, in no triangle
+    cross = np.arange(max(cliques - 1, 0))
+    src, dst = np.concatenate([src, 10 * cross]), np.concatenate([dst, 10 * cross + 15])
+    n = 10 * cliques + tail + 1
+    perm = np.random.default_rng(cliques).permutation(n)
+    g = nd.Graph.from_edges(nd.Context(0), n, torch.from_numpy(perm[src].astype(np.int32)),
+                            torch.from_numpy(perm[dst].astype(np.int32)))
+    ev = g.rcliques("truss").cpu().numpy()
+    assert len(ev) >= 1 << 20
+    back = np.empty(n, np.int64)
+    back[perm] = np.arange(n)
+    a, b = back[ev[:, 0]], back[ev[:, 1]]
+    want = np.where((a < 10 * cliques) & (a // 10 == b // 10), 8, 0).astype(np.int32)
+    assert np.array_equal(g.sdegree("truss").cpu().numpy(), want)
+    for mode in ("snd", "and"):
+        kappa, _ = g.decompose("truss", mode, use_frontier=True)
+        assert np.array_equal(kappa.cpu().numpy(), want)
+    assert np.array_equal(g.update("truss", torch.from_numpy(want)).cpu().numpy(), want)
