@@ -2018,9 +2018,10 @@ __global__ void k_core_shift(const int64_t *__restrict__ row_off,
 // entries a thread are in flight, and only the gather of inv is random (it
 // bounds the pass: one 4-byte word per 128-byte line, 8 TB/s of lines; 268
 // million entries in 4.2 ms, 5.0 with a wave or four lanes per list).
-// Where memory is too short for the shifts (NULL), each entry finds its own.
+// SHIFT false: without room for the shifts, each entry finds its own.
 constexpr int kCoreItems = 8;
 
+template <bool SHIFT>
 __global__ __launch_bounds__(256) void k_core_fill(
     const int32_t *__restrict__ col, const int32_t *__restrict__ rowid,
     const int32_t *__restrict__ inv, const int64_t *__restrict__ shift,
@@ -2038,7 +2039,7 @@ __global__ __launch_bounds__(256) void k_core_fill(
   for (int k = 0; k < kCoreItems; k++) {
     const int64_t p = p0 + k * 256;
     if (c[k] >= 0) {
-      const int64_t by = shift ? shift[r[k]] : off[inv[r[k]]] - row_off[r[k]];
+      const int64_t by = SHIFT ? shift[r[k]] : off[inv[r[k]]] - row_off[r[k]];
       out[p + by] = inv[c[k]];
     }
   }
@@ -2069,7 +2070,8 @@ void build_incidence_core(nd_graph *g, KindState &ks, hipStream_t s) {
       if (e.code != ND_ERR_OOM) throw;
       clear_error();
     }
-    k_core_fill<<<grid_for(g->nnz, 256 * kCoreItems), 256, 0, s>>>(
+    auto fill = shift.p ? k_core_fill<true> : k_core_fill<false>;
+    fill<<<grid_for(g->nnz, 256 * kCoreItems), 256, 0, s>>>(
         g->col.p, g->rowid.p, ks.inv.p, shift.p, g->row_off.p, ks.inc_off.p, g->nnz,
         ks.inc_ids.p);
     ND_LAUNCHED();

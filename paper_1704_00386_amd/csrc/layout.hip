@@ -52,13 +52,15 @@ struct Order {
   const int32_t *order;             // NULL: id order
   const unsigned long long *swept;  // not NULL: so many have d_s > 0 ...
   unsigned long long least;         // ... and `order` is for as many as this
-  __device__ int32_t at(int64_t i) const {
-    return order && (swept == nullptr || *swept >= least) ? order[i] : (int32_t)i;
+  __device__ Order local() const {
+    return Order{swept == nullptr || *swept >= least ? order : nullptr, nullptr, 0};
   }
+  __device__ int32_t at(int64_t i) const { return order ? order[i] : (int32_t)i; }
 };
 struct DegreeIn {
   const int32_t *cnt;
   Order order;
+  __device__ DegreeIn local() const { return DegreeIn{cnt, order.local()}; }
   __device__ int load(int64_t i, int32_t *most) const {
     const int32_t d = cnt[order.at(i)];
     *most = max(*most, d);
@@ -69,6 +71,7 @@ struct LayoutOut {
   const int32_t *cnt;
   Order order;
   int32_t *perm, *inv, *ds;
+  __device__ LayoutOut local() const { return LayoutOut{cnt, order.local(), perm, inv, ds}; }
   __device__ void put(int64_t i, int64_t place) const {
     const int32_t r = order.at(i);
     perm[place] = r;
@@ -81,9 +84,13 @@ __global__ __launch_bounds__(256) void k_count_swept(
     const int32_t *__restrict__ cnt, int64_t n, unsigned long long *__restrict__ out) {
   __shared__ int32_t ws[4];
   int32_t c = 0;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * 256)
-    c += cnt[i] > 0;
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int4 *v = reinterpret_cast<const int4 *>(cnt);  // 256-byte aligned
+  for (int64_t i = t; i < n / 4; i += (int64_t)gridDim.x * 256) {
+    const int4 x = v[i];
+    c += (x.x > 0) + (x.y > 0) + (x.z > 0) + (x.w > 0);
+  }
+  if (t < n % 4) c += cnt[n / 4 * 4 + t] > 0;
 #pragma unroll
   for (int o = kWave / 2; o > 0; o >>= 1) c += __shfl_xor(c, o, kWave);
   if (lane_id() == 0) ws[threadIdx.x / kWave] = c;

@@ -65,11 +65,13 @@ __device__ __forceinline__ void wave_ranks(const int (&bin)[kPartItems],
 }
 
 // In: load(i, &most) returns item i's bin in [0, NB) and raises most to the
-// item's value.
+// item's value.  In and Out: local() the same with what it reads once a thread
+// already read.
 template <int NB, typename In>
 __global__ __launch_bounds__(kPartThreads) void k_part_count(
-    In in, int64_t n, int64_t nb, int32_t *__restrict__ count,
+    In in_, int64_t n, int64_t nb, int32_t *__restrict__ count,
     int32_t *__restrict__ block_most) {
+  const In in = in_.local();
   __shared__ int32_t c[kPartThreads / kWave][kMaxBins];
   __shared__ int32_t cm[kPartThreads / kWave];
   const int w = threadIdx.x / kWave, lane = lane_id(), t = threadIdx.x;
@@ -96,9 +98,11 @@ __global__ __launch_bounds__(kPartThreads) void k_part_count(
 // counts for itself).  Workgroup 0 also writes the head.
 template <int NB, int NT, typename In, typename Out>
 __global__ __launch_bounds__(NT) void k_part_place(
-    In in, Out out, int64_t n, int64_t nb, const int32_t *__restrict__ count,
+    In in_, Out out_, int64_t n, int64_t nb, const int32_t *__restrict__ count,
     const int64_t *__restrict__ off, const int32_t *__restrict__ block_most,
     Head *__restrict__ head) {
+  const In in = in_.local();
+  const Out out = out_.local();
   constexpr int kWaves = NT / kWave;
   __shared__ int32_t c[kWaves][kMaxBins];
   __shared__ int32_t cm[kWaves];

@@ -374,10 +374,12 @@ __global__ void k_fill_u64(uint64_t *p, uint64_t v, int64_t n) {
 // Items grouped by a byte each.
 struct ByteIn {
   const uint8_t *bin;
+  __device__ ByteIn local() const { return *this; }
   __device__ int load(int64_t i, int32_t *) const { return bin[i]; }
 };
 struct ItemOut {
   int32_t *items;
+  __device__ ItemOut local() const { return *this; }
   __device__ void put(int64_t i, int64_t place) const { items[place] = (int32_t)i; }
 };
 
