@@ -686,7 +686,8 @@ def stream_leg(nd, ctx, count, seed=5, n_lo=1000, n_hi=200000, serve=True,
         "updates": updates,
         "aggregate_algorithmic_GBs": {
             "one_per_launch": alg_bytes / t_solo / 1e9,
-            "batched": alg_bytes / t_batch / 1e9,
+            # (batches and the server notify from other sweeps on and do not
+            # count their evaluations)
             "what": "the evaluated h-index updates' algorithmic bytes (id stream, "
                     "tau gathers, offsets and own tau), each evaluated r-clique at "
                     "its graph's mean list length, over the path's wall time "
@@ -730,7 +731,6 @@ def stream_leg(nd, ctx, count, seed=5, n_lo=1000, n_hi=200000, serve=True,
         del got
         srv.close()
         del sctx
-        out["aggregate_algorithmic_GBs"]["served"] = alg_bytes / t_srv / 1e9
         out["served"] = {"arrival_rate_per_s": rate, "graphs_per_s": count / t_srv,
                          "p50_ms": float(np.percentile(lats, 50)),
                          "p99_ms": float(np.percentile(lats, 99)),

@@ -328,3 +328,12 @@ def test_server_cancel_and_busy(nd, ctx):
         srv.wait(ts[2])
     assert e.value.name == "cancelled"
     srv.close()
+
+
+def test_stream_figures_count_their_own_path(nd, ctx):
+    """bench.py's request stream: bytes only for the path whose evaluations
+    were counted (batches and the server run others)."""
+    import bench
+    out = bench.stream_leg(nd, ctx, 4, n_lo=1000, n_hi=4000)
+    assert set(out["aggregate_algorithmic_GBs"]) == {"one_per_launch", "what"}
+    assert out["aggregate_algorithmic_GBs"]["one_per_launch"] > 0
