@@ -68,3 +68,56 @@ def test_layout_at_partition_edges(n):
     assert np.array_equal(gids[order], col)
     _, res = g.decompose("core", max_iters=1, allow_not_converged=True)
     assert res["max_sdegree"] == int(np.diff(off).max())
+
+
+def _random_csr(n, m, seed):
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    return [torch.randint(0, n, (m,), generator=gen, device="cuda", dtype=torch.int32)
+            for _ in range(2)]
+
+
+def _torch_csr(n, src, dst):
+    import torch
+    s, d = src.long(), dst.long()
+    keep = s != d
+    key = torch.unique(torch.cat([s[keep] * n + d[keep], d[keep] * n + s[keep]]))
+    off = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+    torch.cumsum(torch.bincount(key // n, minlength=n), 0, out=off[1:])
+    return off, (key % n).int()
+
+
+# The scan of n S-degrees and the partition of n vertices: one workgroup's two
+# tiles (32768), the partition's switch to scanned counts (64 tiles of 4096), and
+# the tile count (2048 of 4096) above which the scan's tile sums are scanned first.
+@pytest.mark.parametrize("n", [32767, 32768, 32769, 64 * 4096, 64 * 4096 + 1,
+                               2048 * 4096, 2048 * 4096 + 1])
+def test_scan_and_partition_edges(n):
+    import torch
+    nd = _nd()
+    src, dst = _random_csr(n, 3 * n // 2, n)
+    g = nd.Graph.from_edges(nd.Context(0), n, src, dst)
+    off, col = _torch_csr(n, src, dst)
+    goff, gcol = g.csr()
+    assert torch.equal(goff.cuda(), off) and torch.equal(gcol.cuda(), col)
+    # offsets of the lists in the caller's order, and the lists themselves
+    ioff, ids = g.incidence("core")
+    assert torch.equal(ioff.cuda(), off)
+    row = torch.repeat_interleave(torch.arange(n, device="cuda"), off.diff())
+    assert torch.equal(torch.sort(row * n + ids.cuda().flatten().long()).values,
+                       row * n + col)
+
+
+# The sort of 2m keys: one tile of 4096, and 64 tiles, above which its digit
+# counts are scanned rather than added up by every workgroup; and the tiles of 2048
+# keys whose counts place the distinct ones.
+@pytest.mark.parametrize("m", [1023, 1024, 1025, 2048 * 3, 32 * 4096 - 1, 32 * 4096,
+                               32 * 4096 + 1])
+def test_sort_edges(m):
+    import torch
+    nd = _nd()
+    n = max(2, m // 5)
+    src, dst = _random_csr(n, m, m)
+    goff, gcol = nd.Graph.from_edges(nd.Context(0), n, src, dst).csr()
+    off, col = _torch_csr(n, src, dst)
+    assert torch.equal(goff.cuda(), off) and torch.equal(gcol.cuda(), col)
