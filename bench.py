@@ -193,7 +193,7 @@ def summarize_profiles(trace_csv: str, fetch_csv: str, write_csv: str) -> None:
              "The run holds a 1 GiB device copy, one warm-up and two timed steps (build + prepare +",
              "SND with the notification frontier until exact), the full-sweep roofline leg (4 SND",
              "sweeps recomputing every r-clique), AND with the frontier, and the ceiling kernels.",
-             "`k_sweep_small<k, tau type, AND, frontier, lists above 256>` sweeps every bin in one",
+             "`k_sweep_bins<k, tau type, AND, frontier, lists above 256>` sweeps every bin in one",
              "launch; `<3, unsigned char, false, false, false>` is a full sweep that notifies nobody",
              "(tau in 8 bits: every d_s of this workload is below 256), in the SND steps too.", "",
              "| % | calls | total ms | avg us | kernel |", "|---:|---:|---:|---:|---|"]
@@ -984,7 +984,7 @@ def main():
                      "frac": roof["achieved_GBs"] / HBM_PEAK_GBS,
                      "traffic": traffic,
                      "kernel": "full sweep: one application of U to every "
-                               "r-clique with d_s > 0 (k_sweep_small<3, "
+                               "r-clique with d_s > 0 (k_sweep_bins<3, "
                                f"{TAU_CTYPE[res['tau_bytes']]}>)",
                      "bytes_per_launch": roof["bytes_per_sweep"],
                      "avg_launch_ms": roof["avg_sweep_ms"],

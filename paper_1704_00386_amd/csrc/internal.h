@@ -127,18 +127,18 @@ namespace nd {
 
 // ---------------------------------------------------------- sweep bins
 
-// r-cliques are numbered internally by sweep bin, ascending id within a bin,
-// so every sweep bin is a contiguous range of internal ids, r-cliques that
+// r-cliques are numbered internally by sweep bin, within a bin by id (k-truss:
+// see build_layout), so every sweep bin is a contiguous range of internal ids, r-cliques that
 // share vertices stay close together (their gathers hit nearby cache lines),
 // and zero-degree r-cliques (never swept) sit at the end.  Bins in internal
 // order, with their d_s ranges:
 enum SweepBin : int {
-  // (the one-graph sweeps give 1025 and up a workgroup, 257..1024 a wave with
-  // its values in LDS; the lanes below are the batches')
   kBinBlock = 0,  // d_s >= 2048:  one workgroup per r-clique, LDS histogram
-  kBinWave,       // 1025..2047:   one wave, 32 values per lane in registers
-  kBinWave16,     // 513..1024:    one wave, 16 values per lane
-  kBinWave8,      // 257..512:     one wave, 8 values per lane
+  kBinWave,       // 1025..2047:   the same; where it fills the GPU, a wave with
+                  //               its values in registers (swept_apart) or, in
+                  //               a batch, in LDS
+  kBinWave16,     // 513..1024:    one wave, values in LDS (or registers, the same)
+  kBinWave8,      // 257..512:     one wave, values in LDS
   kBinG64,        // 65..256:      one wave, 4 values per lane
   kBinG16,        // 17..64:       16 lanes
   kBinG4,         // 5..16:        4 lanes

@@ -27,11 +27,12 @@
 //                  a full sweep gathers each run of r-cliques flat first
 //                  (one lane per incidence entry, minima to LDS), then
 //                  computes H from LDS (sweep_flat)
-//   257..1024      one wave per r-clique, 8 / 16 rho values per lane
-//                  (257..512 / 513..1024: fewer registers, more waves in
-//                  flight for the shorter lists)
+//   257..1024      one wave per r-clique, its rho values in LDS (update_wave)
 //   >= 1025        one 256-thread workgroup per r-clique, LDS histogram of
 //                  the values below the cap (update_hub)
+//                  full sweeps of 513..2047 hold their values in registers, in
+//                  launches of their own, where such lists fill the GPU
+//                  (swept_apart)
 // SND reads tau_t and writes tau_{t+1} (double buffer, race free, so every
 // iterate is deterministic).  AND reads and writes one array in place with
 // relaxed workgroup-scope atomics: a value read may predate another
@@ -51,11 +52,6 @@ void sweep_kind(const KindState &ks, const SweepArgs &a, bool and_mode,
 namespace {
 
 using namespace dev;
-
-// The previous sweep's changed count (1 for the first sweep: not converged).
-__device__ __forceinline__ unsigned long long prev_changed(const SweepArgs &a) {
-  return a.prev != nullptr ? changed_sum(a.prev) : 1ull;
-}
 
 template <typename T>
 __global__ void k_zero_range(T *__restrict__ tau, int64_t lo, int64_t hi) {

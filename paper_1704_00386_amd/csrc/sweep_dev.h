@@ -103,25 +103,6 @@ __device__ __forceinline__ int32_t gather_rho_arg(const int32_t *__restrict__ id
   return r;
 }
 
-template <int G>
-__device__ __forceinline__ int subgroup_sum(int x) {
-#pragma unroll
-  for (int off = G / 2; off > 0; off >>= 1) x += __shfl_xor(x, off, G);
-  return x;
-}
-
-// Add this wave's changed / recomputed r-cliques to the sweep's counters
-// (one part per workgroup-and-wave hash, see SweepStats).
-__device__ __forceinline__ void stat_add(SweepStats *st, bool changed,
-                                         bool evald) {
-  const uint64_t mc = ballot(changed), me = ballot(evald);
-  if (lane_id() == 0 && (mc | me)) {
-    StatPart &p = st->part[(blockIdx.x + threadIdx.x / kWave) % kStatParts];
-    if (mc) atomicAdd(&p.changed, (unsigned long long)__popcll(mc));
-    if (me) atomicAdd(&p.evaluated, (unsigned long long)__popcll(me));
-  }
-}
-
 // Add wave-wide totals (the same on every lane, summed from ballots) to the
 // sweep's counters: one atomic per wave and counter.
 __device__ __forceinline__ void stat_add_counts(SweepStats *st,
@@ -142,6 +123,11 @@ __device__ __forceinline__ unsigned long long changed_sum(const SweepStats *st) 
 #pragma unroll
   for (int q = 0; q < kStatParts; q++) v += st->part[q].changed;
   return v;
+}
+
+// The previous sweep's changed count (1 for the first sweep: not converged).
+__device__ __forceinline__ unsigned long long prev_changed(const SweepArgs &a) {
+  return a.prev != nullptr ? changed_sum(a.prev) : 1ull;
 }
 
 // How many lanes of this lane's G-lane subgroup have p set: one wave ballot
@@ -386,33 +372,6 @@ __device__ __forceinline__ void notify_kept(const int32_t *__restrict__ ids,
   }
 }
 
-// The same test for lanes holding many values (no argmin mask kept): only the
-// slots with rho in (h, told] read their members' tau again (AND: a member
-// that fell meanwhile flags itself).
-template <int K, int G, int M, typename T, bool AND>
-__device__ __forceinline__ void notify_slots(const int32_t *__restrict__ ids,
-                                             int64_t b, int64_t d, int sl,
-                                             const int32_t *rho, int32_t told,
-                                             int32_t h, const T *tau,
-                                             uint8_t *act_next,
-                                             uint8_t stamp_next,
-                                             uint8_t *sum_next,
-                                             const Support &sp) {
-#pragma unroll
-  for (int m = 0; m < M; m++) {
-    const int64_t j = sl + (int64_t)m * G;
-    if (j < d && h < rho[m] && rho[m] <= told) {
-      const int32_t *q = ids + K * (b + j);
-#pragma unroll
-      for (int x = 0; x < K; x++) {
-        const int32_t r = q[x];
-        if (K == 1 || load_tau<T, AND>(tau_at(tau, r)) == rho[m])
-          mark(r, act_next, stamp_next, sum_next, sp);
-      }
-    }
-  }
-}
-
 // Bit position of the t-th set bit (t counted from 0) of m; t < popc(m).
 // Binary lifting: the largest p with popc(m below bit p) <= t is that bit.
 __device__ __forceinline__ int nth_set_bit(uint64_t m, int t) {
@@ -453,12 +412,10 @@ __device__ __forceinline__ bool update_list(const int32_t *__restrict__ inc_ids,
   const int sl = lane_id() % G;
   const int32_t *ids = inc_ids + K * b;
   // With the frontier, which members hold each minimum is kept, so that
-  // notifying needs no second gather (notify_kept).  Lanes with more than 4
-  // values re-read only the qualifying s-cliques instead (notify_slots):
-  // keeping masks past the search would cost those kernels occupancy.  (AND
-  // without support counting gathers again, by its own looser test.)
-  constexpr bool kKept = FR && M <= 4;
-  constexpr bool kKeep = kKept && K > 1;
+  // notifying needs no second gather (notify_kept).  (AND without support
+  // counting gathers again, by its own looser test.)
+  static_assert(!FR || M <= 4, "lanes with more values would lose occupancy");
+  constexpr bool kKeep = FR && K > 1;
   constexpr int kMaskWords = kKeep ? (K * M + 31) / 32 : 1;
   int32_t rho[M];
   uint32_t amask[kMaskWords];
@@ -493,12 +450,9 @@ __device__ __forceinline__ bool update_list(const int32_t *__restrict__ inc_ids,
     if (!self)
       notify<K, T, AND>(inc_ids, b, d, sl, G, told, h, tau_in, act_next, next,
                         sum_next, sp);
-    else if (kKept)
+    else
       notify_kept<K, G, M>(inc_ids, b, d, sl, rho, amask, told, h, act_next,
                            next, sum_next, sp);
-    else
-      notify_slots<K, G, M, T, AND>(inc_ids, b, d, sl, rho, told, h, tau_in,
-                                    act_next, next, sum_next, sp);
   }
   return lead && ch;
 }
@@ -564,7 +518,9 @@ __device__ __forceinline__ bool update_wave(const int32_t *__restrict__ inc_ids,
       notify<K, T, AND>(inc_ids, b, d, lane, kWave, told, h, tau_in, act_next,
                         next, sum_next, sp);
     } else {
-      // as notify_slots, two rows of the wave in flight
+      // as notify_kept, from the minima in LDS: only the s-cliques whose minimum
+      // lies in (h, told] read their members' values again (one that fell
+      // meanwhile flags itself), two rows of the wave in flight
       for (int j0 = lane; j0 < d; j0 += 2 * kWave) {
         int32_t rho[2], id[2][K], v[2][K];
 #pragma unroll

@@ -13,17 +13,12 @@ namespace {
 
 using namespace dev;
 
-// The previous sweep's changed count (1 for the first sweep: not converged).
-__device__ __forceinline__ unsigned long long prev_changed(const SweepArgs &a) {
-  return a.prev != nullptr ? changed_sum(a.prev) : 1ull;
-}
-
 // Frontier state of this sweep (uniform over the launch): flags are read
 // only if the previous sweep wrote them (and a.flags_unused is clear); this
 // sweep notifies once the previous one changed few enough r-cliques, and
 // keeps notifying after; the first sweep notifies only with a.notify_first.
 __device__ __forceinline__ void frontier_mode(const SweepArgs &a,
-                                              unsigned long long prev_changed,
+                                              unsigned long long before,
                                               const uint8_t **act,
                                               uint8_t **act_next,
                                               const uint8_t **act_sum,
@@ -35,13 +30,13 @@ __device__ __forceinline__ void frontier_mode(const SweepArgs &a,
       !a.flags_unused && a.prev != nullptr && a.prev->notified;
   const bool notify =
       a.prev != nullptr
-          ? (a.prev->notified || prev_changed <= a.notify_below)
+          ? (a.prev->notified || before <= a.notify_below)
           : a.notify_first != 0;
   *act = flags_valid ? a.act : nullptr;
   *act_next = notify ? a.act_next : nullptr;
   *act_sum = flags_valid ? a.act_sum : nullptr;
   *sum_next = notify ? a.act_sum_next : nullptr;
-  if (a.sums_after != 0 && prev_changed >= a.sums_after)
+  if (a.sums_after != 0 && before >= a.sums_after)
     *sum_next = nullptr;  // k_group_sums writes them
   if (notify) {  // slack is kept from the first notifying sweep on
     sp->slack = a.slack;
@@ -226,7 +221,7 @@ __device__ __forceinline__ void sweep_flat_fr(const SweepArgs &a, int64_t lo,
 
 // One bin [lo, hi) of G lanes per r-clique with M values per lane, swept by
 // the workgroups block .. of nblocks (a launch of its own, or a block range
-// of k_sweep_small).  With `flat` LDS (lists up to 256), a full sweep that
+// of k_sweep_bins).  With `flat` LDS (lists up to 256), a full sweep that
 // notifies nobody runs as sweep_flat and a full SND sweep that notifies as
 // sweep_flat_fr.  Sweeps that read flags find their flagged r-cliques per
 // wave (sweep_sparse): run-based variants of those (marking, or compacting
@@ -256,20 +251,22 @@ __device__ __forceinline__ void sweep_bin(const SweepArgs &a, int64_t lo,
       sweep_flat_fr<K, G, T, AND>(a, lo, hi, block, nblocks, act_next, sum_next,
                                   sp, flat, &n_ch, &n_ev);
   } else if (FR && act != nullptr) {
-    // Sparse, up to 16 entries: a lane per r-clique.  The flagged r-cliques
-    // share few cache lines, so a step is a chain of misses (ids, values,
-    // ids again to notify); with 64 r-cliques per step instead of 16 there are
-    // a quarter of the chains.
-    // The members of a fixed set are many at once and lie anywhere: there a
-    // lane's list is a cache line of its own, and 16 r-cliques a step are quicker
-    // (see k_sweep_set).
-    constexpr bool kLane = G <= 4 && M == 4 && !SET;
-    uint8_t *mbuf = kLane ? flat->mask + threadIdx.x / kWave * kWaveList : nullptr;
-    sweep_sparse<K, kLane ? 1 : G, kLane ? 0 : M, T, AND>(
-                                  a.inc_off, a.inc_ids, tin, tout, a.cap_by_tau,
-                                  lo, hi, wave, waves, act, act_next, a.stamp,
-                                  &n_ch, &n_ev, act_sum, sum_next, sp, buf, mbuf,
-                                  spread);
+    if constexpr (FR) {
+      // Sparse, up to 16 entries: a lane per r-clique.  The flagged r-cliques
+      // share few cache lines, so a step is a chain of misses (ids, values,
+      // ids again to notify); with 64 r-cliques per step instead of 16 there are
+      // a quarter of the chains.
+      // The members of a fixed set are many at once and lie anywhere: there a
+      // lane's list is a cache line of its own, and 16 r-cliques a step are quicker
+      // (see k_sweep_set).
+      constexpr bool kLane = G <= 4 && M == 4 && !SET;
+      uint8_t *mbuf = kLane ? flat->mask + threadIdx.x / kWave * kWaveList : nullptr;
+      sweep_sparse<K, kLane ? 1 : G, kLane ? 0 : M, T, AND>(
+                                    a.inc_off, a.inc_ids, tin, tout, a.cap_by_tau,
+                                    lo, hi, wave, waves, act, act_next, a.stamp,
+                                    &n_ch, &n_ev, act_sum, sum_next, sp, buf, mbuf,
+                                    spread);
+    }
   } else if (M == 4 && act == nullptr && act_next == nullptr) {
     if constexpr (M == 4)
       sweep_flat<K, G, T, AND>(a, lo, hi, block, nblocks, flat, &n_ch, &n_ev);
@@ -360,7 +357,7 @@ __device__ __forceinline__ void sweep_hubs(const SweepArgs &a, int64_t lo,
 constexpr int kRanges = kBinZero - kBinG64 + 2;
 constexpr int64_t kHubBlocks = 1024;
 constexpr int kHubMin = 1025;  // smallest d_s of kBinWave
-struct SmallBins {
+struct BinRanges {
   int64_t lo[kRanges], hi[kRanges];
   unsigned first[kRanges + 1];
 };
@@ -368,7 +365,7 @@ struct SmallBins {
 // The range of this workgroup, its share of it swept.  SET: a fixed set is
 // swept (PartialAND), its members flagged in act, and nothing notifies.
 template <int K, typename T, bool AND, bool FR, bool LONG, bool SET, typename Lds>
-__device__ __forceinline__ void sweep_range(const SweepArgs &a, const SmallBins &sb,
+__device__ __forceinline__ void sweep_range(const SweepArgs &a, const BinRanges &sb,
                                             Lds &lds, const uint8_t *act,
                                             uint8_t *act_next,
                                             const uint8_t *act_sum,
@@ -420,7 +417,7 @@ union RangeLds {
 // LONG: with the ranges of lists above 256.  8-bit values have them only where
 // wider ones were narrowed (see k_narrow in driver.hip).
 template <int K, typename T, bool AND, bool FR, bool LONG>
-__global__ __launch_bounds__(256, 6) void k_sweep_small(SweepArgs a, SmallBins sb) {
+__global__ __launch_bounds__(256, 6) void k_sweep_bins(SweepArgs a, BinRanges sb) {
   __shared__ RangeLds<T> lds;
   const unsigned long long pc = prev_changed(a);
   if (pc == 0) return;
@@ -434,9 +431,9 @@ __global__ __launch_bounds__(256, 6) void k_sweep_small(SweepArgs a, SmallBins s
 
 // In-place sweeps of a fixed set, without the notifying sweeps' registers
 // (100,000 members of a k-core of 1,000,000 vertices: 57 us a sweep in
-// k_sweep_small, 36 here).
+// k_sweep_bins, 36 here).
 template <int K, typename T, bool LONG>
-__global__ __launch_bounds__(256, 6) void k_sweep_set(SweepArgs a, SmallBins sb) {
+__global__ __launch_bounds__(256, 6) void k_sweep_set(SweepArgs a, BinRanges sb) {
   __shared__ RangeLds<T> lds;
   if (prev_changed(a) == 0) return;
   sweep_range<K, T, true, true, LONG, true>(a, sb, lds, a.act, nullptr, nullptr, nullptr,
@@ -467,7 +464,7 @@ void launch_bins(const KindState &ks, const SweepArgs &a, hipStream_t s) {
   // lanes per r-clique of the ranges after the hubs
   constexpr int kLanes[kRanges] = {256, 64, 64, 16, 4, 1};
   static_assert(kHubMin == kWaveList + 1 && kRanges == 6, "ranges and bins agree");
-  SmallBins sb{};
+  BinRanges sb{};
   int64_t total = 0;
   bool apart16 = false, apart32 = false;
   if constexpr (!FR && K <= 2) {
@@ -510,9 +507,9 @@ void launch_bins(const KindState &ks, const SweepArgs &a, hipStream_t s) {
           k_sweep_set<K, T, false><<<grid, 256, 0, s>>>(a, sb);
       }
     } else if (with_long) {
-      k_sweep_small<K, T, AND, FR, true><<<grid, 256, 0, s>>>(a, sb);
+      k_sweep_bins<K, T, AND, FR, true><<<grid, 256, 0, s>>>(a, sb);
     } else {
-      k_sweep_small<K, T, AND, FR, false><<<grid, 256, 0, s>>>(a, sb);
+      k_sweep_bins<K, T, AND, FR, false><<<grid, 256, 0, s>>>(a, sb);
     }
     ND_LAUNCHED();
   }
