@@ -61,13 +61,13 @@ __global__ __launch_bounds__(256, 6) void k_batch_sweep(
       act_next = G.act[(local + 1) & 1];
       sum_next = G.act_sum[(local + 1) & 1];
       if (threadIdx.x == 0) a.stats->notified = 1;
-      if (G.slack != nullptr) {
-        sp.slack = G.slack;
-        sp.lost = G.act[local & 1];
-        sp.lost_next = act_next;
-        sp.shift = (int)G.lost_shift;
-      }
+      sp.slack = G.slack;
     }
+  }
+  if (FR) {  // read only while slack is kept
+    sp.lost = G.act[local & 1];
+    sp.lost_next = G.act[(local + 1) & 1];
+    sp.shift = (int)G.lost_shift;
   }
   int type = tile.type, list = kWaveList;
   if (sizeof(T) == 2 && type == kBinWave && tile.hi - tile.lo >= kWaveTile) {

@@ -1063,15 +1063,13 @@ __device__ bool update_hub(const int64_t *__restrict__ inc_off,
     }
   }
   const bool ch = h != told;
-  auto store = [&] {
-    if (t != 0) return;
-    store_tau<T, AND>(tau_out + R, h, ch);
-    if (FR && sp.slack) ((T *)sp.slack)[R] = slack_word<T>(ch, ge, c);
-  };
   const bool notifies = FR && ch && act_next != nullptr;
-  // AND with support counting notifies before R's value is written (notify)
-  const bool first = AND && sp.slack != nullptr && notifies;
-  if (!first) store();
+  // AND with support counting notifies before R's value is written (notify; with
+  // k = 1 S has no third member)
+  const bool first = AND && K > 1 && sp.slack != nullptr && notifies;
+  if (t == 0 && !first) store_tau<T, AND>(tau_out + R, h, ch);
+  if (FR && sp.slack && t == 0)
+    ((T *)sp.slack)[R] = slack_word<T>(ch, ge, c);
   if (notifies) {
     const uint8_t next = stamp == 255 ? 1 : stamp + 1;
     if ((!AND || sp.slack) && t == 0)
@@ -1081,7 +1079,7 @@ __device__ bool update_hub(const int64_t *__restrict__ inc_off,
   }
   if (first) {
     __syncthreads();  // every thread has read
-    store();
+    if (t == 0) store_tau<T, AND>(tau_out + R, h, true);
   }
   __syncthreads();
   return t == 0 && ch;

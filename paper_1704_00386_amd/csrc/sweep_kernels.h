@@ -38,12 +38,12 @@ __device__ __forceinline__ void frontier_mode(const SweepArgs &a,
   *sum_next = notify ? a.act_sum_next : nullptr;
   if (a.sums_after != 0 && before >= a.sums_after)
     *sum_next = nullptr;  // k_group_sums writes them
-  if (notify) {  // slack is kept from the first notifying sweep on
-    sp->slack = a.slack;
-    sp->lost = a.lost;
-    sp->lost_next = a.lost_next;
-    sp->shift = a.lost_shift;
-  }
+  // Slack is kept from the first notifying sweep on.  (The rest without a branch,
+  // which keeps it in scalar registers; none is read while slack is NULL.)
+  sp->slack = notify ? a.slack : nullptr;
+  sp->lost = a.lost;
+  sp->lost_next = a.lost_next;
+  sp->shift = a.lost_shift;
   if (notify && blockIdx.x == 0 && threadIdx.x == 0) a.stats->notified = 1;
 }
 
@@ -258,7 +258,7 @@ __device__ __forceinline__ void sweep_bin(const SweepArgs &a, int64_t lo,
       // a quarter of the chains.
       // The members of a fixed set are many at once and lie anywhere: there a
       // lane's list is a cache line of its own, and 16 r-cliques a step are quicker
-      // (see k_sweep_set).
+      // (see k_sweep_bins).
       constexpr bool kLane = G <= 4 && M == 4 && !SET;
       uint8_t *mbuf = kLane ? flat->mask + threadIdx.x / kWave * kWaveList : nullptr;
       sweep_sparse<K, kLane ? 1 : G, kLane ? 0 : M, T, AND>(
@@ -362,82 +362,66 @@ struct BinRanges {
   unsigned first[kRanges + 1];
 };
 
-// The range of this workgroup, its share of it swept.  SET: a fixed set is
-// swept (PartialAND), its members flagged in act, and nothing notifies.
-template <int K, typename T, bool AND, bool FR, bool LONG, bool SET, typename Lds>
-__device__ __forceinline__ void sweep_range(const SweepArgs &a, const BinRanges &sb,
-                                            Lds &lds, const uint8_t *act,
-                                            uint8_t *act_next,
-                                            const uint8_t *act_sum,
-                                            uint8_t *sum_next, const Support &sp,
-                                            bool spread) {
-  int i = 0;
-  while (i + 1 < kRanges && blockIdx.x >= sb.first[i + 1]) i++;
-  const int64_t block = blockIdx.x - sb.first[i];
-  const int64_t nblocks = sb.first[i + 1] - sb.first[i];
-  const int64_t lo = sb.lo[i], hi = sb.hi[i];
-  if constexpr (LONG) {
-    if (i == 0) {
-      sweep_hubs<K, T, AND, FR>(a, lo, hi, block, nblocks, act, act_next, sum_next,
-                                sp, lds.hub);
-      return;
-    }
-    if (i == 1) {
-      sweep_bin<K, 64, 0, T, AND, FR, SET>(a, lo, hi, block, nblocks, act, act_next,
-                                           act_sum, sum_next, sp, &lds.flat, spread);
-      return;
-    }
-  }
-  switch (kBinG64 + i - 2) {
-    case kBinG64:
-      sweep_bin<K, 64, 4, T, AND, FR, SET>(a, lo, hi, block, nblocks, act, act_next,
-                                           act_sum, sum_next, sp, &lds.flat, spread);
-      break;
-    case kBinG16:
-      sweep_bin<K, 16, 4, T, AND, FR, SET>(a, lo, hi, block, nblocks, act, act_next,
-                                           act_sum, sum_next, sp, &lds.flat, spread);
-      break;
-    case kBinG4:
-      sweep_bin<K, 4, 4, T, AND, FR, SET>(a, lo, hi, block, nblocks, act, act_next,
-                                          act_sum, sum_next, sp, &lds.flat, spread);
-      break;
-    default:  // kBinG1
-      sweep_bin<K, 1, 4, T, AND, FR, SET>(a, lo, hi, block, nblocks, act, act_next,
-                                          act_sum, sum_next, sp, &lds.flat, spread);
-      break;
-  }
-}
-
-template <typename T>
-union RangeLds {
-  FlatLds<T> flat;
-  HubLds hub;
-};
-
 // LONG: with the ranges of lists above 256.  8-bit values have them only where
-// wider ones were narrowed (see k_narrow in driver.hip).
-template <int K, typename T, bool AND, bool FR, bool LONG>
+// wider ones were narrowed (see k_narrow in driver.hip).  SET: in-place sweeps of
+// a fixed set (PartialAND), its members flagged in act, without the notifying
+// sweeps' registers (100,000 members of a k-core of 1,000,000 vertices: 57 us a
+// sweep as a frontier's, 36 so).
+template <int K, typename T, bool AND, bool FR, bool LONG, bool SET>
 __global__ __launch_bounds__(256, 6) void k_sweep_bins(SweepArgs a, BinRanges sb) {
-  __shared__ RangeLds<T> lds;
+  __shared__ union {
+    FlatLds<T> flat;
+    HubLds hub;
+  } lds;
   const unsigned long long pc = prev_changed(a);
   if (pc == 0) return;
   const uint8_t *act = nullptr, *act_sum = nullptr;
   uint8_t *act_next = nullptr, *sum_next = nullptr;
   Support sp;
-  if (FR) frontier_mode(a, pc, &act, &act_next, &act_sum, &sum_next, &sp);
-  sweep_range<K, T, AND, FR, LONG, false>(a, sb, lds, act, act_next, act_sum, sum_next,
-                                          sp, FR && pc < a.spread_below);
-}
-
-// In-place sweeps of a fixed set, without the notifying sweeps' registers
-// (100,000 members of a k-core of 1,000,000 vertices: 57 us a sweep in
-// k_sweep_bins, 36 here).
-template <int K, typename T, bool LONG>
-__global__ __launch_bounds__(256, 6) void k_sweep_set(SweepArgs a, BinRanges sb) {
-  __shared__ RangeLds<T> lds;
-  if (prev_changed(a) == 0) return;
-  sweep_range<K, T, true, true, LONG, true>(a, sb, lds, a.act, nullptr, nullptr, nullptr,
-                                            Support(), false);
+  if constexpr (SET)
+    act = a.act;
+  else if (FR)
+    frontier_mode(a, pc, &act, &act_next, &act_sum, &sum_next, &sp);
+  const bool spread = FR && !SET && pc < a.spread_below;
+  int i = 0;
+  while (i + 1 < kRanges && blockIdx.x >= sb.first[i + 1]) i++;
+  const int64_t block = blockIdx.x - sb.first[i];
+  const int64_t nblocks = sb.first[i + 1] - sb.first[i];
+  if constexpr (LONG) {
+    if (i == 0) {
+      sweep_hubs<K, T, AND, FR>(a, sb.lo[0], sb.hi[0], block, nblocks, act,
+                                act_next, sum_next, sp, lds.hub);
+      return;
+    }
+    if (i == 1) {
+      sweep_bin<K, 64, 0, T, AND, FR, SET>(a, sb.lo[1], sb.hi[1], block, nblocks, act,
+                                           act_next, act_sum, sum_next, sp, &lds.flat,
+                                           spread);
+      return;
+    }
+  }
+  switch (kBinG64 + i - 2) {
+    case kBinG64:
+      sweep_bin<K, 64, 4, T, AND, FR, SET>(a, sb.lo[i], sb.hi[i], block, nblocks, act,
+                                           act_next, act_sum, sum_next, sp, &lds.flat,
+                                           spread);
+      break;
+    case kBinG16:
+      sweep_bin<K, 16, 4, T, AND, FR, SET>(a, sb.lo[i], sb.hi[i], block, nblocks, act,
+                                           act_next, act_sum, sum_next, sp, &lds.flat,
+                                           spread);
+      break;
+    case kBinG4:
+      sweep_bin<K, 4, 4, T, AND, FR, SET>(a, sb.lo[i], sb.hi[i], block, nblocks, act,
+                                          act_next, act_sum, sum_next, sp, &lds.flat,
+                                          spread);
+      break;
+    default:  // kBinG1
+      sweep_bin<K, 1, 4, T, AND, FR, SET>(a, sb.lo[i], sb.hi[i], block, nblocks, act,
+                                          act_next, act_sum, sum_next, sp, &lds.flat,
+                                          spread);
+      break;
+  }
 }
 
 // A full sweep that notifies nobody over one bin of the longer lists, M values
@@ -500,16 +484,15 @@ void launch_bins(const KindState &ks, const SweepArgs &a, hipStream_t s) {
     const bool with_long = sizeof(T) > 1 || sb.hi[1] > 0;
     const unsigned grid = (unsigned)total;
     if (AND && FR && a.fixed_set) {
-      if constexpr (AND && FR) {
-        if (with_long)
-          k_sweep_set<K, T, true><<<grid, 256, 0, s>>>(a, sb);
-        else
-          k_sweep_set<K, T, false><<<grid, 256, 0, s>>>(a, sb);
-      }
+      constexpr bool kSet = AND && FR;
+      if (with_long)
+        k_sweep_bins<K, T, AND, FR, true, kSet><<<grid, 256, 0, s>>>(a, sb);
+      else
+        k_sweep_bins<K, T, AND, FR, false, kSet><<<grid, 256, 0, s>>>(a, sb);
     } else if (with_long) {
-      k_sweep_bins<K, T, AND, FR, true><<<grid, 256, 0, s>>>(a, sb);
+      k_sweep_bins<K, T, AND, FR, true, false><<<grid, 256, 0, s>>>(a, sb);
     } else {
-      k_sweep_bins<K, T, AND, FR, false><<<grid, 256, 0, s>>>(a, sb);
+      k_sweep_bins<K, T, AND, FR, false, false><<<grid, 256, 0, s>>>(a, sb);
     }
     ND_LAUNCHED();
   }
