@@ -46,6 +46,12 @@ constexpr int64_t kWatchGathers = (int64_t)1 << 26;  // see watch in sweep_loop
 constexpr int64_t kWatchApart = (int64_t)1 << 24;
 // Sweeps enqueued one by one for narrowing's sake (see sweep_loop).
 constexpr int64_t kNarrowSweeps = 8;
+// Workgroups per CU once few r-cliques change: as many as stay resident by
+// their LDS.  The waves' shares are lanes of one load then, and a second round of
+// workgroups only waits for the first (path of 1,000,000 vertices, two changes a
+// sweep: 14.1 us a sweep at 16, 10.8 at 8; dense sweeps want more of them, 17.9M
+// incidences 2.15 ms at 16 and 2.22 at 8).
+constexpr int kGridTail = 8;
 constexpr int kGridPerCu = 64;    // sweep workgroups per CU (they stride;
                                   // measured best of 8..64 and uncapped)
 
@@ -329,7 +335,8 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
   bool narrowing = tb > 1 && !indicator && !fixed_set && ks.P * ks.k >= kWatchGathers &&
                    (!and_mode || b.slack != nullptr);
   if (narrowing) chunk = 1;
-  int64_t t = 0;  // sweeps enqueued
+  bool tail = false;  // few r-cliques changed in the last sweep read back
+  int64_t t = 0;      // sweeps enqueued
   int64_t sweeps = 0, updates = 0;
   bool converged = false, stop_ratio = false, stop_cb = false;
   hipEvent_t *ev = ctx->ev;  // ev[0..1]: whole loop; ev[2..3]: one sweep
@@ -366,7 +373,7 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
       a.stats = b.ring + (t % ring_len);
       a.prev = t > 0 ? b.ring + ((t - 1) % ring_len) : nullptr;
       a.cap_by_tau = 1;
-      a.grid_cap = ctx->num_cu * grid_per_cu;
+      a.grid_cap = ctx->num_cu * (tail ? std::min(grid_per_cu, kGridTail) : grid_per_cu);
       if (flags && !(plain && i == 0)) {
         a.act = b.act[t & 1];
         a.act_next = b.act[(t + 1) & 1];
@@ -450,6 +457,8 @@ nd_status sweep_loop(nd_graph *g, const KindState &ks, nd_opts opts,
       tb /= 2;
       narrowing = tb > 1;
     }
+    tail = frontier && hst[(t - 1) % ring_len].notified &&
+           hst[(t - 1) % ring_len].changed < kSpreadBelow;
     // once few r-cliques change, notifications keep the summaries themselves
     if (sums_after != 0 && hst[(t - 1) % ring_len].notified &&
         hst[(t - 1) % ring_len].changed < sums_after)
