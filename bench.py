@@ -159,8 +159,8 @@ def measured_traffic():
     return rec.get("hbm_bytes_per_sweep")
 
 
-# k_sweep_*<..., AND, frontier, lists above 256>
-FULL_SWEEP_SUFFIX = (", false, false, false>", ", false, false, true>")
+# k_sweep_bins<..., AND, frontier, lists above 256, fixed set>
+FULL_SWEEP_SUFFIX = (", false, false, false, false>", ", false, false, true, false>")
 HEADLINE_FLAGS = "--only-headline --steps 2 --warmup 1 --calib-copy"
 
 
@@ -193,9 +193,10 @@ def summarize_profiles(trace_csv: str, fetch_csv: str, write_csv: str) -> None:
              "The run holds a 1 GiB device copy, one warm-up and two timed steps (build + prepare +",
              "SND with the notification frontier until exact), the full-sweep roofline leg (4 SND",
              "sweeps recomputing every r-clique), AND with the frontier, and the ceiling kernels.",
-             "`k_sweep_bins<k, tau type, AND, frontier, lists above 256>` sweeps every bin in one",
-             "launch; `<3, unsigned char, false, false, false>` is a full sweep that notifies nobody",
-             "(tau in 8 bits: every d_s of this workload is below 256), in the SND steps too.", "",
+             "`k_sweep_bins<k, tau type, AND, frontier, lists above 256, fixed set>` sweeps every bin",
+             "in one launch; `<3, unsigned char, false, false, false, false>` is a full sweep that",
+             "notifies nobody (tau in 8 bits: every d_s of this workload is below 256), in the SND",
+             "steps too.", "",
              "| % | calls | total ms | avg us | kernel |", "|---:|---:|---:|---:|---|"]
     full_avg = 0.0
     for r in sorted(rows, key=lambda r: -float(r["TotalDurationNs"]))[:36]:
@@ -205,7 +206,7 @@ def summarize_profiles(trace_csv: str, fetch_csv: str, write_csv: str) -> None:
             full_avg += avg
         lines.append(f"| {100 * float(r['TotalDurationNs']) / tot:.1f} | {r['Calls']} | "
                      f"{float(r['TotalDurationNs']) / 1e6:.2f} | {avg:.1f} | `{name}` |")
-    lines += ["", f"Full sweep = the `k_sweep_*<..., false, false, ..>` launches of a sweep: "
+    lines += ["", f"Full sweep = the `k_sweep_bins<..., false, false, ..>` launches of a sweep: "
               f"{full_avg:.0f} us per sweep (sum of their averages)."]
     open(os.path.join(out_dir, "kernel_trace_sbm_nucleus34.md"), "w").write("\n".join(lines) + "\n")
 

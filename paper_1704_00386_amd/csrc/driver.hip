@@ -49,8 +49,8 @@ constexpr int64_t kNarrowSweeps = 8;
 // Workgroups per CU once few r-cliques change: as many as stay resident by
 // their LDS.  The waves' shares are lanes of one load then, and a second round of
 // workgroups only waits for the first (path of 1,000,000 vertices, two changes a
-// sweep: 14.1 us a sweep at 16, 10.8 at 8; dense sweeps want more of them, 17.9M
-// incidences 2.15 ms at 16 and 2.22 at 8).
+// sweep: 14.1 us a sweep at 16, 10.8 at 8; dense sweeps want more of them, k-core of
+// 32M incidences 2.15 ms at 16 and 2.22 at 8).
 constexpr int kGridTail = 8;
 constexpr int kGridPerCu = 64;    // sweep workgroups per CU (they stride;
                                   // measured best of 8..64 and uncapped)

@@ -387,7 +387,7 @@ struct SweepArgs {
   void *lost_next;
   int lost_shift;
   // PartialAND (Section 4.3, end): act marks a fixed set (stamp 1) that is
-  // the only thing recomputed, every sweep, and nothing notifies.
+  // the only thing recomputed, every sweep, and nothing notifies (in place).
   int fixed_set;
   // At most this many workgroups per lanes-per-r-clique kernel (they stride
   // over the rest of the bin); 0: one pass, no cap.

@@ -353,7 +353,8 @@ __device__ __forceinline__ void sweep_hubs(const SweepArgs &a, int64_t lo,
 // the other took 65 + 14 + 66 us a sweep on a 1.7M-vertex k-core with 35,000
 // neighbours at most).  Range 0 are the hubs (d_s > 1024), range 1 the lists
 // of 257..1024, range i the bin kBinG64 + i - 2; range i has the workgroups
-// [first[i], first[i+1]).
+// [first[i], first[i+1]).  (Bins of 513..2047 that fill the GPU by themselves are
+// left to k_sweep_regs in full sweeps that notify nobody.)
 constexpr int kRanges = kBinZero - kBinG64 + 2;
 constexpr int64_t kHubBlocks = 1024;
 constexpr int kHubMin = 1025;  // smallest d_s of kBinWave
