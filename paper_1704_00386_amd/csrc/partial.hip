@@ -74,10 +74,8 @@ struct EgoArgs {
   int take;                  // so many at a time
 };
 
-// Queries dealt out by class (powers of two of d_s, largest first), all zero to
-// start with.
-
-// Queries dealt out by class (powers of two of d_s, largest first).
+// Queries dealt out by class (powers of two of d_s, largest first); all zero to
+// start with where there are many.
 struct EgoDeal {
   unsigned long long total[kEgoClasses];   // queries per class
   unsigned long long placed[kEgoClasses];
